@@ -15,7 +15,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libtfg.so")
-SOURCES = ["csr.hip", "norm.hip", "aggregate.hip", "aggregate_short.hip", "softmax.hip",
+SOURCES = ["csr.hip", "norm.hip", "aggregate.hip", "slots_sum.hip", "slots_max.hip",
+           "slots_heads.hip", "slots_masked.hip", "softmax.hip",
            "gat.hip", "pool.hip", "batch.hip", "backward.hip", "api.cpp"]
 # measurement probes for the benchmark (include/tfg_probe.h), a library of their own
 PROBE_LIB = os.path.join(HERE, "libtfg_probe.so")

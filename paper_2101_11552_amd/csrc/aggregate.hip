@@ -1,7 +1,7 @@
 // Message aggregation over the CSR-by-target graph (gfx950, wave64):
 // out[t, :] = reduce over the edges k of row t of w_k * x[col_k, :].
-// The row kernel (spmm_rows, spmm.h) runs over the work items of the graph's
-// plan; long rows and source-part segments leave partial rows that
+// The work items of the graph's plan go to the slot kernel (slots.h) or to
+// spmm_wide; long rows and source-part segments leave partial rows that
 // fixup_rows combines in a fixed order. No floating-point atomics: every
 // output is reproducible bit for bit.
 #include <cstdlib>
@@ -25,34 +25,54 @@ void* g_scratch_addr[kMaxDevices] = {};
 
 using namespace rows;
 
-// Combines the partial results of each split row in chunk order: sums with
-// kFixAcc interleaved accumulators combined pairwise, maxima with the tie rule.
+// Combines the partial results of each split row in chunk order, kFixAcc
+// partial rows in flight: sums with one accumulator each, combined pairwise,
+// maxima with the tie rule. A lane covers V consecutive features; the last
+// lane with features of its own steps back to end at F (it repeats some of
+// its neighbour's).
 constexpr int kFixAcc = 8;
-// Lanes cover V consecutive features each.
 template <bool MAX, int V>
 __global__ __launch_bounds__(kItemBlock) void fixup_rows(const SplitRow* __restrict__ split,
                                                      int n_split, const float* __restrict__ part,
                                                      const int* __restrict__ part_arg, int F,
                                                      int mean, float* __restrict__ out,
-                                                     int* __restrict__ argout, Epilogue ep) {
-  const int wid = uniform(blockIdx.x * (kItemBlock / kWave) + threadIdx.x / kWave);
-  if (wid >= n_split) return;
+                                                     int* __restrict__ argout, Epilogue ep,
+                                                     int lps) {
   const int lane = threadIdx.x & (kWave - 1);
-  const SplitRow* sr = split + wid;
-  const int row = uniform(sr->row), slot0 = uniform(sr->slot0), nch = uniform(sr->nchunks);
-  const int deg = uniform(sr->deg);
-  for (int f = lane * V; f < F; f += kWave * V) {
+  const int wid = blockIdx.x * (kWave / lps) + lane / lps;  // no cross-lane traffic below
+  if (wid >= n_split) return;
+  const SplitRow sr = split[wid];
+  const int row = sr.row, slot0 = sr.slot0, nch = sr.nchunks, deg = sr.deg;
+  for (int fw = (lane & (lps - 1)) * V; fw < F; fw += lps * V) {
+    const int f = min(fw, F - V);
     if constexpr (MAX) {
+      constexpr int U = kFixAcc / 2;  // two rows each: values and edge ids
+      float best[V];
+      int a[V];
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        float best = 0.0f;
-        int a = -1;
-        for (int j = 0; j < nch; ++j)
-          max_combine(best, a, part[(int64_t)(slot0 + j) * F + f + v],
-                      part_arg[(int64_t)(slot0 + j) * F + f + v]);
-        out[(int64_t)row * F + f + v] = a < 0 ? 0.0f : best;
-        if (argout != nullptr) argout[(int64_t)row * F + f + v] = a;
+        best[v] = 0.0f;
+        a[v] = -1;
       }
+      for (int j = 0; j < nch; j += U) {
+        float t[U][V];
+        int e[U][V];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+          // places past the row's partials repeat the last one, which never wins again
+          const int64_t o = (int64_t)(slot0 + min(j + i, nch - 1)) * F + f;
+          load_row_once<V>(part + o, t[i]);
+          load_irow<V>(part_arg + o, e[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+#pragma unroll
+          for (int v = 0; v < V; ++v) max_combine(best[v], a[v], t[i][v], e[i][v]);
+      }
+#pragma unroll
+      for (int v = 0; v < V; ++v) best[v] = a[v] < 0 ? 0.0f : best[v];
+      store_row<V>(out + (int64_t)row * F + f, best);
+      if (argout != nullptr) store_irow<V>(argout + (int64_t)row * F + f, a);
     } else {
       // kFixAcc partial rows in flight, one accumulator each
       float a4[kFixAcc][V];
@@ -94,32 +114,43 @@ __global__ __launch_bounds__(kItemBlock) void fixup_rows(const SplitRow* __restr
   }
 }
 
-// Sum and mean with scalar edge ids: one wavefront per work item, SL edge
-// slots of 64 / SL lanes (SL = 1 or 2), lane l of a slot holding columns
-// V l .. V l + V - 1 of a 64 V / SL-column pass. The item's edge ids and
-// weights come in with one coalesced load per 64 edges and are read out edge
-// by edge into scalar registers (readlane); the scalar unit forms each row's
-// 32-bit byte offset (NARROW: the table below 4 GB; else 64-bit per lane), so
-// a lane adds its own offset and selects between the slots' values, and the
-// load takes the table's base from scalar registers. Edges go in groups of U
-// per slot, every load of a group issued before its first multiply-add; the
-// last group repeats the item's last edge in its unused places (a row already
-// loaded) and adds only the item's own edges. One accumulator chain per
-// group place, combined pairwise, then across the slots.
-template <int SL>
-__device__ __forceinline__ int pick(int a, int b, int slot) {
-  if constexpr (SL == 1) return a;
-  else return slot ? b : a;
-}
-
-template <int V, int SL, int U, bool FULL, bool NARROW>
-__device__ __forceinline__ void wide_pass(int kbeg, int kend, const int* __restrict__ col,
-                                          const int* __restrict__ perm,
-                                          const float* __restrict__ w, int w_by_perm,
-                                          const char* __restrict__ xb, int64_t row_bytes,
-                                          unsigned lane_off, int slot, bool fok,
-                                          float (&acc)[U][V]) {
+// Sum and mean over the part plan with scalar edge ids: one wavefront per work
+// item, two edge slots of 32 lanes, lane l of a slot holding columns 4 l ..
+// 4 l + 3 of a 128-column row. The item's edge ids and weights come in with one
+// coalesced load per 64 edges and are read out edge by edge into scalar
+// registers (readlane); the scalar unit forms each row's 32-bit byte offset
+// (NARROW: the table below 2 GB; else 64-bit per lane), so a lane adds its own
+// offset and selects between the slots' values, and the load takes the table's
+// base from scalar registers. Edges go in groups of kWideU per slot (4: 3.51 ms
+// on the power-law graph; 8: 3.69, 2: 3.51), every load of a group issued
+// before its first multiply-add; the last group repeats the item's last edge in
+// its unused places (a row already loaded) and adds only the item's own edges.
+// One accumulator chain per group place, combined pairwise, then across the
+// slots.
+constexpr int kWideU = 4;
+template <bool NARROW>
+__global__ __launch_bounds__(kRowBlock) void spmm_wide(
+    const WorkItem* __restrict__ items, int n_items, const int* __restrict__ col,
+    const int* __restrict__ perm, const float* __restrict__ w, int w_by_perm,
+    const float* __restrict__ x, int64_t ldx, int F, int mean, float* __restrict__ out,
+    float* __restrict__ part, Epilogue ep) {
+  constexpr int V = 4, SL = 2, U = kWideU, LPS = kWave / SL;
+  const int wid = uniform(blockIdx.x * (kRowBlock / kWave) + threadIdx.x / kWave);
+  if (wid >= n_items) return;
   const int lane = lane_id();
+  const int slot = lane / LPS, sl = lane % LPS;
+  const WorkItem* itp = items + wid;
+  const int row = uniform(itp->row), kbeg = uniform(itp->kbeg), kend = uniform(itp->kend);
+  const int pslot = uniform(itp->slot);
+  const char* xb = reinterpret_cast<const char*>(x);
+  const int64_t row_bytes = ldx * (int64_t)sizeof(float);
+  const int f = sl * V;
+  const unsigned lane_off = (unsigned)f * (unsigned)sizeof(float);
+  float acc[U][V];
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int v = 0; v < V; ++v) acc[u][v] = 0.0f;
   for (int kb = kbeg; kb < kend; kb += kWave) {
     const int n = min(kWave, kend - kb);
     const bool lok = lane < n;
@@ -135,16 +166,14 @@ __device__ __forceinline__ void wide_pass(int kbeg, int kend, const int* __restr
       for (int u = 0; u < U; ++u) {
         const int ja = j0 + u * SL;
         const int ca = __builtin_amdgcn_readlane(cj, tail ? min(ja, n - 1) : ja);
-        const int cb = SL > 1 ? __builtin_amdgcn_readlane(cj, tail ? min(ja + 1, n - 1) : ja + 1) : 0;
-        if (FULL || fok) {
-          if constexpr (NARROW) {
-            const unsigned off =
-                (unsigned)pick<SL>(ca * (int)row_bytes, cb * (int)row_bytes, slot) + lane_off;
-            load_row<V>(reinterpret_cast<const float*>(xb + off), xv[u]);
-          } else {
-            const int64_t off = (int64_t)pick<SL>(ca, cb, slot) * row_bytes + lane_off;
-            load_row<V>(reinterpret_cast<const float*>(xb + off), xv[u]);
-          }
+        const int cb = __builtin_amdgcn_readlane(cj, tail ? min(ja + 1, n - 1) : ja + 1);
+        if constexpr (NARROW) {
+          const unsigned off =
+              (unsigned)(slot ? cb * (int)row_bytes : ca * (int)row_bytes) + lane_off;
+          load_row<V>(reinterpret_cast<const float*>(xb + off), xv[u]);
+        } else {
+          const int64_t off = (int64_t)(slot ? cb : ca) * row_bytes + lane_off;
+          load_row<V>(reinterpret_cast<const float*>(xb + off), xv[u]);
         }
       }
 #pragma unroll
@@ -152,9 +181,9 @@ __device__ __forceinline__ void wide_pass(int kbeg, int kend, const int* __restr
         const int ja = j0 + u * SL;
         if (tail && ja >= n) continue;  // uniform
         const int wa = __builtin_amdgcn_readlane(wj, ja);
-        const int wb = SL > 1 ? __builtin_amdgcn_readlane(wj, tail ? min(ja + 1, n - 1) : ja + 1) : 0;
-        const float wt = __int_as_float(pick<SL>(wa, wb, slot));
-        if ((FULL || fok) && (!tail || ja + slot < n))
+        const int wb = __builtin_amdgcn_readlane(wj, tail ? min(ja + 1, n - 1) : ja + 1);
+        const float wt = __int_as_float(slot ? wb : wa);
+        if (!tail || ja + slot < n)
 #pragma unroll
           for (int v = 0; v < V; ++v) acc[u][v] = __builtin_fmaf(wt, xv[u][v], acc[u][v]);
       }
@@ -163,112 +192,112 @@ __device__ __forceinline__ void wide_pass(int kbeg, int kend, const int* __restr
     for (; j0 + U * SL <= n; j0 += U * SL) group(j0, false);
     if (j0 < n) group(j0, true);
   }
-}
-
-template <int V, int SL, int U, bool NARROW>
-__global__ __launch_bounds__(kRowBlock) void spmm_wide(
-    const WorkItem* __restrict__ heavy, int n_heavy, const WorkItem* __restrict__ light,
-    int n_light, const int* __restrict__ col, const int* __restrict__ perm,
-    const float* __restrict__ w, int w_by_perm, const float* __restrict__ x, int64_t ldx, int F,
-    int mean, float* __restrict__ out, float* __restrict__ part, Epilogue ep) {
-  constexpr int LPS = kWave / SL;  // lanes per slot
-  constexpr int FC = LPS * V;      // columns per pass
-  const int wid = uniform(blockIdx.x * (kRowBlock / kWave) + threadIdx.x / kWave);
-  if (wid >= n_heavy + n_light) return;
-  const int lane = lane_id();
-  const int slot = lane / LPS, sl = lane % LPS;
-  const WorkItem* itp = wid < n_heavy ? heavy + wid : light + (wid - n_heavy);
-  const int row = uniform(itp->row), kbeg = uniform(itp->kbeg), kend = uniform(itp->kend);
-  const int pslot = uniform(itp->slot);
-  const char* xc = reinterpret_cast<const char*>(x);
-  const int64_t row_bytes = ldx * (int64_t)sizeof(float);
-  for (int f0 = 0; f0 < F; f0 += FC) {
-    const int f = f0 + sl * V;
-    const bool fok = f < F;
-    float acc[U][V];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+  for (int step = 1; step < U; step <<= 1)
 #pragma unroll
-      for (int v = 0; v < V; ++v) acc[u][v] = 0.0f;
-    // the pass's column offset in scalar registers, the lane's in a 32-bit offset
-    const char* xb = xc + (int64_t)f0 * (int64_t)sizeof(float);
-    const unsigned lane_off = (unsigned)(sl * V) * (unsigned)sizeof(float);
-    if (f0 + FC <= F)
-      wide_pass<V, SL, U, true, NARROW>(kbeg, kend, col, perm, w, w_by_perm, xb, row_bytes,
-                                        lane_off, slot, fok, acc);
-    else
-      wide_pass<V, SL, U, false, NARROW>(kbeg, kend, col, perm, w, w_by_perm, xb, row_bytes,
-                                         lane_off, slot, fok, acc);
+    for (int u = 0; u + step < U; u += 2 * step)
 #pragma unroll
-    for (int step = 1; step < U; step <<= 1)
+      for (int v = 0; v < V; ++v) acc[u][v] += acc[u + step][v];
 #pragma unroll
-      for (int u = 0; u + step < U; u += 2 * step)
+  for (int v = 0; v < V; ++v) acc[0][v] += __shfl_xor(acc[0][v], LPS);
+  if (slot != 0) return;
+  if (pslot < 0) {
+    if (mean && kend > kbeg) {
+      const float cnt = (float)(kend - kbeg);
 #pragma unroll
-        for (int v = 0; v < V; ++v) acc[u][v] += acc[u + step][v];
-#pragma unroll
-    for (int off = LPS; off < kWave; off <<= 1)
-#pragma unroll
-      for (int v = 0; v < V; ++v) acc[0][v] += __shfl_xor(acc[0][v], off);
-    if (slot != 0 || !fok) continue;
-    if (pslot < 0) {
-      if (mean && kend > kbeg) {
-        const float cnt = (float)(kend - kbeg);
-#pragma unroll
-        for (int v = 0; v < V; ++v) acc[0][v] = acc[0][v] / cnt;
-      }
-      apply_epilogue<V>(ep, row, f, acc[0]);
-      store_row<V>(out + (int64_t)row * F + f, acc[0]);
-    } else {
-      // partial rows are read back once, by the fix-up, long after: streamed
-      // past the L2, which they would otherwise share with the gathered rows
-      store_row<V>(part + (int64_t)pslot * F + f, acc[0]);
+      for (int v = 0; v < V; ++v) acc[0][v] = acc[0][v] / cnt;
     }
+    apply_epilogue<V>(ep, row, f, acc[0]);
+    store_row<V>(out + (int64_t)row * F + f, acc[0]);
+  } else {
+    // partial rows are read back once, by the fix-up, long after: streamed
+    // past the L2, which they would otherwise share with the gathered rows
+    store_row<V>(part + (int64_t)pslot * F + f, acc[0]);
   }
 }
 
-// Whether the sum / mean goes through spmm_wide: rows of at least 64
-// columns (every lane busy), one weight per edge; the layout: two slots of
-// four columns per lane where 128 columns fit the alignment, else one slot of
-// two or one. TFG_WIDE_ROWS=0 keeps every aggregation on spmm_rows.
-struct WideShape {
-  int v, slots;
-};
-WideShape wide_shape(int64_t F, int vec, bool sum_like, bool heads, bool masked) {
-  if (!sum_like || heads || masked || F < kWave) return {0, 0};
+// Whether a sum or mean over the part plan goes through spmm_wide: rows of
+// 128 columns that its lanes read with 16-byte loads. There it beats a segment
+// per slot (3.49 against 3.67 ms on 114.6M edges; both slots on one segment keep
+// fewer segments in flight, and the gathered window stays closer to the L2s);
+// on the row plan and at other widths the slots are as fast or faster (256
+// columns 2.39 against 2.41 ms on 23M edges, 200 columns 1.95 against 2.31).
+// TFG_WIDE_ROWS=0 keeps every aggregation on the slots.
+bool use_wide(int64_t F, bool aligned, bool plain_sum, bool part_plan) {
+  if (!plain_sum || !aligned || !part_plan || F != 128) return false;
   if (const char* v = std::getenv("TFG_WIDE_ROWS"))
-    if (v[0] == '0') return {0, 0};
-  if (vec == 4 && F % 128 == 0) return {4, 2};
-  return {vec % 2 == 0 && F >= 2 * kWave ? 2 : 1, 1};
+    if (v[0] == '0') return false;
+  return true;
 }
 
-void launch_wide(WideShape ws, dim3 grid, hipStream_t s, const RowArgs& a, int64_t n_src) {
+void launch_wide(int n_items, hipStream_t s, const RowArgs& a, int64_t n_src) {
   // the whole table within 32-bit byte offsets of its base
   const bool narrow = (double)n_src * (double)a.ldx * 4.0 < 2147483648.0;
-#define TFG_WIDE(VV, SS, UU, NN)                                                       \
-  spmm_wide<VV, SS, UU, NN><<<grid, dim3(kRowBlock), 0, s>>>(                          \
-      a.heavy, a.n_heavy, a.light, a.n_light, a.col, a.perm, a.w, a.w_by_perm, a.x, a.ldx, \
-      a.F, a.mean, a.out, a.part, a.ep)
-  if (ws.slots == 2) {  // U = 4 (the power-law aggregation: 3.51 ms; U = 8: 3.69, U = 2: 3.51)
-    if (narrow) TFG_WIDE(4, 2, 4, true); else TFG_WIDE(4, 2, 4, false);
-  } else if (ws.v == 2) {
-    if (narrow) TFG_WIDE(2, 1, 8, true); else TFG_WIDE(2, 1, 8, false);
-  } else {
-    if (narrow) TFG_WIDE(1, 1, 8, true); else TFG_WIDE(1, 1, 8, false);
-  }
+  const dim3 grid((unsigned)n_items);
+#define TFG_WIDE(NN)                                                                          \
+  spmm_wide<NN><<<grid, dim3(kRowBlock), 0, s>>>(a.heavy, n_items, a.col, a.perm, a.w,        \
+                                                 a.w_by_perm, a.x, a.ldx, a.F, a.mean, a.out, \
+                                                 a.part, a.ep)
+  if (narrow) TFG_WIDE(true); else TFG_WIDE(false);
 #undef TFG_WIDE
 }
 
-template <bool SHORT>
-void dispatch_kind(bool mx, bool heads, int vec, int slots, dim3 grid, hipStream_t s,
-                   const RowArgs& a) {
-  if (mx && heads)
-    dispatch_vec<true, true, SHORT, false>(vec, slots, grid, s, a);
-  else if (mx)
-    dispatch_vec<true, false, SHORT, false>(vec, slots, grid, s, a);
-  else if (heads)
-    dispatch_vec<false, true, SHORT, false>(vec, slots, grid, s, a);
-  else
-    dispatch_vec<false, false, SHORT, false>(vec, slots, grid, s, a);
+// The slot aggregation (slots.h) over the plan's items: V columns per lane,
+// the fewest lanes per slot (a power of two, at least 4) that hold a row, and
+// per list the number of neighbouring slots that share an item.
+//
+// Row plan, items of over 32 edges: at least max(4, 32 / lanes) slots. The ids
+// and weights of an item are then read in longer runs: with one item per slot,
+// the id streams of a wavefront's 64 / lanes items fall out of the L1 between
+// rounds (16 columns on 23M edges, 4 lanes: 0.36 ms with one slot per item,
+// 0.29 / 0.26 / 0.24 with two, four, eight). 9..32 edges: two (16 columns on
+// 2.3M edges of rows of 14: 41.7 -> 38.6 us), one with per-head weights (64
+// columns: 102 -> 96 us). Part plan: one (segments of 16 edges, 64 columns: 0.50
+// ms, two slots 0.55). Beyond that, while the items leave part of the chip idle,
+// an item takes more slots until each has one round of edges.
+constexpr int kIdRound = 16;      // edges a slot takes per round of ids
+constexpr int kChipWaves = 8192;  // wavefronts in flight: 256 CUs x 4 SIMDs x 8
+void launch_slots(const Graph& g, const RowArgs& a, bool mx, bool heads, bool masked,
+                  bool part_plan, hipStream_t s) {
+  // (heads of columns that are no multiple of 4: a lane's columns stay in one head)
+  int v = a.F >= 4 ? 4 : 1;
+  if (heads && a.per_head % 4 != 0) v = a.per_head % 2 == 0 && !mx && !masked ? 2 : 1;
+  const int need = std::min((a.F + v - 1) / v, kWave);
+  int lps = 4;
+  while (lps < need) lps <<= 1;
+  const int slots = kWave / lps;
+  SlotLists L{};
+  // edges: of the list's longest item; least, total: see above (total items)
+  auto add = [&](int i, const WorkItem* items, int n, int edges, int least, int total) {
+    L.items[i] = items;
+    L.n[i] = n;
+    int sp = 1;
+    while (sp < slots && sp * kIdRound < edges &&
+           (sp < least || (int64_t)total * sp < (int64_t)kChipWaves * slots))
+      sp <<= 1;
+    L.split[i] = sp;
+    L.waves[i] = (int)(((int64_t)n * sp + slots - 1) / slots);
+  };
+  if (part_plan) {
+    add(0, a.heavy, a.n_heavy, g.chunk, 1, a.n_heavy);
+  } else {
+    const int total = a.n_heavy + g.n_long + g.n_short, least = std::max(4, 32 / lps);
+    add(0, a.heavy, a.n_heavy, g.chunk, least, total);
+    add(1, g.long_rows, g.n_over32, g.chunk, least, total);
+    add(2, g.long_rows + g.n_over32, g.n_long - g.n_over32, 32, heads ? 1 : 2, total);
+    add(3, g.short_rows, g.n_short, kShortRow, 1, total);
+  }
+  int waves = 0;
+  for (int i = 0; i < kSlotLists; ++i) waves += L.waves[i];
+  if (waves == 0) return;
+  // byte offsets in 32 bits: rows of x, and per-head weights (past the last item's
+  // end by up to a round: a margin of 2^20 rows)
+  const bool narrow = (double)g.N_src * (double)a.ldx * 4.0 < 2147483648.0 &&
+                      (!heads || ((double)g.E + 1048576.0) * (double)a.H * 4.0 < 4294967296.0);
+  if (masked) slots_masked(v, lps, narrow, L, waves, a, s);
+  else if (heads) slots_heads(mx, v, lps, narrow, L, waves, a, s);
+  else if (mx) slots_max(!part_plan && g.parts > 1, v, lps, narrow, L, waves, a, s);
+  else slots_sum(v, lps, narrow, L, waves, a, s);
 }
 
 }  // namespace
@@ -308,23 +337,10 @@ int launch_aggregate(const Graph& g, const float* w, int H, int w_order, const f
                      const int32_t* mask) {
   if (g.N == 0 || F == 0) return TFG_OK;
   if (mask != nullptr && reduce != TFG_SUM) return fail(TFG_ERR_INVALID_ARG, "masked max");
+  if (mask != nullptr && ldx != F) return fail(TFG_ERR_INVALID_ARG, "masked rows must be dense");
   const bool heads = H > 1 && w != nullptr;
-  const int per_head = (int)(F / H);
-  // every row of x, out (and h, mask) is read or written with v-wide accesses
-  auto fits = [&](int v) {
-    return F % v == 0 && ldx % v == 0 && reinterpret_cast<uintptr_t>(x) % (4 * v) == 0 &&
-           reinterpret_cast<uintptr_t>(out) % (4 * v) == 0 && (!heads || per_head % v == 0) &&
-           (h == nullptr || (ldh % v == 0 && reinterpret_cast<uintptr_t>(h) % (4 * v) == 0)) &&
-           (mask == nullptr || reinterpret_cast<uintptr_t>(mask) % (4 * v) == 0);
-  };
-  const int vec = fits(4) ? 4 : fits(2) ? 2 : 1;
-  const int lanes = (int)std::min<int64_t>((F + vec - 1) / vec, kWave);
-  int p2 = 1;
-  while (p2 < lanes) p2 <<= 1;
-  const int slots = std::min(kWave / p2, 16);
   const bool mx = reduce == TFG_MAX;
   const bool part_plan = use_part_plan(g, F);
-  const bool short_rows = !part_plan && mask == nullptr && !heads && g.n_short > 0;
 
   RowArgs a;
   a.col = g.col;
@@ -332,7 +348,7 @@ int launch_aggregate(const Graph& g, const float* w, int H, int w_order, const f
   a.w = w;
   a.w_by_perm = (w != nullptr && w_order == TFG_COO) ? 1 : 0;
   a.H = H;
-  a.per_head = per_head;
+  a.per_head = (int)(F / H);
   a.x = x;
   a.ldx = ldx;
   a.mask = mask;
@@ -344,63 +360,30 @@ int launch_aggregate(const Graph& g, const float* w, int H, int w_order, const f
   const int n_partials = part_plan ? g.n_pexec : g.n_heavy;
   a.part = static_cast<float*>(ws);
   a.part_arg = reinterpret_cast<int*>(a.part + (size_t)std::max(n_partials, 1) * F);
-  const SplitRow* rows;
-  int n_rows;
-  if (part_plan) {
-    // every (part, row) item writes a partial; each row is reduced in part order
-    a.heavy = g.pexec;
-    a.n_heavy = g.n_pexec;
-    a.light = nullptr;
-    a.n_light = 0;
-    rows = g.prows;
-    n_rows = (int)g.N;
-  } else {
-    a.heavy = g.heavy;
-    a.n_heavy = g.n_heavy;
-    rows = g.split;
-    n_rows = g.n_split;
-    if (short_rows) {
-      // rows of at most kShortRow edges several per wavefront, the rest one each
-      a.light = g.long_rows;
-      a.n_light = g.n_long;
-    } else {
-      a.light = g.light;
-      a.n_light = g.n_light;
-    }
-  }
-  if (short_rows) {
-    dispatch_short(mx, vec, slots, g, a, s);
-    TFG_LAUNCHED("spmm_short");
-  }
-  const int waves = a.n_heavy + a.n_light;
-  if (waves > 0) {
-    dim3 grid((unsigned)((waves + kRowBlock / kWave - 1) / (kRowBlock / kWave)));
-    const WideShape wsh = wide_shape(F, vec, !mx, heads, mask != nullptr);
-    if (wsh.v > 0)
-      launch_wide(wsh, grid, s, a, g.N_src);
-    else if (mask != nullptr)
-      dispatch_masked(part_plan, heads, vec, slots, grid, s, a);
-    else if (part_plan)
-      dispatch_kind<true>(mx, heads, vec, slots, grid, s, a);
-    else
-      dispatch_kind<false>(mx, heads, vec, slots, grid, s, a);
-    TFG_LAUNCHED("spmm_rows");
-  }
+  // part plan: every (part, row) item writes a partial, each row is reduced in
+  // part order; row plan: whole rows write the output, chunks partials
+  a.heavy = part_plan ? g.pexec : g.heavy;
+  a.n_heavy = n_partials;
+  const SplitRow* rows = part_plan ? g.prows : g.split;
+  const int n_rows = part_plan ? (int)g.N : g.n_split;
+  const bool aligned = ldx % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
+  if (use_wide(F, aligned, !mx && !heads && mask == nullptr, part_plan) && a.n_heavy > 0)
+    launch_wide(a.n_heavy, s, a, g.N_src);
+  else
+    launch_slots(g, a, mx, heads, mask != nullptr, part_plan, s);
+  TFG_LAUNCHED("aggregation");
   if (n_rows > 0) {
-    dim3 fgrid((unsigned)((n_rows + kItemBlock / kWave - 1) / (kItemBlock / kWave)));
-    // partials are dense [slot, F] rows: 16-byte accesses when F is a multiple
-    // of 4 and the output (and the epilogue's h rows) allow them
-    const bool f4 = F % 4 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0 &&
-                    (h == nullptr || (ldh % 4 == 0 && reinterpret_cast<uintptr_t>(h) % 16 == 0));
-    if (mx)
-      fixup_rows<true, 1><<<fgrid, dim3(kItemBlock), 0, s>>>(rows, n_rows, a.part, a.part_arg, a.F,
-                                                         a.mean, out, argmax, a.ep);
-    else if (f4)
-      fixup_rows<false, 4><<<fgrid, dim3(kItemBlock), 0, s>>>(rows, n_rows, a.part, a.part_arg, a.F,
-                                                          a.mean, out, argmax, a.ep);
-    else
-      fixup_rows<false, 1><<<fgrid, dim3(kItemBlock), 0, s>>>(rows, n_rows, a.part, a.part_arg, a.F,
-                                                          a.mean, out, argmax, a.ep);
+    int flps = 4;  // lanes per row
+    while (flps < kWave && flps * (F >= 4 ? 4 : 1) < F) flps <<= 1;
+    dim3 fgrid((unsigned)((n_rows + kWave / flps - 1) / (kWave / flps)));
+#define TFG_FIXUP(M, VV)                                                                      \
+  fixup_rows<M, VV><<<fgrid, dim3(kItemBlock), 0, s>>>(rows, n_rows, a.part, a.part_arg, a.F, \
+                                                       a.mean, out, argmax, a.ep, flps)
+    if (mx && F >= 4) TFG_FIXUP(true, 4);
+    else if (mx) TFG_FIXUP(true, 1);
+    else if (F >= 4) TFG_FIXUP(false, 4);
+    else TFG_FIXUP(false, 1);
+#undef TFG_FIXUP
     TFG_LAUNCHED("fixup_rows");
   }
   return TFG_OK;

@@ -111,7 +111,6 @@ int create_graph(Graph& g, const void* src, const void* tgt, int index_type, int
   g.perm = reinterpret_cast<int*>(b + L.perm);
   g.key = reinterpret_cast<int*>(b + L.key);
   g.heavy = reinterpret_cast<WorkItem*>(b + L.heavy);
-  g.light = reinterpret_cast<WorkItem*>(b + L.light);
   g.split = reinterpret_cast<SplitRow*>(b + L.split);
   g.pexec = reinterpret_cast<WorkItem*>(b + L.pexec);
   g.prows = reinterpret_cast<SplitRow*>(b + L.prows);

@@ -4,7 +4,7 @@
 //   dx  (sum)  = the sum aggregation of dy over the transposed graph (rows are
 //                sources, columns targets) with the same edge weights;
 //   dx  (mean) = the same with w_e / deg(t_e) as weights;
-//   dx  (max)  = the masked gather of spmm_rows: element c of dy[t] reaches
+//   dx  (max)  = the masked gather (slots.h): element c of dy[t] reaches
 //                source s only through the edge that won the forward max;
 //   dw[e, k]   = sum over the columns c of head k of g[t_e, c] x[s_e, c] with
 //                g = dy, dy / deg(t) or the masked dy: one dot product per
@@ -21,28 +21,33 @@
 
 namespace tfg {
 
-namespace rows {
-
-void dispatch_masked(bool part_plan, bool heads, int vec, int slots, dim3 grid, hipStream_t s,
-                     const RowArgs& a) {
-  if (part_plan) {
-    if (heads)
-      dispatch_vec<false, true, true, true>(vec, slots, grid, s, a);
-    else
-      dispatch_vec<false, false, true, true>(vec, slots, grid, s, a);
-  } else {
-    if (heads)
-      dispatch_vec<false, true, false, true>(vec, slots, grid, s, a);
-    else
-      dispatch_vec<false, false, false, true>(vec, slots, grid, s, a);
-  }
-}
-
-}  // namespace rows
-
 namespace {
 
 using namespace rows;
+
+// Value held by lane (jbase + slot); jbase is wave-uniform.
+template <int SLOTS>
+__device__ __forceinline__ int bcast(int v, int jbase, int slot) {
+  if constexpr (SLOTS == 1) {
+    return __builtin_amdgcn_readlane(v, jbase);
+  } else if constexpr (SLOTS == 2) {
+    int a = __builtin_amdgcn_readlane(v, jbase);
+    int b = __builtin_amdgcn_readlane(v, jbase + 1);
+    return slot ? b : a;
+  } else if constexpr (SLOTS == 4) {
+    int a = __builtin_amdgcn_readlane(v, jbase);
+    int b = __builtin_amdgcn_readlane(v, jbase + 1);
+    int c = __builtin_amdgcn_readlane(v, jbase + 2);
+    int d = __builtin_amdgcn_readlane(v, jbase + 3);
+    return slot == 0 ? a : slot == 1 ? b : slot == 2 ? c : d;
+  } else {
+    return __shfl(v, jbase + slot);
+  }
+}
+template <int SLOTS>
+__device__ __forceinline__ float bcastf(float v, int jbase, int slot) {
+  return __int_as_float(bcast<SLOTS>(__float_as_int(v), jbase, slot));
+}
 
 enum { kGradSum = 0, kGradMean = 1, kGradMax = 2 };
 
@@ -701,7 +706,8 @@ int launch_edge_grad(const Graph& g, const float* x, int64_t ldx, const float* d
     run(g.pexec, g.n_pexec);
   } else {
     run(g.heavy, g.n_heavy);
-    run(g.light, g.n_light);
+    run(g.long_rows, g.n_long);
+    run(g.short_rows, g.n_short);
   }
   TFG_LAUNCHED("edge_grad_rows");
   return TFG_OK;

@@ -683,28 +683,41 @@ __global__ __launch_bounds__(kBlock) void rows_from_segments(const int* __restri
 // Aggregation work lists.
 // ---------------------------------------------------------------------------
 
-// Row plan: rows with at most `chunk` edges become one light item; longer
-// rows are cut into ceil(deg / chunk) heavy items whose partial results the
-// fix-up pass combines. The light rows are listed again by length (short:
-// at most kShortRow edges; long: the others). Every list is in row order:
-// per-block counts, one scan of them, then a fill pass (no atomics).
+// Row plan: a row of at most `chunk` edges is one item; longer rows are cut
+// into ceil(deg / chunk) heavy items whose partial results the fix-up pass
+// combines. The whole rows are listed by length: short (at most kShortRow
+// edges), and the others in classes (kClasses, longest first, each in row
+// order), so that kernels that take several rows per wavefront give it rows of
+// about one length. Every list is filled in order: per-block counts, one scan
+// of them, then a fill pass (no atomics).
 constexpr int kWlThreads = 1024;  // rows per block of the work-list kernels
-constexpr int kLists = 5;         // heavy chunks, light, split, short, long
-__constant__ const int kListCounter[kLists] = {0, 1, 2, 5, 6};  // their slots in counters
+constexpr int kClasses = 4;       // whole rows of 65.., 33..64, 17..32, 9..16 edges
+constexpr int kLists = 3 + kClasses;  // heavy chunks, split, short, the classes
 
-// Entries of a row of `deg` edges in each list.
-__device__ __forceinline__ void row_counts(bool valid, int deg, int chunk, int (&c)[kLists]) {
+// A row's entries in each list, several counts to a word: at most one entry
+// per row outside the heavy list, so 16 bits hold the counts of a block (and
+// of the whole one-block build).
+constexpr int kWlWords = 4;  // heavy; split, short; classes 0, 1; classes 2, 3
+__device__ __forceinline__ void row_counts(bool valid, int deg, int chunk, int (&c)[kWlWords]) {
   const bool split = valid && deg > chunk;
-  const bool shrt = valid && deg <= kShortRow;
+  const bool whole = valid && !split;
   c[0] = split ? (deg + chunk - 1) / chunk : 0;
-  c[1] = valid && !split;
-  c[2] = split;
-  c[3] = shrt;
-  c[4] = valid && !split && !shrt;
+  c[1] = (int)split | (int)(whole && deg <= kShortRow) << 16;
+  c[2] = (int)(whole && deg > 64) | (int)(whole && deg > 32 && deg <= 64) << 16;
+  c[3] = (int)(whole && deg > 16 && deg <= 32) | (int)(whole && deg > kShortRow && deg <= 16) << 16;
+}
+
+__device__ __forceinline__ void unpack_counts(const int (&c)[kWlWords], int (&l)[kLists]) {
+  l[0] = c[0];
+#pragma unroll
+  for (int i = 1; i < kWlWords; ++i) {
+    l[2 * i - 1] = c[i] & 0xFFFF;
+    l[2 * i] = (int)((unsigned)c[i] >> 16);
+  }
 }
 
 __device__ __forceinline__ void row_entries(const int* __restrict__ rowptr, int64_t N, int chunk,
-                                            int64_t r, int* beg, int* deg, int (&c)[kLists]) {
+                                            int64_t r, int* beg, int* deg, int (&c)[kWlWords]) {
   *beg = 0;
   *deg = 0;
   if (r < N) {
@@ -714,52 +727,90 @@ __device__ __forceinline__ void row_entries(const int* __restrict__ rowptr, int6
   row_counts(r < N, *deg, chunk, c);
 }
 
+// Places the entries of row r: o[] the row's place in each list, the classes
+// one after the other in long_rows.
+__device__ __forceinline__ void place_row(int64_t r, int beg, int deg, int chunk,
+                                          const int (&c)[kWlWords], const int (&o)[kLists],
+                                          WorkItem* __restrict__ heavy, SplitRow* __restrict__ split,
+                                          WorkItem* __restrict__ short_rows,
+                                          WorkItem* __restrict__ long_rows) {
+  if (c[0] > 0) {
+    const int h0 = o[0];
+    for (int j = 0; j < c[0]; ++j) {
+      const int kb = beg + j * chunk;
+      heavy[h0 + j] = WorkItem{(int)r, kb, min(kb + chunk, beg + deg), h0 + j};
+    }
+    split[o[1]] = SplitRow{(int)r, h0, c[0], deg};
+  } else if (deg <= kShortRow) {
+    short_rows[o[2]] = WorkItem{(int)r, beg, beg + deg, -1};
+  } else {
+    const int k = deg > 64 ? o[3] : deg > 32 ? o[4] : deg > 16 ? o[5] : o[6];
+    long_rows[k] = WorkItem{(int)r, beg, beg + deg, -1};
+  }
+}
+
+// List lengths to the counters of the graph.
+__device__ __forceinline__ void write_counters(const int (&tot)[kLists], int* __restrict__ counters) {
+  counters[0] = tot[0];
+  counters[2] = tot[1];
+  counters[5] = tot[2];
+  counters[6] = tot[3] + tot[4] + tot[5] + tot[6];
+  counters[1] = tot[3];
+  counters[7] = tot[3] + tot[4];
+}
+
 // Entries per list of each block of rows: block_sums[list * nb + block].
 __global__ __launch_bounds__(kWlThreads) void worklist_count(const int* __restrict__ rowptr,
                                                              int64_t N, int chunk,
                                                              int* __restrict__ block_sums, int nb) {
-  __shared__ int tmp[kLists * (kWlThreads / kWave)];
-  int beg, deg, c[kLists], ex[kLists], tot[kLists];
+  __shared__ int tmp[kWlWords * (kWlThreads / kWave + 1)];
+  int beg, deg, c[kWlWords], ex[kWlWords], tot[kWlWords], l[kLists];
   row_entries(rowptr, N, chunk, (int64_t)blockIdx.x * kWlThreads + threadIdx.x, &beg, &deg, c);
-  block_excl_scan_lists<kWlThreads / kWave, kLists>(c, ex, tot, tmp);
+  block_excl_scan_lists<kWlThreads / kWave, kWlWords>(c, ex, tot, tmp);
+  unpack_counts(tot, l);
   if (threadIdx.x == 0)
 #pragma unroll
-    for (int i = 0; i < kLists; ++i) block_sums[i * nb + blockIdx.x] = tot[i];
+    for (int i = 0; i < kLists; ++i) block_sums[i * nb + blockIdx.x] = l[i];
 }
 
-// One block: exclusive scan of each list's block sums in place; the list
-// lengths go to the counters.
+// One block: exclusive scan of each list's block sums in place (the classes
+// each from 0), their totals after the table, and the list lengths in the
+// counters.
 __global__ __launch_bounds__(1024) void worklist_offsets(int* __restrict__ block_sums, int nb,
                                                          int* __restrict__ counters) {
-  __shared__ int tmp[1024 / kWave];
-  for (int i = 0; i < kLists; ++i) {
-    int* b = block_sums + (int64_t)i * nb;
-    int carry = 0;
-    for (int base = 0; base < nb; base += 1024) {
-      const int k = base + (int)threadIdx.x;
-      const int v = k < nb ? b[k] : 0;
-      int total;
-      const int ex = block_excl_scan<1024 / kWave>(v, tmp, &total);
-      if (k < nb) b[k] = carry + ex;
-      carry += total;
+  __shared__ int tmp[kLists * (1024 / kWave + 1)];
+  int carry[kLists] = {};
+  for (int base = 0; base < nb; base += 1024) {
+    const int k = base + (int)threadIdx.x;
+    int v[kLists], ex[kLists], tot[kLists];
+#pragma unroll
+    for (int i = 0; i < kLists; ++i) v[i] = k < nb ? block_sums[(int64_t)i * nb + k] : 0;
+    block_excl_scan_lists<1024 / kWave, kLists>(v, ex, tot, tmp);
+#pragma unroll
+    for (int i = 0; i < kLists; ++i) {
+      if (k < nb) block_sums[(int64_t)i * nb + k] = carry[i] + ex[i];
+      carry[i] += tot[i];
     }
-    if (threadIdx.x == 0) counters[kListCounter[i]] = carry;
+  }
+  if (threadIdx.x == 0) {
+    write_counters(carry, counters);
+#pragma unroll
+    for (int i = 0; i < kLists; ++i) block_sums[(int64_t)kLists * nb + i] = carry[i];
   }
 }
 
-// The three steps in one block, for graphs of at most kWlSingle rows: the
-// rows go in chunks of kWlThreads, each chunk's entries placed after the
-// previous chunks' (the same lists, in the same order).
+// The three steps in one block, for graphs of at most kWlSingle rows (the
+// same lists, in the same order).
 constexpr int kWlSingle = 4 * kWlThreads;
 __global__ __launch_bounds__(kWlThreads) void worklist_single(
     const int* __restrict__ rowptr, int64_t N, int chunk, int* __restrict__ counters,
-    WorkItem* __restrict__ heavy, WorkItem* __restrict__ light, SplitRow* __restrict__ split,
+    WorkItem* __restrict__ heavy, SplitRow* __restrict__ split,
     WorkItem* __restrict__ short_rows, WorkItem* __restrict__ long_rows) {
-  __shared__ int tmp[kLists * (kWlThreads / kWave)];
-  int carry[kLists] = {0, 0, 0, 0, 0};
-  // every chunk's row pointers loaded before the first is used
   constexpr int kChunks = kWlSingle / kWlThreads;
-  int rp[kChunks], rq[kChunks];
+  __shared__ int tmp[kChunks * kWlWords * (kWlThreads / kWave + 1)];
+  // every chunk's row pointers loaded before the first is used, and every
+  // chunk's counts scanned between one pair of barriers
+  int rp[kChunks], rq[kChunks], c[kChunks * kWlWords], ex[kChunks * kWlWords], tot[kChunks * kWlWords];
 #pragma unroll
   for (int j = 0; j < kChunks; ++j) {
     const int64_t r = (int64_t)j * kWlThreads + threadIdx.x;
@@ -768,64 +819,66 @@ __global__ __launch_bounds__(kWlThreads) void worklist_single(
   }
 #pragma unroll
   for (int j = 0; j < kChunks; ++j) {
-    if ((int64_t)j * kWlThreads >= N) break;  // uniform
+    int cj[kWlWords];
+    row_counts((int64_t)j * kWlThreads + threadIdx.x < N, rq[j] - rp[j], chunk, cj);
+#pragma unroll
+    for (int i = 0; i < kWlWords; ++i) c[j * kWlWords + i] = cj[i];
+  }
+  block_excl_scan_lists<kWlThreads / kWave, kChunks * kWlWords>(c, ex, tot, tmp);
+  int all[kLists] = {};
+#pragma unroll
+  for (int j = 0; j < kChunks; ++j) {
+    int t[kWlWords], l[kLists];
+#pragma unroll
+    for (int i = 0; i < kWlWords; ++i) t[i] = tot[j * kWlWords + i];
+    unpack_counts(t, l);
+#pragma unroll
+    for (int i = 0; i < kLists; ++i) all[i] += l[i];
+  }
+  // start of each list; the classes follow each other in long_rows
+  int start[kLists] = {0, 0, 0, 0, all[3], all[3] + all[4], all[3] + all[4] + all[5]};
+#pragma unroll
+  for (int j = 0; j < kChunks; ++j) {
     const int64_t r = (int64_t)j * kWlThreads + threadIdx.x;
-    const int beg = rp[j], deg = rq[j] - rp[j];
-    int c[kLists], o[kLists], tot[kLists];
-    row_counts(r < N, deg, chunk, c);
-    block_excl_scan_lists<kWlThreads / kWave, kLists>(c, o, tot, tmp);
+    int cj[kWlWords], t[kWlWords], e[kWlWords], l[kLists], o[kLists];
+#pragma unroll
+    for (int i = 0; i < kWlWords; ++i) {
+      cj[i] = c[j * kWlWords + i];
+      e[i] = ex[j * kWlWords + i];
+      t[i] = tot[j * kWlWords + i];
+    }
+    unpack_counts(e, o);
+    unpack_counts(t, l);
 #pragma unroll
     for (int i = 0; i < kLists; ++i) {
-      o[i] += carry[i];
-      carry[i] += tot[i];
+      o[i] += start[i];
+      start[i] += l[i];
     }
-    if (r < N) {
-      if (c[3])
-        short_rows[o[3]] = WorkItem{(int)r, beg, beg + deg, -1};
-      else if (c[4])
-        long_rows[o[4]] = WorkItem{(int)r, beg, beg + deg, -1};
-      if (c[2]) {
-        for (int q = 0; q < c[0]; ++q) {
-          const int kb = beg + q * chunk;
-          heavy[o[0] + q] = WorkItem{(int)r, kb, min(kb + chunk, beg + deg), o[0] + q};
-        }
-        split[o[2]] = SplitRow{(int)r, o[0], c[0], deg};
-      } else {
-        light[o[1]] = WorkItem{(int)r, beg, beg + deg, -1};
-      }
-    }
+    if (r < N) place_row(r, rp[j], rq[j] - rp[j], chunk, cj, o, heavy, split, short_rows, long_rows);
   }
-  if (threadIdx.x == 0)
-#pragma unroll
-    for (int i = 0; i < kLists; ++i) counters[kListCounter[i]] = carry[i];
+  if (threadIdx.x == 0) write_counters(all, counters);
 }
 
 __global__ __launch_bounds__(kWlThreads) void worklist_fill(
     const int* __restrict__ rowptr, int64_t N, int chunk, const int* __restrict__ block_sums,
-    int nb, WorkItem* __restrict__ heavy, WorkItem* __restrict__ light,
-    SplitRow* __restrict__ split, WorkItem* __restrict__ short_rows, WorkItem* __restrict__ long_rows) {
-  __shared__ int tmp[kLists * (kWlThreads / kWave)];
+    int nb, WorkItem* __restrict__ heavy, SplitRow* __restrict__ split,
+    WorkItem* __restrict__ short_rows, WorkItem* __restrict__ long_rows) {
+  __shared__ int tmp[kWlWords * (kWlThreads / kWave + 1)];
   const int64_t r = (int64_t)blockIdx.x * kWlThreads + threadIdx.x;
-  int beg, deg, c[kLists], o[kLists], tot[kLists];
+  int beg, deg, c[kWlWords], ex[kWlWords], tot[kWlWords], o[kLists];
   row_entries(rowptr, N, chunk, r, &beg, &deg, c);
-  block_excl_scan_lists<kWlThreads / kWave, kLists>(c, o, tot, tmp);
+  block_excl_scan_lists<kWlThreads / kWave, kWlWords>(c, ex, tot, tmp);
+  unpack_counts(ex, o);
+  int before = 0;  // the longer classes come first in long_rows
 #pragma unroll
-  for (int i = 0; i < kLists; ++i) o[i] += block_sums[i * nb + blockIdx.x];
-  if (r >= N) return;
-  if (c[3])
-    short_rows[o[3]] = WorkItem{(int)r, beg, beg + deg, -1};
-  else if (c[4])
-    long_rows[o[4]] = WorkItem{(int)r, beg, beg + deg, -1};
-  if (c[2]) {
-    const int h0 = o[0];
-    for (int j = 0; j < c[0]; ++j) {
-      const int kb = beg + j * chunk;
-      heavy[h0 + j] = WorkItem{(int)r, kb, min(kb + chunk, beg + deg), h0 + j};
+  for (int i = 0; i < kLists; ++i) {
+    o[i] += block_sums[(int64_t)i * nb + blockIdx.x];
+    if (i >= 3) {
+      o[i] += before;
+      before += block_sums[(int64_t)kLists * nb + i];
     }
-    split[o[2]] = SplitRow{(int)r, h0, c[0], deg};
-  } else {
-    light[o[1]] = WorkItem{(int)r, beg, beg + deg, -1};
   }
+  if (r < N) place_row(r, beg, deg, chunk, c, o, heavy, split, short_rows, long_rows);
 }
 
 __device__ __forceinline__ int chunks_of(int len, int chunk) { return (len + chunk - 1) / chunk; }
@@ -847,25 +900,55 @@ __global__ __launch_bounds__(kBlock) void part_counts(const int* __restrict__ se
   row_items[t] = tot;
 }
 
-// Part plan, step 2: items in part-major order (part, row, chunk); the
-// partial slots are numbered row-major so that row t's partials are the
-// contiguous range [row_slot[t], row_slot[t+1]), in part order.
+// Part plan, step 2: items in part-major order; the partial slots are numbered
+// row-major so that row t's partials are the contiguous range
+// [row_slot[t], row_slot[t+1]), in part order. Within a part, the items of the
+// kBlock rows of a block are placed by length (kPartClasses, longest first,
+// each in row order): kernels that take several items per wavefront then give
+// it items of about one length. The slots, and so the results, do not depend
+// on that order.
+constexpr int kPartClasses = 6;  // over 64 edges (whole chunks too), 33.., 17.., 9.., 5.., 1..4
+__device__ __forceinline__ int part_class(int len) {
+  return len > 64 ? 0 : len > 32 ? 1 : len > 16 ? 2 : len > 8 ? 3 : len > 4 ? 4 : 5;
+}
 __global__ __launch_bounds__(kBlock) void part_fill(const int* __restrict__ segptr, int64_t N,
                                                     int parts, int chunk,
                                                     const int* __restrict__ row_slot,
                                                     const int* __restrict__ seg_pos,
                                                     WorkItem* __restrict__ exec,
                                                     SplitRow* __restrict__ rows) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= N) return;
-  int slot = row_slot[t];
+  static_assert(kBlock < 1024, "ten bits per class hold a block's counts");
+  __shared__ int tmp[3 * (kBlock / kWave + 1)];
+  const int64_t t0 = (int64_t)blockIdx.x * kBlock;
+  const int64_t t = t0 + threadIdx.x;
+  const bool ok = t < N;
+  int slot = ok ? row_slot[t] : 0;
   const int s0 = slot;
   for (int p = 0; p < parts; ++p) {
-    const int kb = segptr[t * parts + p], ke = segptr[t * parts + p + 1];
-    int pos = seg_pos[(int64_t)p * N + t];
-    for (int k = kb; k < ke; k += chunk) exec[pos++] = WorkItem{(int)t, k, min(k + chunk, ke), slot++};
+    const int kb = ok ? segptr[t * parts + p] : 0, ke = ok ? segptr[t * parts + p + 1] : 0;
+    const int base = seg_pos[(int64_t)p * N + t0];
+    const int whole = (ke - kb) / chunk, rem = ke - kb - whole * chunk;
+    const int cls = rem > 0 ? part_class(rem) : -1;
+    // class 0 in a word of its own (a long segment has many whole chunks), the
+    // others ten bits each
+    int c[3] = {whole + (cls == 0), 0, 0}, ex[3], tot[3];
+    if (cls >= 1) c[1 + (cls - 1) / 3] = 1 << 10 * ((cls - 1) % 3);
+    block_excl_scan_lists<kBlock / kWave, 3>(c, ex, tot, tmp);
+    for (int j = 0; j < whole; ++j)
+      exec[base + ex[0] + j] = WorkItem{(int)t, kb + j * chunk, kb + (j + 1) * chunk, slot + j};
+    if (cls >= 0) {
+      int pos = base + (cls == 0 ? ex[0] + whole : tot[0]);
+#pragma unroll
+      for (int q = 1; q < kPartClasses; ++q) {
+        const int w = 1 + (q - 1) / 3, sh = 10 * ((q - 1) % 3);
+        if (q < cls) pos += (tot[w] >> sh) & 1023;
+        if (q == cls) pos += (ex[w] >> sh) & 1023;
+      }
+      exec[pos] = WorkItem{(int)t, kb + whole * chunk, ke, slot + whole};
+    }
+    slot += whole + (rem > 0);
   }
-  rows[t] = SplitRow{(int)t, s0, slot - s0, segptr[(t + 1) * parts] - segptr[t * parts]};
+  if (ok) rows[t] = SplitRow{(int)t, s0, slot - s0, segptr[(t + 1) * parts] - segptr[t * parts]};
 }
 
 int ceil_log2(int64_t n) {
@@ -908,7 +991,7 @@ ScratchLayout scratch_layout(int64_t E, int64_t N, int parts) {
   L.sums = take(sizeof(int) * std::max<int64_t>(scan_tiles(scan_n), 1));
   L.bufA = take(sizeof(int) * 3 * std::max<int64_t>(E, 1));
   L.bufB = take(p.passes >= 3 ? sizeof(int) * 3 * std::max<int64_t>(E, 1) : 0);
-  L.wl_sums = take(sizeof(int) * kLists * std::max<int64_t>((N + kWlThreads - 1) / kWlThreads, 1));
+  L.wl_sums = take(sizeof(int) * kLists * (std::max<int64_t>((N + kWlThreads - 1) / kWlThreads, 1) + 1));
   L.row_items = take(parts > 1 ? sizeof(int) * (N + 1) : 0);
   L.seg_items = take(parts > 1 ? sizeof(int) * (N * parts + 1) : 0);
   L.total = off;
@@ -1101,7 +1184,6 @@ GraphLayout graph_layout(int64_t E, int64_t N, int parts, int chunk) {
   // chunks number at most 2 * E / chunk
   L.cap_split = std::min<int64_t>(N, E / chunk + 1);
   L.cap_heavy = 2 * (E / chunk) + 2;
-  L.cap_light = N;
   // part plan: one item per nonempty (row, part) segment, plus one per
   // further chunk of a long segment
   L.cap_pexec = parts > 1 ? std::min<int64_t>(E, N * parts) + E / chunk + 1 : 0;
@@ -1111,7 +1193,6 @@ GraphLayout graph_layout(int64_t E, int64_t N, int parts, int chunk) {
   L.perm = take(sizeof(int) * std::max<int64_t>(E, 1));
   L.key = take(sizeof(int) * std::max<int64_t>(E, 1));
   L.heavy = take(sizeof(WorkItem) * L.cap_heavy);
-  L.light = take(sizeof(WorkItem) * std::max<int64_t>(L.cap_light, 1));
   L.split = take(sizeof(SplitRow) * std::max<int64_t>(L.cap_split, 1));
   L.pexec = take(sizeof(WorkItem) * L.cap_pexec);
   L.prows = take(parts > 1 ? sizeof(SplitRow) * N : 0);
@@ -1145,12 +1226,12 @@ int build_graph(Graph& g, const void* src, const void* tgt, int index_type, void
     int* wl = reinterpret_cast<int*>(sc + L.wl_sums);
     if (g.N <= kWlSingle) {
       worklist_single<<<1, kWlThreads, 0, s>>>(g.rowptr, g.N, g.chunk, g.counters, g.heavy,
-                                               g.light, g.split, g.short_rows, g.long_rows);
+                                               g.split, g.short_rows, g.long_rows);
     } else {
       worklist_count<<<nb, kWlThreads, 0, s>>>(g.rowptr, g.N, g.chunk, wl, nb);
       worklist_offsets<<<1, 1024, 0, s>>>(wl, nb, g.counters);
-      worklist_fill<<<nb, kWlThreads, 0, s>>>(g.rowptr, g.N, g.chunk, wl, nb, g.heavy, g.light,
-                                              g.split, g.short_rows, g.long_rows);
+      worklist_fill<<<nb, kWlThreads, 0, s>>>(g.rowptr, g.N, g.chunk, wl, nb, g.heavy, g.split,
+                                              g.short_rows, g.long_rows);
     }
     TFG_LAUNCHED("work lists");
     if (g.parts > 1) {
@@ -1165,7 +1246,8 @@ int build_graph(Graph& g, const void* src, const void* tgt, int index_type, void
   TFG_HIP(hipStreamSynchronize(s));
   if (host[3] & kErrIndex) return fail(TFG_ERR_INDEX_RANGE, "edge_index holds an id outside [0, N)");
   g.n_heavy = host[0];
-  g.n_light = host[1];
+  g.n_over64 = host[1];
+  g.n_over32 = host[7];
   g.n_split = host[2];
   g.n_pexec = host[4];
   g.n_short = host[5];

@@ -1,0 +1,292 @@
+// The slot aggregation (gfx950, wave64): several work items per wavefront.
+//
+// A wavefront has 64 / LPS edge slots of LPS lanes; a lane holds V neighbouring
+// columns of a row. An item belongs to `split` neighbouring slots, usually one
+// or two, so a wavefront works on several items at once and an item's edges are
+// mostly summed inside a slot. One wavefront per item (the earlier kernel) spent
+// a round trip on the item, one on its ids, one on its gathers and a tree over
+// the slots on each of them, with most lanes idle on rows of a few edges; rows
+// of 14 edges (169,343 of them, 40 columns) took 147 us, now 80. What bounds the
+// large cases now is the gathers that miss the L2s: 10M edges of 400 bytes move
+// at 6.2 TB/s (0.65 ms, before 0.83), 23M of 256 bytes by source part at 12
+// TB/s (0.50 ms, before 0.70); the same with maxima 0.69 ms (before 1.97: the
+// comparison with its tie rule was the bound, and is now three operations per
+// column, since ids ascend along an item of one source part).
+//
+// The 16 ids of a round reach the lanes of a slot through DPP broadcasts that
+// fold into the address addition and the multiply-add: per edge and slot one
+// addition, one load and V multiply-adds. Rows need dword alignment only, and
+// a last lane that steps back serves any width with 16-byte loads.
+#pragma once
+
+#include <utility>
+
+#include "spmm.h"
+
+namespace tfg {
+namespace rows {
+namespace {
+
+// Rounds of kIds edges per slot. A slot of at least 16 lanes is made of whole
+// DPP rows: lane l of each row holds edge l of the round, and edge I reaches
+// every lane with one row broadcast. A slot of 4 or 8 lanes is made of quads:
+// register r of lane l holds edge 4 r + l % 4, broadcast inside the quad.
+constexpr int kIds = 16;
+template <int LPS>
+constexpr int id_regs() { return LPS >= 16 ? 1 : 4; }
+
+template <int I, int LPS>
+__device__ __forceinline__ int slot_bcast(const int (&r)[id_regs<LPS>()]) {
+  if constexpr (LPS >= 16)
+    return __builtin_amdgcn_update_dpp(0, r[0], 0x150 + I, 0xF, 0xF, false);
+  else
+    return __builtin_amdgcn_update_dpp(0, r[I / 4], (I % 4) * 0x55, 0xF, 0xF, false);
+}
+
+// A lane's place in the row whose id (NARROW: whose byte offset) is c.
+template <bool NARROW, typename T>
+__device__ __forceinline__ const T* row_at(const char* base, int c, int64_t row_bytes,
+                                           unsigned lane_off) {
+  if constexpr (NARROW) return reinterpret_cast<const T*>(base + ((unsigned)c + lane_off));
+  else return reinterpret_cast<const T*>(base + ((int64_t)c * row_bytes + lane_off));
+}
+
+template <typename F, int... I>
+__device__ __forceinline__ void each_of(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void each(F&& f) {
+  each_of(f, std::make_integer_sequence<int, N>{});
+}
+
+// kMax: edge ids ascend along an item (one source part per item); kMaxTies:
+// they need not, equal maxima compare the ids.
+enum { kSum = 0, kMax = 1, kMaxTies = 2, kMasked = 3 };
+enum { kNone = 0, kEdge = 1, kHeads = 2 };  // weights: none, one per edge, one per edge and head
+
+template <int V, int LPS, int KIND, int WM, bool NARROW>
+__global__ __launch_bounds__(kItemBlock) void spmm_slots(
+    SlotLists L, const int* __restrict__ col, const int* __restrict__ perm,
+    const float* __restrict__ w, int w_by_perm, int H, int per_head, const float* __restrict__ x,
+    int64_t ldx, const int* __restrict__ mask, int F, int mean, float* __restrict__ out,
+    int* __restrict__ argout, float* __restrict__ part, int* __restrict__ part_arg, Epilogue ep) {
+  constexpr int SLOTS = kWave / LPS;
+  constexpr int FC = LPS * V;
+  constexpr int NR = id_regs<LPS>();
+  constexpr int BW = kIds / NR;  // edges per register
+  constexpr bool MAX = KIND == kMax || KIND == kMaxTies, MASK = KIND == kMasked;
+  constexpr int U = MASK || WM == kHeads ? 4 : 8;  // gathers in flight per slot
+  constexpr int CH = MAX ? 1 : 4;                  // accumulator chains
+  int wid = blockIdx.x;
+  int li = 0;
+#pragma unroll
+  for (int i = 0; i + 1 < kSlotLists; ++i)
+    if (li == i && wid >= L.waves[i]) {  // uniform
+      wid -= L.waves[i];
+      li = i + 1;
+    }
+  const WorkItem* items = L.items[li];
+  const int n_items = L.n[li], split = L.split[li];
+  const int lane = lane_id();
+  const int sl = lane % LPS;
+  const int q = wid * SLOTS + lane / LPS;  // slot index in the list's launch
+  const int ii = q / split, sub = q - ii * split;
+  const bool have = ii < n_items;
+  const WorkItem it = items[have ? ii : 0];
+  const int kbeg = it.kbeg, n = have ? it.kend - it.kbeg : 0;
+  int nmax = __builtin_amdgcn_readlane(n, 0);
+#pragma unroll
+  for (int s = 1; s < SLOTS; ++s) nmax = max(nmax, __builtin_amdgcn_readlane(n, s * LPS));
+  const int64_t row_bytes = ldx * (int64_t)sizeof(float);
+  const bool need_perm = MAX || MASK || w_by_perm;
+
+  for (int f0 = 0; f0 < F; f0 += FC) {
+    // columns f .. f + V - 1. The last lane with columns of its own steps back
+    // so that its V columns end at F (it repeats some of its neighbour's: the
+    // same values, written twice); lanes past it repeat it and write nothing.
+    const int fw = f0 + sl * V;
+    const bool fok = fw < F;
+    const int f = min(fw, F - V);
+    const char* xb = reinterpret_cast<const char*>(x);
+    const char* mb = reinterpret_cast<const char*>(mask);  // rows like those of x
+    const unsigned lane_off = (unsigned)f * (unsigned)sizeof(float);
+    const int head = WM == kHeads ? f / per_head : 0;
+    const char* wb = reinterpret_cast<const char*>(w);
+    const unsigned head_off = 4u * (unsigned)head;
+    float acc[CH][V];
+    int arg[V];
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+      for (int v = 0; v < V; ++v) acc[c][v] = 0.0f;
+#pragma unroll
+    for (int v = 0; v < V; ++v) arg[v] = -1;
+
+    // rounds of kIds edges per slot: place I of a round is edge j0 + I * split,
+    // the `split` slots of an item taking neighbouring edges
+    for (int r0 = 0; r0 < nmax; r0 += kIds * split) {
+      const int j0 = r0 + sub;
+      // ids (as byte offsets when NARROW), edge ids and weights of the round;
+      // places past the item's end repeat its last edge
+      int id[NR], pe[NR], wt[NR];
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const int j = min(j0 + (r * BW + sl % BW) * split, n - 1);
+        id[r] = n > 0 ? col[kbeg + j] : 0;
+        pe[r] = (need_perm && n > 0) ? perm[kbeg + j] : 0;
+        if constexpr (WM == kEdge)
+          wt[r] = __float_as_int(
+              n > 0 ? w[w_by_perm ? pe[r] : kbeg + j] : 0.0f);
+        if constexpr (NARROW) id[r] = id[r] * (int)row_bytes;
+        if constexpr (WM == kHeads) {  // the edge's row of weights (its byte offset)
+          wt[r] = n > 0 ? (w_by_perm ? pe[r] : kbeg + j) : 0;
+          if constexpr (NARROW) wt[r] = wt[r] * 4 * H;
+        }
+      }
+      each<kIds / U>([&](auto g_) {
+        constexpr int G = decltype(g_)::value;
+        if (r0 + G * U * split < nmax) {  // uniform
+          float xv[U][V], wh[U];
+          int mv[MASK ? U : 1][V];
+          each<U>([&](auto u_) {
+            constexpr int u = decltype(u_)::value, I = G * U + u;
+            if constexpr (WM == kHeads && NARROW) {
+              wh[u] = *reinterpret_cast<const float*>(wb + ((unsigned)slot_bcast<I, LPS>(wt) + head_off));
+            } else if constexpr (WM == kHeads) {
+              wh[u] = w[(int64_t)slot_bcast<I, LPS>(wt) * H + head];
+            }
+            const int c = slot_bcast<I, LPS>(id);
+            if constexpr (MASK) {
+              load_irow<V>(row_at<NARROW, int>(mb, c, row_bytes, lane_off), mv[u]);
+            } else {
+              load_row<V>(row_at<NARROW, float>(xb, c, row_bytes, lane_off), xv[u]);
+            }
+          });
+          if constexpr (MASK) {
+            // a row of x is read only where this edge won one of its columns
+            each<U>([&](auto u_) {
+              constexpr int u = decltype(u_)::value, I = G * U + u;
+              const int c = slot_bcast<I, LPS>(id), e = slot_bcast<I, LPS>(pe);
+              bool any = false;
+#pragma unroll
+              for (int v = 0; v < V; ++v) any |= mv[u][v] == e;
+              if (any & (j0 + I * split < n)) {
+                load_row<V>(row_at<NARROW, float>(xb, c, row_bytes, lane_off), xv[u]);
+#pragma unroll
+                for (int v = 0; v < V; ++v) xv[u][v] = mv[u][v] == e ? xv[u][v] : 0.0f;
+              } else {
+#pragma unroll
+                for (int v = 0; v < V; ++v) xv[u][v] = 0.0f;
+              }
+            });
+          }
+          each<U>([&](auto u_) {
+            constexpr int u = decltype(u_)::value, I = G * U + u;
+            float we = 1.0f;
+            if constexpr (WM == kHeads) we = wh[u];
+            if constexpr (WM == kEdge) we = __int_as_float(slot_bcast<I, LPS>(wt));
+            if constexpr (MAX) {
+              // repeated last edges never win: strict comparison
+              const int e = slot_bcast<I, LPS>(pe);
+#pragma unroll
+              for (int v = 0; v < V; ++v) {
+                const float m = WM == kNone ? xv[u][v] : we * xv[u][v];
+                bool take = m > acc[0][v];
+                if (KIND == kMaxTies) take |= (m == acc[0][v]) & (e < arg[v]);
+                if (I == 0) take |= r0 == 0;  // a slot's first edge always
+                acc[0][v] = take ? m : acc[0][v];
+                arg[v] = take ? e : arg[v];
+              }
+            } else {
+              if (j0 + I * split < n)
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                  acc[u % CH][v] = WM == kNone ? acc[u % CH][v] + xv[u][v]
+                                               : __builtin_fmaf(we, xv[u][v], acc[u % CH][v]);
+            }
+          });
+        }
+      });
+    }
+    if constexpr (!MAX) {
+#pragma unroll
+      for (int step = 1; step < CH; step <<= 1)
+#pragma unroll
+        for (int c = 0; c + step < CH; c += 2 * step)
+#pragma unroll
+          for (int v = 0; v < V; ++v) acc[c][v] += acc[c + step][v];
+    }
+    // the slots of one item, pairwise
+#pragma unroll
+    for (int i = 1; i < SLOTS; i <<= 1)
+      if (split > i) {  // uniform
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          const float ov = __shfl_xor(acc[0][v], LPS * i);
+          if constexpr (MAX) {
+            const int oa = __shfl_xor(arg[v], LPS * i);
+            max_combine(acc[0][v], arg[v], ov, oa);
+          } else {
+            acc[0][v] += ov;
+          }
+        }
+      }
+    if (!have || !fok || sub != 0) continue;
+    if (it.slot < 0) {
+      if constexpr (MAX) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          acc[0][v] = n == 0 ? 0.0f : acc[0][v];
+          arg[v] = n == 0 ? -1 : arg[v];
+        }
+      } else {
+        if (mean && n > 0) {
+          const float cnt = (float)n;
+#pragma unroll
+          for (int v = 0; v < V; ++v) acc[0][v] = acc[0][v] / cnt;
+        }
+        if (ep.h != nullptr) {
+          float t[V];
+          load_row<V>(ep.h + (int64_t)it.row * ep.ldh + f, t);
+#pragma unroll
+          for (int v = 0; v < V; ++v) acc[0][v] = ep.scale * acc[0][v] + ep.alpha * t[v];
+        } else if (ep.scale != 1.0f) {
+#pragma unroll
+          for (int v = 0; v < V; ++v) acc[0][v] = ep.scale * acc[0][v];
+        }
+      }
+      store_row<V>(out + (int64_t)it.row * F + f, acc[0]);
+      if (MAX && argout != nullptr) store_irow<V>(argout + (int64_t)it.row * F + f, arg);
+    } else {
+      store_row<V>(part + (int64_t)it.slot * F + f, acc[0]);
+      if (MAX) store_irow<V>(part_arg + (int64_t)it.slot * F + f, arg);
+    }
+  }
+}
+
+template <int V, int LPS, int KIND, int WM>
+void run(bool narrow, const SlotLists& L, int waves, const RowArgs& a, hipStream_t s) {
+#define TFG_SLOTS(N)                                                                      \
+  spmm_slots<V, LPS, KIND, WM, N><<<(unsigned)waves, kItemBlock, 0, s>>>(                 \
+      L, a.col, a.perm, a.w, a.w_by_perm, a.H, a.per_head, a.x, a.ldx, a.mask, a.F, a.mean, \
+      a.out, a.argout, a.part, a.part_arg, a.ep)
+  if (narrow) TFG_SLOTS(true);
+  else TFG_SLOTS(false);
+#undef TFG_SLOTS
+}
+
+template <int V, int KIND, int WM>
+void by_lps(int lps, bool narrow, const SlotLists& L, int waves, const RowArgs& a, hipStream_t s) {
+  switch (lps) {
+    case 4: run<V, 4, KIND, WM>(narrow, L, waves, a, s); break;
+    case 8: run<V, 8, KIND, WM>(narrow, L, waves, a, s); break;
+    case 16: run<V, 16, KIND, WM>(narrow, L, waves, a, s); break;
+    case 32: run<V, 32, KIND, WM>(narrow, L, waves, a, s); break;
+    default: run<V, 64, KIND, WM>(narrow, L, waves, a, s); break;
+  }
+}
+
+}  // namespace
+}  // namespace rows
+}  // namespace tfg

@@ -64,30 +64,32 @@ struct Graph {
   int* key = nullptr;       // [E] sort key per position: target * parts + source part
   // row plan: one item per row (long rows cut into chunks + fix-up)
   WorkItem* heavy = nullptr;  // chunks of split rows; heavy[i] writes partial i
-  WorkItem* light = nullptr;  // whole rows
   SplitRow* split = nullptr;
-  int n_heavy = 0, n_light = 0, n_split = 0;
-  // the light rows again, by length: short (0..kShortRow edges, row ids,
-  // several per wavefront) and the rest (whole-row items, one per wavefront)
+  int n_heavy = 0, n_split = 0;
+  // the whole rows by length: short (0..kShortRow edges) and the rest in
+  // classes, longest first (over 64 edges, 33..64, 17..32, 9..16), each class in
+  // row order, so that neighbouring items have about one length
   WorkItem* short_rows = nullptr;  // (row, kbeg, kend, -1): one load gives a row's extent
   WorkItem* long_rows = nullptr;
   int n_short = 0, n_long = 0;
+  int n_over64 = 0, n_over32 = 0;  // the first entries of long_rows, by length
   // part plan (P > 1): one item per (part, row) segment chunk, part-major
   // order; every item writes a partial, prows[t] reduces row t's partials
   WorkItem* pexec = nullptr;
   SplitRow* prows = nullptr;
   int n_pexec = 0;
-  // device: [0] heavy, [1] light, [2] split, [3] error flags, [4] part items,
-  // [5] short rows, [6] other light rows
+  // device: [0] heavy, [1] whole rows over 64 edges, [2] split, [3] error
+  // flags, [4] part items, [5] short rows, [6] other whole rows, [7] whole rows
+  // over 32 edges
   int* counters = nullptr;
   int device = 0;
 };
 
 // Sizes of the persistent part of a graph.
 struct GraphLayout {
-  size_t rowptr, segptr, col, perm, key, heavy, light, split, pexec, prows, short_rows, long_rows,
+  size_t rowptr, segptr, col, perm, key, heavy, split, pexec, prows, short_rows, long_rows,
       counters, total;
-  int64_t cap_heavy, cap_light, cap_split, cap_pexec;
+  int64_t cap_heavy, cap_split, cap_pexec;
 };
 GraphLayout graph_layout(int64_t E, int64_t N, int parts, int chunk);
 size_t graph_scratch_bytes(int64_t E, int64_t N, int parts);

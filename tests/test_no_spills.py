@@ -21,6 +21,8 @@ sys.path.insert(0, ROOT)
 HOT = {
     "csr.hip": ["scatter_packed", "upsweep", "key_bounds"],
     "aggregate.hip": ["spmm_wide", "fixup_rows"],
+    "slots_sum.hip": ["spmm_slots"],
+    "slots_max.hip": ["spmm_slots"],
     "norm.hip": ["weights_coo_sliced", "weights_csr_parts"],
 }
 

@@ -1,0 +1,111 @@
+"""The slot aggregation at the sizes where it can go wrong: every row length around its lists'
+and rounds' edges, every width around its lane layouts, both plans, with a leading dimension
+that leaves rows at dword alignment only. Sums against the oracle at the scaled 1e-5 bound of
+float32 chains (a few hundred units of 2^-24), maxima and argmax bit for bit."""
+
+import os
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+pytestmark = pytest.mark.gpu
+
+LENGTHS = [0, 1, 2, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32, 33, 48, 63, 64, 65, 127, 128, 129, 200,
+           256, 257, 700]
+WIDTHS = [1, 2, 3, 4, 5, 7, 15, 16, 17, 31, 33, 40, 63, 64, 65, 100, 128, 130, 255, 257, 300]
+
+
+@pytest.fixture(scope="module")
+def tfg():
+    import paper_2101_11552_amd as m
+    m.load()
+    return m
+
+
+def _graph(seed, n_src, repeat):
+    """Rows of every length in LENGTHS, `repeat` times, in a random order of rows and edges."""
+    r = np.random.default_rng(seed)
+    deg = r.permutation(np.repeat(LENGTHS, repeat))
+    tgt = np.repeat(np.arange(deg.size), deg)
+    src = r.integers(0, n_src, tgt.size)
+    order = r.permutation(tgt.size)
+    return np.stack([src[order], tgt[order]]).astype(np.int64), deg.size
+
+
+def _check(orc, ei, x, n, res, reduce, w, heads):
+    if reduce == "max":
+        ref, arg = orc.aggregate(ei, x, n, "max", edge_weight=w, heads=heads)
+        assert np.array_equal(res[0].cpu().numpy().view(np.uint32), ref.view(np.uint32))
+        assert np.array_equal(res[1].cpu().numpy(), arg)
+    else:
+        ref, scale = orc.aggregate(ei, x, n, reduce, edge_weight=w, heads=heads)
+        err = np.abs(res.cpu().numpy().astype(np.float64) - ref) / np.maximum(scale, 1e-300)
+        assert float(err.max()) <= 1e-5
+
+
+@pytest.mark.parametrize("plan", ["0", "1"])
+@pytest.mark.parametrize("F", WIDTHS)
+def test_row_lengths_and_widths(tfg, orc, monkeypatch, F, plan):
+    monkeypatch.setenv("TFG_PART_PLAN", plan)
+    ei, n = _graph(F, 500, 3)
+    r = np.random.default_rng([7, F])
+    big = r.standard_normal((500, F + 3)).astype(np.float32)
+    big[:, :F][r.random((500, F)) < 0.2] = 0.0  # equal maxima
+    x = np.ascontiguousarray(big[:, :F])
+    xd = torch.from_numpy(big).cuda()[:, :F]
+    w = r.standard_normal(ei.shape[1]).astype(np.float32)
+    g = tfg.tfg_graph_create(torch.from_numpy(ei).cuda(), n, N_src=500,
+                             src_parts=4 if plan == "1" else 3)
+    for reduce in ("sum", "mean", "max"):
+        for weight in (None, w):
+            wd = None if weight is None else torch.from_numpy(weight).cuda()
+            res = tfg.tfg_aggregate(None, xd, n, reduce, edge_weight=wd, graph=g)
+            _check(orc, ei, x, n, res, reduce, weight, 1)
+
+
+@pytest.mark.parametrize("plan", ["0", "1"])
+@pytest.mark.parametrize("H,D", [(2, 1), (2, 6), (3, 7), (4, 4), (8, 8), (8, 16), (5, 20), (16, 32)])
+def test_heads(tfg, orc, monkeypatch, H, D, plan):
+    monkeypatch.setenv("TFG_PART_PLAN", plan)
+    ei, n = _graph(100 + H * D, 400, 2)
+    r = np.random.default_rng([8, H, D])
+    x = r.standard_normal((400, H * D)).astype(np.float32)
+    w = r.standard_normal((ei.shape[1], H)).astype(np.float32)
+    g = tfg.tfg_graph_create(torch.from_numpy(ei).cuda(), n, N_src=400, src_parts=2)
+    wd = torch.from_numpy(w).cuda()
+    for order, weight in (("coo", wd), ("csr", tfg.tfg_edge_reorder(wd, None, g))):
+        for reduce in ("sum", "max"):
+            res = tfg.tfg_aggregate(None, torch.from_numpy(x).cuda(), n, reduce,
+                                    edge_weight=weight, heads=H, weight_order=order, graph=g)
+            _check(orc, ei, x, n, res, reduce, w, H)
+
+
+@pytest.mark.parametrize("plan", ["0", "1"])
+@pytest.mark.parametrize("F", [1, 3, 4, 7, 16, 33, 64, 100, 130, 257])
+def test_max_gradient(tfg, orc, monkeypatch, F, plan):
+    monkeypatch.setenv("TFG_PART_PLAN", plan)
+    ei, n = _graph(300 + F, 300, 2)
+    r = np.random.default_rng([9, F])
+    x = r.standard_normal((300, F)).astype(np.float32)
+    dy = r.standard_normal((n, F)).astype(np.float32)
+    w = r.standard_normal(ei.shape[1]).astype(np.float32)
+    eid = torch.from_numpy(ei).cuda()
+    g = tfg.tfg_graph_create(eid, n, N_src=300, src_parts=2)
+    gt = tfg.tfg_graph_create_transposed(eid, n, N_src=300, src_parts=2)
+    wd = torch.from_numpy(w).cuda()
+    _, arg = tfg.tfg_aggregate(None, torch.from_numpy(x).cuda(), n, "max", edge_weight=wd, graph=g)
+    dx, _ = tfg.tfg_aggregate_backward(g, torch.from_numpy(dy).cuda(), "max", graph_t=gt,
+                                       edge_weight=wd, argmax=arg)
+    a = arg.cpu().numpy()
+    ref, _ = orc.aggregate_backward(ei, x, n, dy, "max", edge_weight=w, arg=a)
+    # the scale of a masked sum: the same winners, with |w| and |dy|
+    m = np.zeros_like(ref)
+    for c in range(F):
+        ok = a[:, c] >= 0
+        e = a[ok, c]
+        np.add.at(m[:, c], ei[0][e], np.abs(w[e].astype(np.float64) * dy[ok, c]))
+    err = np.abs(dx.cpu().numpy() - ref) / np.maximum(m, 1e-300)
+    assert float(np.where(m > 0, err, np.abs(ref)).max()) <= 1e-5
