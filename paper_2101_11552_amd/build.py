@@ -17,7 +17,7 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libtfg.so")
 SOURCES = ["csr.hip", "norm.hip", "aggregate.hip", "slots_sum.hip", "slots_max.hip",
            "slots_heads.hip", "slots_masked.hip", "softmax.hip",
-           "gat.hip", "pool.hip", "batch.hip", "backward.hip", "api.cpp"]
+           "gat.hip", "gat_dot.hip", "pool.hip", "batch.hip", "backward.hip", "api.cpp"]
 # measurement probes for the benchmark (include/tfg_probe.h), a library of their own
 PROBE_LIB = os.path.join(HERE, "libtfg_probe.so")
 PROBE_SOURCES = ["probe.hip"]

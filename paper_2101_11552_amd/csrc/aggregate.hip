@@ -257,16 +257,12 @@ void launch_wide(int n_items, hipStream_t s, const RowArgs& a, int64_t n_src) {
 // an item takes more slots until each has one round of edges.
 constexpr int kIdRound = 16;      // edges a slot takes per round of ids
 constexpr int kChipWaves = 8192;  // wavefronts in flight: 256 CUs x 4 SIMDs x 8
-void launch_slots(const Graph& g, const RowArgs& a, bool mx, bool heads, bool masked,
-                  bool part_plan, hipStream_t s) {
-  // (heads of columns that are no multiple of 4: a lane's columns stay in one head)
-  int v = a.F >= 4 ? 4 : 1;
-  if (heads && a.per_head % 4 != 0) v = a.per_head % 2 == 0 && !mx && !masked ? 2 : 1;
-  const int need = std::min((a.F + v - 1) / v, kWave);
-  int lps = 4;
-  while (lps < need) lps <<= 1;
+}  // namespace
+
+namespace rows {
+void slot_lists(const Graph& g, const WorkItem* pieces, int n_pieces, bool part_plan, int lps,
+                bool heads, SlotLists& L, int* waves) {
   const int slots = kWave / lps;
-  SlotLists L{};
   // edges: of the list's longest item; least, total: see above (total items)
   auto add = [&](int i, const WorkItem* items, int n, int edges, int least, int total) {
     L.items[i] = items;
@@ -279,16 +275,30 @@ void launch_slots(const Graph& g, const RowArgs& a, bool mx, bool heads, bool ma
     L.waves[i] = (int)(((int64_t)n * sp + slots - 1) / slots);
   };
   if (part_plan) {
-    add(0, a.heavy, a.n_heavy, g.chunk, 1, a.n_heavy);
+    add(0, pieces, n_pieces, g.chunk, 1, n_pieces);
   } else {
-    const int total = a.n_heavy + g.n_long + g.n_short, least = std::max(4, 32 / lps);
-    add(0, a.heavy, a.n_heavy, g.chunk, least, total);
+    const int total = n_pieces + g.n_long + g.n_short, least = std::max(4, 32 / lps);
+    add(0, pieces, n_pieces, g.chunk, least, total);
     add(1, g.long_rows, g.n_over32, g.chunk, least, total);
     add(2, g.long_rows + g.n_over32, g.n_long - g.n_over32, 32, heads ? 1 : 2, total);
     add(3, g.short_rows, g.n_short, kShortRow, 1, total);
   }
-  int waves = 0;
-  for (int i = 0; i < kSlotLists; ++i) waves += L.waves[i];
+  *waves = 0;
+  for (int i = 0; i < kSlotLists; ++i) *waves += L.waves[i];
+}
+}  // namespace rows
+
+namespace {
+void launch_slots(const Graph& g, const RowArgs& a, bool mx, bool heads, bool masked,
+                  bool part_plan, hipStream_t s) {
+  // (heads of columns that are no multiple of 4: a lane's columns stay in one head)
+  int v = a.F >= 4 ? 4 : 1;
+  if (heads && a.per_head % 4 != 0) v = a.per_head % 2 == 0 && !mx && !masked ? 2 : 1;
+  SlotLists L{};
+  const int need = std::min((a.F + v - 1) / v, kWave);
+  int lps = 4, waves;
+  while (lps < need) lps <<= 1;
+  slot_lists(g, a.heavy, a.n_heavy, part_plan, lps, heads, L, &waves);
   if (waves == 0) return;
   // byte offsets in 32 bits: rows of x, and per-head weights (past the last item's
   // end by up to a round: a margin of 2^20 rows)

@@ -152,6 +152,10 @@ struct SlotLists {
   int split[kSlotLists];
   int waves[kSlotLists];
 };
+// Fills L for a plan's items (pieces: those that write partials; the row plan's
+// whole rows follow) and lps lanes per slot, and counts the wavefronts.
+void slot_lists(const Graph& g, const WorkItem* pieces, int n_pieces, bool part_plan, int lps,
+                bool heads, SlotLists& L, int* waves);
 void slots_sum(int vec, int lps, bool narrow, const SlotLists& L, int waves, const RowArgs& a,
                hipStream_t s);
 void slots_masked(int vec, int lps, bool narrow, const SlotLists& L, int waves, const RowArgs& a,

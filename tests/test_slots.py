@@ -109,3 +109,34 @@ def test_max_gradient(tfg, orc, monkeypatch, F, plan):
         np.add.at(m[:, c], ei[0][e], np.abs(w[e].astype(np.float64) * dy[ok, c]))
     err = np.abs(dx.cpu().numpy() - ref) / np.maximum(m, 1e-300)
     assert float(np.where(m > 0, err, np.abs(ref)).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("plan", ["0", "1"])
+@pytest.mark.parametrize("H,D", [(1, 1), (1, 4), (2, 8), (8, 8), (4, 32), (8, 16), (2, 64), (5, 24),
+                                 (3, 6), (3, 7), (16, 32)])
+def test_attention_rows(tfg, orc, monkeypatch, H, D, plan):
+    """Both fused layers over rows of every length, whole or by source part, with the
+    coefficients. Scores of about one unit: their float32 error (a few 1e-7) passes through
+    the exponential unamplified and stays inside the 1e-5 bar of the sums and of alpha."""
+    monkeypatch.setenv("TFG_PART_PLAN", plan)
+    ei, n = _graph(500 + 70 * H + D, 30, 2)
+    ei[0] = np.random.default_rng(D).integers(0, n, ei.shape[1])  # square
+    r = np.random.default_rng([10, H, D])
+    q, k, h = (r.standard_normal((n, H * D)).astype(np.float32) for _ in range(3))
+    a_s, a_d = (0.5 * r.standard_normal((H, D)).astype(np.float32) for _ in range(2))
+    g = tfg.tfg_graph_create(torch.from_numpy(ei).cuda(), n, src_parts=3)
+    dv = [torch.from_numpy(t).cuda() for t in (q, k, h, a_s, a_d)]
+
+    def check(res, ref):
+        out, alpha, scale = ref
+        err = np.abs(res[0].cpu().numpy() - out) / np.maximum(scale, 1e-300)
+        assert float(err.max()) <= 1e-5
+        rel = np.abs(res[1].cpu().numpy() - alpha) / np.maximum(alpha, 1e-30)
+        assert float(rel.max()) <= 1e-5
+
+    check(tfg.tfg_gat_aggregate(g, dv[2], dv[3], dv[4], 0.2, want_alpha=True),
+          orc.gat_layer(ei, h, a_s, a_d, H, slope=np.float32(0.2)))
+    if D & (D - 1) == 0:
+        sc = np.float32(0.5 / np.sqrt(D))
+        check(tfg.tfg_gat_dot_aggregate(g, *dv[:3], H, scale=float(sc), want_alpha=True),
+              orc.dot_layer(ei, q, k, h, H, sc))
