@@ -8,7 +8,7 @@
 //                source s only through the edge that won the forward max;
 //   dw[e, k]   = sum over the columns c of head k of g[t_e, c] x[s_e, c] with
 //                g = dy, dy / deg(t) or the masked dy: one dot product per
-//                edge (edge_grad_rows), walking the forward graph so that the
+//                edge (edge_grad_slots), walking the forward graph so that the
 //                dy row of a target is loaded once.
 // Segment softmax: ds = alpha * (dalpha - sum over the segment of alpha * dalpha)
 // per head, the sum accumulated in double (softmax_grad_items; long rows in
@@ -16,8 +16,8 @@
 // Every result has one writer and a fixed summation order: no atomics.
 #include <cstdlib>
 
+#include "slots.h"
 #include "softmax_stats.h"
-#include "spmm.h"
 
 namespace tfg {
 
@@ -25,199 +25,181 @@ namespace {
 
 using namespace rows;
 
-// Value held by lane (jbase + slot); jbase is wave-uniform.
-template <int SLOTS>
-__device__ __forceinline__ int bcast(int v, int jbase, int slot) {
-  if constexpr (SLOTS == 1) {
-    return __builtin_amdgcn_readlane(v, jbase);
-  } else if constexpr (SLOTS == 2) {
-    int a = __builtin_amdgcn_readlane(v, jbase);
-    int b = __builtin_amdgcn_readlane(v, jbase + 1);
-    return slot ? b : a;
-  } else if constexpr (SLOTS == 4) {
-    int a = __builtin_amdgcn_readlane(v, jbase);
-    int b = __builtin_amdgcn_readlane(v, jbase + 1);
-    int c = __builtin_amdgcn_readlane(v, jbase + 2);
-    int d = __builtin_amdgcn_readlane(v, jbase + 3);
-    return slot == 0 ? a : slot == 1 ? b : slot == 2 ? c : d;
-  } else {
-    return __shfl(v, jbase + slot);
-  }
-}
-template <int SLOTS>
-__device__ __forceinline__ float bcastf(float v, int jbase, int slot) {
-  return __int_as_float(bcast<SLOTS>(__float_as_int(v), jbase, slot));
-}
-
 enum { kGradSum = 0, kGradMean = 1, kGradMax = 2 };
 
-// Sums each of the U values of a lane over the LPS lanes of its slot, U <= LPS
-// (powers of two), with log2(LPS) xor exchanges in which the values are also
-// transposed: at an exchange over offset o while c > 1 values remain, the
-// lane with bit o set keeps the upper half of its values and sends the lower
-// half (the partner the reverse), so c halves. After log2(U) such steps each
-// lane holds one value, the sum for index sl / (LPS / U) over its group; the
-// remaining exchanges are plain butterflies. log2(LPS) + U - 1 shuffles in
-// all, against U * log2(LPS) for U separate trees.
-template <int U, int LPS>
-__device__ __forceinline__ float transpose_sum(float (&p)[U], int sl) {
-  int cnt = U;
-#pragma unroll
-  for (int o = LPS / 2; o >= 1; o >>= 1) {
-    if (cnt > 1) {
-      const bool up = (sl & o) != 0;
-      const int half = cnt / 2;
-#pragma unroll
-      for (int j = 0; j < U / 2; ++j) {
-        if (j < half) {
-          const float send = up ? p[j] : p[j + half];
-          const float keep = up ? p[j + half] : p[j];
-          p[j] = keep + __shfl_xor(send, o);
-        }
-      }
-      cnt = half;
-    } else {
-      p[0] += __shfl_xor(p[0], o);
-    }
-  }
-  return p[0];
+// Per-edge dot products <g[t, k], x[s, k]> (dw, and the attention's scaled dot
+// products): work items in edge slots as in slots.h, the dy row of an item's
+// target in registers. Head k's D columns sit on G lanes, a power of two (the
+// last ones step back to end at column D and leave out what their neighbour
+// has; lanes past the columns add nothing); the partial products of a group of
+// four edges are summed over the G lanes with DPP moves, and lane g of a head
+// keeps edge g, so that four edges go out with one store. Columns beyond 64 lanes
+// go in passes inside a group; heads beyond them in passes over the edges.
+// One wavefront per item, each with its own tree over the lanes, took 137 us for
+// 1.35M edges and 8 heads of 16 in two launches; now 112 in one, the gathers of
+// 512-byte rows at 6 TB/s. 23M edges of 64 columns by source part: 0.68 -> 0.47
+// ms. Rows wider than 256 columns had one thread per edge (2M edges of 300
+// columns: 2.50 -> 0.32 ms).
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __int_as_float(
+                 __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
 
-// dw for the work items of the forward graph. Lanes are (edge slot, V
-// columns); each lane keeps its V columns of g[t] in registers. With one head
-// (WHOLE) the U partial dot products of a lane are summed over the slot with
-// transpose_sum; with several heads they are summed over the G lanes of each
-// head with a shift-down tree (the head's first lane holds the result).
-template <int V, int SLOTS, int MODE, bool WHOLE>
-__global__ __launch_bounds__(kItemBlock) void edge_grad_rows(
-    const WorkItem* __restrict__ items, int n_items, const int* __restrict__ rowptr,
-    const int* __restrict__ col, const int* __restrict__ perm, const float* __restrict__ x,
-    int64_t ldx, const float* __restrict__ dy, const int* __restrict__ arg, int F, int H, int G,
-    float* __restrict__ dw, int dw_by_perm, float scale) {
-  constexpr int LPS = kWave / SLOTS;
-  // 4 gathers in flight per slot with the transposing reduction keeps the
-  // kernel within 64 VGPRs (8 waves per SIMD); 8 would need 79
-  constexpr int UMAX = WHOLE ? 4 : 8;
-  constexpr int U = SLOTS * UMAX <= kWave ? UMAX : kWave / SLOTS;
-  const int wid = uniform(blockIdx.x * (kItemBlock / kWave) + threadIdx.x / kWave);
-  if (wid >= n_items) return;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int slot = lane / LPS, sl = lane % LPS;
-  const WorkItem* itp = items + wid;
-  const int row = uniform(itp->row), kbeg = uniform(itp->kbeg), kend = uniform(itp->kend);
-  if (kbeg >= kend) return;
-  const int f = sl * V;
-  const bool fok = f < F;
-  const int r = sl % G, head = sl / G;
-  const bool need_perm = MODE == kGradMax || dw_by_perm;
-
-  float gy[V];
-  int ga[V];
+// Each t[u] summed over the aligned groups of G lanes (a power of two).
+template <int U>
+__device__ __forceinline__ void lanes_sum(float (&t)[U], int G) {
+  if (G >= 2)
 #pragma unroll
-  for (int v = 0; v < V; ++v) {
-    gy[v] = 0.0f;
-    ga[v] = -1;
-  }
-  if (fok) {
-    load_row<V>(dy + (int64_t)row * F + f, gy);
-    if constexpr (MODE == kGradMean) {
-      const float cnt = (float)(rowptr[row + 1] - rowptr[row]);
+    for (int u = 0; u < U; ++u) t[u] = dpp_add<0xB1>(t[u]);  // quad lanes ^ 1
+  if (G >= 4)
 #pragma unroll
-      for (int v = 0; v < V; ++v) gy[v] = gy[v] / cnt;
-    }
-    if constexpr (MODE == kGradMax) load_irow<V>(arg + (int64_t)row * F + f, ga);
-  }
-
-  for (int kb = kbeg; kb < kend; kb += kWave) {
-    const int n = min(kWave, kend - kb);
-    const bool lok = lane < n;
-    const int cj = lok ? __builtin_nontemporal_load(col + kb + lane) : 0;
-    const int pj = (lok && need_perm) ? __builtin_nontemporal_load(perm + kb + lane) : 0;
-    for (int s0 = 0; s0 < n; s0 += SLOTS * U) {
-      float p[U];
-      int pe[U];
-      bool ok[U];
+    for (int u = 0; u < U; ++u) t[u] = dpp_add<0x4E>(t[u]);  // quad lanes ^ 2
+  if (G >= 8)
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int jb = s0 + u * SLOTS;
-        ok[u] = jb + slot < n;
-        const int c = bcast<SLOTS>(cj, jb, slot);
-        pe[u] = need_perm ? bcast<SLOTS>(pj, jb, slot) : 0;
-        float xv[V];
-        if (ok[u] && fok) {
-          load_row<V>(x + (int64_t)c * ldx + f, xv);
-        } else {
+    for (int u = 0; u < U; ++u) t[u] = dpp_add<0x141>(t[u]);  // row_half_mirror
+  if (G >= 16)
 #pragma unroll
-          for (int v = 0; v < V; ++v) xv[v] = 0.0f;
-        }
-        float acc = 0.0f;
+    for (int u = 0; u < U; ++u) t[u] = dpp_add<0x140>(t[u]);  // row_mirror
+  for (int o = 16; o < G; o <<= 1)
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-          const float t = (MODE == kGradMax && ga[v] != pe[u]) ? 0.0f : gy[v];
-          acc = __builtin_fmaf(t, xv[v], acc);
-        }
-        p[u] = acc;
-      }
-      if constexpr (WHOLE) {
-        // lane sl ends with the dot product of edge slot u = sl / (LPS / U)
-        constexpr int STRIDE = LPS / U;
-        const int u = sl / STRIDE;
-        const int j = s0 + u * SLOTS + slot;
-        const int pu = need_perm ? __shfl(pj, j & (kWave - 1)) : 0;
-        const float val = transpose_sum<U, LPS>(p, sl);
-        if (sl % STRIDE == 0 && j < n) {
-          const int64_t e = dw_by_perm ? pu : kb + j;
-          dw[e] = val * scale;
-        }
-      } else {
-        for (int off = 1; off < G; off <<= 1)
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const float o = __shfl_down(p[u], off);
-            if (r + off < G) p[u] += o;
-          }
-        if (r == 0 && fok) {
-#pragma unroll
-          for (int u = 0; u < U; ++u)
-            if (ok[u]) {
-              const int64_t e = dw_by_perm ? pe[u] : kb + s0 + u * SLOTS + slot;
-              dw[e * H + head] = p[u] * scale;
-            }
-        }
-      }
-    }
-  }
+    for (int u = 0; u < U; ++u) t[u] += __shfl_xor(t[u], o);
 }
 
-// Fallback for shapes the lane mapping above does not cover (more than 64
-// vector columns, or heads that are not a whole number of vectors): one
-// thread per (graph position, head), columns in order.
-template <int MODE>
-__global__ __launch_bounds__(kBlock) void edge_grad_simple(
-    const int* __restrict__ rowptr, int64_t N, int64_t E, const int* __restrict__ col,
+template <int V, int LPS, int MODE, bool NARROW>
+__global__ __launch_bounds__(kItemBlock) void edge_grad_slots(
+    SlotLists L, const int* __restrict__ rowptr, const int* __restrict__ col,
     const int* __restrict__ perm, const float* __restrict__ x, int64_t ldx,
-    const float* __restrict__ dy, const int* __restrict__ arg, int F, int H,
+    const float* __restrict__ dy, const int* __restrict__ arg, int H, int D, int G,
     float* __restrict__ dw, int dw_by_perm, float scale) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= E * H) return;
-  const int64_t k = i / H;
-  const int h = (int)(i - k * H);
-  int64_t lo = 0, hi = N;  // the row t with rowptr[t] <= k < rowptr[t + 1]
-  while (hi - lo > 1) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (rowptr[mid] <= k) lo = mid; else hi = mid;
+  constexpr int SLOTS = kWave / LPS;
+  constexpr int NR = id_regs<LPS>();
+  constexpr int BW = kIds / NR;
+  constexpr int U = 8, Q = 4;  // gathers in flight per slot; edges per reduction
+  int wid = blockIdx.x;
+  int li = 0;
+#pragma unroll
+  for (int i = 0; i + 1 < kSlotLists; ++i)
+    if (li == i && wid >= L.waves[i]) {  // uniform
+      wid -= L.waves[i];
+      li = i + 1;
+    }
+  const WorkItem* items = L.items[li];
+  const int n_items = L.n[li], split = L.split[li];
+  const int lane = lane_id();
+  const int sl = lane % LPS;
+  const int q = wid * SLOTS + lane / LPS;
+  const int ii = q / split, sub = q - ii * split;
+  const bool have = ii < n_items;
+  const WorkItem it = items[have ? ii : 0];
+  const int kbeg = it.kbeg, n = have ? it.kend - it.kbeg : 0;
+  int nmax = __builtin_amdgcn_readlane(n, 0);
+#pragma unroll
+  for (int s = 1; s < SLOTS; ++s) nmax = max(nmax, __builtin_amdgcn_readlane(n, s * LPS));
+  if (nmax == 0) return;
+  const int F = H * D;
+  const int64_t row_bytes = ldx * (int64_t)sizeof(float);
+  const char* xb = reinterpret_cast<const char*>(x);
+  const bool need_perm = MODE == kGradMax || dw_by_perm;
+  const float cnt = MODE == kGradMean && n > 0 ? (float)(rowptr[it.row + 1] - rowptr[it.row]) : 1.0f;
+
+  for (int p0 = 0; p0 < H * G; p0 += LPS) {
+    const int pl = p0 + sl;
+    const bool hok = pl < H * G;  // a lane of an existing head
+    const int head = hok ? pl / G : 0, g = hok ? pl - head * G : 0;
+    // the columns of pass c0: c0 + g V .., stepped back at the head's end
+    auto columns = [&](int c0, int& f, int& skip, float (&gy)[V], int (&ga)[V]) {
+      const int cw = c0 + g * V, c = min(cw, D - V);
+      f = head * D + c;
+      skip = cw - c;  // the first columns, its neighbour's
+      if (n > 0) {
+        load_row<V>(dy + (int64_t)it.row * F + f, gy);
+        if constexpr (MODE == kGradMax) load_irow<V>(arg + (int64_t)it.row * F + f, ga);
+      }
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        gy[v] = n > 0 ? gy[v] : 0.0f;
+        if constexpr (MODE == kGradMean) gy[v] = gy[v] / cnt;
+      }
+    };
+    const int cstep = G * V;            // columns per pass
+    const bool ragged = D % cstep != 0;  // some lanes skip columns
+    int f, skip;
+    float gy[V];
+    int ga[V];
+    columns(0, f, skip, gy, ga);
+    for (int r0 = 0; r0 < nmax; r0 += kIds * split) {
+      const int j0 = r0 + sub;
+      int id[NR], pe[NR];
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const int j = min(j0 + (r * BW + sl % BW) * split, n - 1);
+        id[r] = n > 0 ? col[kbeg + j] : 0;
+        pe[r] = (need_perm && n > 0) ? perm[kbeg + j] : 0;
+        if constexpr (NARROW) id[r] = id[r] * (int)row_bytes;
+      }
+      each<kIds / U>([&](auto g_) {
+        constexpr int GR = decltype(g_)::value;
+        if (r0 + GR * U * split < nmax) {  // uniform
+          float t[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) t[u] = 0.0f;
+          for (int c0 = 0; c0 < D; c0 += cstep) {
+            if (cstep < D) columns(c0, f, skip, gy, ga);  // uniform: more than one pass
+            const unsigned lane_off = (unsigned)f * (unsigned)sizeof(float);
+            float xv[U][V];
+            each<U>([&](auto u_) {
+              constexpr int u = decltype(u_)::value, I = GR * U + u;
+              load_row<V>(row_at<NARROW, float>(xb, slot_bcast<I, LPS>(id), row_bytes, lane_off),
+                          xv[u]);
+            });
+            if (ragged) {  // uniform; zeros on both sides, whatever x holds there
+#pragma unroll
+              for (int v = 0; v < V; ++v) {
+                gy[v] = v < skip ? 0.0f : gy[v];
+#pragma unroll
+                for (int u = 0; u < U; ++u) xv[u][v] = v < skip ? 0.0f : xv[u][v];
+              }
+            }
+            each<U>([&](auto u_) {
+              constexpr int u = decltype(u_)::value, I = GR * U + u;
+              const int e = MODE == kGradMax ? slot_bcast<I, LPS>(pe) : 0;
+#pragma unroll
+              for (int v = 0; v < V; ++v) {
+                const bool use = MODE == kGradMax ? ga[v] == e : true;
+                const float w = use ? gy[v] : 0.0f;
+                t[u] = __builtin_fmaf(w, xv[u][v], t[u]);
+              }
+            });
+          }
+          lanes_sum<U>(t, G);
+          // lane g of a head keeps the edges g, g + min(G, Q), ... of each Q
+          const int gl = min(G, Q);
+          each<U / Q>([&](auto b_) {
+            constexpr int b = decltype(b_)::value * Q;
+            int pq[Q];
+            if (dw_by_perm)  // uniform
+              each<Q>([&](auto i_) {
+                constexpr int i = decltype(i_)::value;
+                pq[i] = slot_bcast<GR * U + b + i, LPS>(pe);
+              });
+            for (int o = 0; o < Q; o += gl) {  // uniform
+              const int mine = o + (g & (gl - 1));
+              const int j = j0 + (GR * U + b + mine) * split;
+              float val = t[b];
+              int e = dw_by_perm ? pq[0] : kbeg + j;
+#pragma unroll
+              for (int i = 1; i < Q; ++i) {
+                val = mine == i ? t[b + i] : val;
+                if (dw_by_perm) e = mine == i ? pq[i] : e;
+              }
+              if (hok && g < gl && j < n) dw[(int64_t)e * H + head] = val * scale;
+            }
+          });
+        }
+      });
+    }
   }
-  const int64_t t = lo, s = col[k], e = perm[k];
-  const int D = F / H;
-  const float cnt = (float)(rowptr[t + 1] - rowptr[t]);
-  float acc = 0.0f;
-  for (int c = h * D; c < (h + 1) * D; ++c) {
-    float g = dy[t * F + c];
-    if (MODE == kGradMean) g = g / cnt;
-    if (MODE == kGradMax && arg[t * F + c] != (int)e) g = 0.0f;
-    acc = __builtin_fmaf(g, x[s * ldx + c], acc);
-  }
-  dw[(dw_by_perm ? e : k) * H + h] = acc * scale;
 }
 
 // Weights of the transposed graph for the mean gradient, in its graph order:
@@ -225,29 +207,33 @@ __global__ __launch_bounds__(kBlock) void edge_grad_simple(
 // weights in edge order, e = k for weights already in the transposed order;
 // t_k = col[k].
 __global__ __launch_bounds__(kBlock) void mean_weights(const int* __restrict__ tcol,
-                                                       const int* __restrict__ tperm, int64_t E,
-                                                       int H, const int* __restrict__ rowptr,
+                                                       const int* __restrict__ tperm, unsigned n,
+                                                       unsigned H, const int* __restrict__ rowptr,
                                                        const float* __restrict__ w, int by_perm,
                                                        float* __restrict__ wt) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= E * H) return;
-  const int64_t k = i / H;
-  const int h = (int)(i - k * H);
+  const unsigned i = blockIdx.x * kBlock + threadIdx.x;  // (position, head), below 2^31
+  if (i >= n) return;
+  const unsigned k = i / H, h = i - k * H;
   const int t = tcol[k];
   const float cnt = (float)(rowptr[t + 1] - rowptr[t]);
-  const float wv = w ? w[(by_perm ? (int64_t)tperm[k] : k) * H + h] : 1.0f;
+  const float wv = w ? w[(by_perm ? (int64_t)tperm[k] : (int64_t)k) * H + h] : 1.0f;
   wt[i] = wv / cnt;
 }
 
-// Graph order -> caller's edge order: out[perm[k], h] = in[k, h].
-__global__ __launch_bounds__(kBlock) void to_edge_order(const int* __restrict__ perm, int64_t E,
-                                                        int H, const float* __restrict__ in,
+// Graph order -> caller's edge order: out[perm[k], h] = in[k, h]; K values of
+// one edge per thread (E * H / K threads, below 2^31).
+template <int K>
+__global__ __launch_bounds__(kBlock) void to_edge_order(const int* __restrict__ perm, unsigned n,
+                                                        unsigned hk, const float* __restrict__ in,
                                                         float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= E * H) return;
-  const int64_t k = i / H;
-  const int h = (int)(i - k * H);
-  out[(int64_t)perm[k] * H + h] = in[i];
+  const unsigned i = blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  const unsigned k = i / hk, h = i - k * hk;
+  float v[K];
+  load_row<K>(in + (int64_t)i * K, v);
+  float* o = out + ((int64_t)perm[k] * hk + h) * K;
+  if constexpr (K == 4) *reinterpret_cast<f4*>(o) = f4{v[0], v[1], v[2], v[3]};
+  else *o = v[0];
 }
 
 // The same scatter for one value per edge on large graphs, in two passes
@@ -360,14 +346,34 @@ __global__ __launch_bounds__(kPermThreads) void perm_place(const int2* __restric
 }
 
 // Caller's edge order -> graph order: out[k, h] = in[perm[k], h].
-__global__ __launch_bounds__(kBlock) void to_graph_order(const int* __restrict__ perm, int64_t E,
-                                                         int H, const float* __restrict__ in,
+template <int K>
+__global__ __launch_bounds__(kBlock) void to_graph_order(const int* __restrict__ perm, unsigned n,
+                                                         unsigned hk, const float* __restrict__ in,
                                                          float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= E * H) return;
-  const int64_t k = i / H;
-  const int h = (int)(i - k * H);
-  out[i] = in[(int64_t)perm[k] * H + h];
+  const unsigned i = blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  const unsigned k = i / hk, h = i - k * hk;
+  float v[K];
+  load_row<K>(in + ((int64_t)perm[k] * hk + h) * K, v);
+  float* o = out + (int64_t)i * K;
+  if constexpr (K == 4) *reinterpret_cast<f4*>(o) = f4{v[0], v[1], v[2], v[3]};
+  else *o = v[0];
+}
+
+// Launches one of the two over E edges of H values (E * H below 2^31).
+template <bool TO_EDGE>
+void launch_reorder(const int* perm, int64_t E, int H, const float* in, float* out, hipStream_t s) {
+  const int K = H % 4 == 0 ? 4 : 1;
+  const unsigned hk = (unsigned)(H / K), n = (unsigned)(E * hk);
+  const unsigned nb = (unsigned)(((int64_t)n + kBlock - 1) / kBlock);
+#define TFG_REORDER(KK)                                                        \
+  do {                                                                         \
+    if (TO_EDGE) to_edge_order<KK><<<nb, kBlock, 0, s>>>(perm, n, hk, in, out); \
+    else to_graph_order<KK><<<nb, kBlock, 0, s>>>(perm, n, hk, in, out);        \
+  } while (0)
+  if (K == 4) TFG_REORDER(4);
+  else TFG_REORDER(1);
+#undef TFG_REORDER
 }
 
 // Softmax gradient ds = alpha * (dalpha - sum over the row of alpha *
@@ -625,9 +631,11 @@ __global__ __launch_bounds__(kGradSplitWaves * kWave) void softmax_grad_split(
   for (int hb = 0; hb < H; hb += HP) {
     const int h = hb + hh;
     const bool act = h < H;
+    // the chunks' sums, a share per slot, then over the slots
     double dot = 0.0;
     if (act)
-      for (int c = 0; c < nch; ++c) dot += pdot[(int64_t)(s0 + c) * H + h];
+      for (int c = slot; c < nch; c += SL) dot += pdot[(int64_t)(s0 + c) * H + h];
+    dot = slots_sum(dot, HP);
     for (int c = w; c < nch; c += kGradSplitWaves) {
       const int kb = rb + c * chunk, ke = min(re, kb + chunk);
       grad_sweep_write(perm, alpha, da, H, h, act, kb, ke, slot, SL, dot, ds);
@@ -635,81 +643,44 @@ __global__ __launch_bounds__(kGradSplitWaves * kWave) void softmax_grad_split(
   }
 }
 
-template <int V, int MODE, bool WHOLE>
-void launch_edge_grad_slots(int slots, dim3 grid, hipStream_t s, const WorkItem* items,
-                            int n_items, const Graph& g, const float* x, int64_t ldx,
-                            const float* dy, const int* arg, int F, int H, int G, float* dw,
-                            int by_perm, float scale) {
-#define TFG_EG(SL)                                                                      \
-  edge_grad_rows<V, SL, MODE, WHOLE><<<grid, kItemBlock, 0, s>>>(                       \
-      items, n_items, g.rowptr, g.col, g.perm, x, ldx, dy, arg, F, H, G, dw, by_perm, scale)
-  switch (slots) {
-    case 1: TFG_EG(1); break;
-    case 2: TFG_EG(2); break;
-    case 4: TFG_EG(4); break;
-    case 8: TFG_EG(8); break;
-    default: TFG_EG(16); break;
-  }
-#undef TFG_EG
-}
-
 template <int MODE>
 int launch_edge_grad(const Graph& g, const float* x, int64_t ldx, const float* dy,
                      const int* arg, int64_t F, int H, float* dw, int by_perm, hipStream_t s,
                      float scale = 1.0f) {
   const int D = (int)(F / H);
-  auto fits = [&](int v) {
-    return D % v == 0 && ldx % v == 0 && reinterpret_cast<uintptr_t>(x) % (4 * v) == 0 &&
-           reinterpret_cast<uintptr_t>(dy) % (4 * v) == 0 &&
-           (arg == nullptr || reinterpret_cast<uintptr_t>(arg) % (4 * v) == 0);
-  };
-  const int vec = fits(4) ? 4 : fits(2) ? 2 : 1;
-  if (F / vec > kWave) {
-    const int64_t n = g.E * H;
-    edge_grad_simple<MODE><<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, s>>>(
-        g.rowptr, g.N, g.E, g.col, g.perm, x, ldx, dy, arg, (int)F, H, dw, by_perm, scale);
-    TFG_LAUNCHED("edge_grad_simple");
-    return TFG_OK;
+  const int vec = D >= 4 ? 4 : 1;
+  int G = 1;  // lanes per head
+  while (G < kWave && G * vec < D) G <<= 1;
+  int lps = 4, waves;
+  while (lps < std::min<int64_t>((int64_t)H * G, kWave)) lps <<= 1;
+  SlotLists L{};
+  const bool part_plan = use_part_plan(g, F);
+  slot_lists(g, part_plan ? g.pexec : g.heavy, part_plan ? g.n_pexec : g.n_heavy, part_plan, lps,
+             true, L, &waves);
+  if (waves == 0) return TFG_OK;
+  const bool narrow = (double)g.N_src * (double)ldx * 4.0 < 2147483648.0;
+#define TFG_EG(VV, LL)                                                                        \
+  do {                                                                                        \
+    if (narrow)                                                                               \
+      edge_grad_slots<VV, LL, MODE, true><<<(unsigned)waves, kItemBlock, 0, s>>>(             \
+          L, g.rowptr, g.col, g.perm, x, ldx, dy, arg, H, D, G, dw, by_perm, scale);          \
+    else                                                                                      \
+      edge_grad_slots<VV, LL, MODE, false><<<(unsigned)waves, kItemBlock, 0, s>>>(            \
+          L, g.rowptr, g.col, g.perm, x, ldx, dy, arg, H, D, G, dw, by_perm, scale);          \
+  } while (0)
+#define TFG_EG_LPS(VV)                   \
+  switch (lps) {                         \
+    case 4: TFG_EG(VV, 4); break;        \
+    case 8: TFG_EG(VV, 8); break;        \
+    case 16: TFG_EG(VV, 16); break;      \
+    case 32: TFG_EG(VV, 32); break;      \
+    default: TFG_EG(VV, 64); break;      \
   }
-  int p2 = 1;
-  while (p2 < F / vec) p2 <<= 1;
-  const int slots = std::min(kWave / p2, 16);
-  // every edge belongs to exactly one work item of either plan (the row plan
-  // keeps its long-row chunks and its whole rows in two lists)
-  auto run = [&](const WorkItem* it, int n) {
-    if (n <= 0) return;
-    dim3 grid((unsigned)((n + kItemBlock / kWave - 1) / (kItemBlock / kWave)));
-    const int G = D / vec;
-    if (H == 1) {
-      if (vec == 4)
-        launch_edge_grad_slots<4, MODE, true>(slots, grid, s, it, n, g, x, ldx, dy, arg, (int)F,
-                                              H, G, dw, by_perm, scale);
-      else if (vec == 2)
-        launch_edge_grad_slots<2, MODE, true>(slots, grid, s, it, n, g, x, ldx, dy, arg, (int)F,
-                                              H, G, dw, by_perm, scale);
-      else
-        launch_edge_grad_slots<1, MODE, true>(slots, grid, s, it, n, g, x, ldx, dy, arg, (int)F,
-                                              H, G, dw, by_perm, scale);
-    } else {
-      if (vec == 4)
-        launch_edge_grad_slots<4, MODE, false>(slots, grid, s, it, n, g, x, ldx, dy, arg, (int)F,
-                                               H, G, dw, by_perm, scale);
-      else if (vec == 2)
-        launch_edge_grad_slots<2, MODE, false>(slots, grid, s, it, n, g, x, ldx, dy, arg, (int)F,
-                                               H, G, dw, by_perm, scale);
-      else
-        launch_edge_grad_slots<1, MODE, false>(slots, grid, s, it, n, g, x, ldx, dy, arg, (int)F,
-                                               H, G, dw, by_perm, scale);
-    }
-  };
-  if (use_part_plan(g, F)) {
-    run(g.pexec, g.n_pexec);
-  } else {
-    run(g.heavy, g.n_heavy);
-    run(g.long_rows, g.n_long);
-    run(g.short_rows, g.n_short);
-  }
-  TFG_LAUNCHED("edge_grad_rows");
+  if (vec == 4) TFG_EG_LPS(4)
+  else TFG_EG_LPS(1)
+#undef TFG_EG_LPS
+#undef TFG_EG
+  TFG_LAUNCHED("edge_grad_slots");
   return TFG_OK;
 }
 
@@ -737,7 +708,7 @@ int launch_perm_scatter(const int* perm, int64_t E, int H, const float* in, floa
   if (n == 0) return TFG_OK;
   const size_t need = perm_scatter_ws_bytes(E, H);
   if (need == 0 || ws == nullptr || ws_bytes < need) {
-    to_edge_order<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, s>>>(perm, E, H, in, out);
+    launch_reorder<true>(perm, E, H, in, out, s);
     TFG_LAUNCHED("to_edge_order");
     return TFG_OK;
   }
@@ -778,18 +749,17 @@ int launch_edge_reorder(const int* perm_from, const int* perm_to, int64_t E, int
                         const float* in, float* out, void* ws, size_t ws_bytes, hipStream_t s) {
   const int64_t n = E * H;
   if (n == 0) return TFG_OK;
-  const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
   if (perm_from != nullptr && perm_to != nullptr) {
     const size_t tb = align_up(sizeof(float) * (size_t)n, 256);
     float* tmp = static_cast<float*>(ws);
     const int rc = launch_perm_scatter(perm_from, E, H, in, tmp, static_cast<char*>(ws) + tb,
                                        ws_bytes > tb ? ws_bytes - tb : 0, s);
     if (rc) return rc;
-    to_graph_order<<<nb, kBlock, 0, s>>>(perm_to, E, H, tmp, out);
+    launch_reorder<false>(perm_to, E, H, tmp, out, s);
   } else if (perm_from != nullptr) {
     return launch_perm_scatter(perm_from, E, H, in, out, ws, ws_bytes, s);
   } else {
-    to_graph_order<<<nb, kBlock, 0, s>>>(perm_to, E, H, in, out);
+    launch_reorder<false>(perm_to, E, H, in, out, s);
   }
   TFG_LAUNCHED("edge reorder");
   return TFG_OK;
@@ -840,7 +810,7 @@ int launch_aggregate_backward(const Graph& g, const Graph* gt, const float* w, i
         float* wt = reinterpret_cast<float*>(base + off);
         off += ew;
         if (EH > 0) {
-          mean_weights<<<eb, kBlock, 0, s>>>(gt->col, gt->perm, g.E, H, g.rowptr, wg,
+          mean_weights<<<eb, kBlock, 0, s>>>(gt->col, gt->perm, (unsigned)EH, (unsigned)H, g.rowptr, wg,
                                              wg_order == TFG_COO ? 1 : 0, wt);
           TFG_LAUNCHED("mean_weights");
         }

@@ -132,24 +132,38 @@ __global__ __launch_bounds__(kBlock) void edge_scores(const IdxT* __restrict__ s
   out[i] = z >= 0.0f ? z : slope * z;
 }
 
-// The same scores over a graph handle: one thread per (graph position, head),
-// the source from col, the target from the stored sort key (target * parts +
-// part), written at the position (graph order) or at the edge id perm[k]
-// (the caller's order). Same operands and operations as edge_scores.
+// The same scores over a graph handle: one thread per graph position and K
+// heads, the source from col, the target from the stored sort key (target *
+// parts + part), written at the position (graph order) or at the edge id
+// perm[k] (the caller's order). Same operands and operations as edge_scores.
+// (E * H is below 2^31 here. One thread per head and a 64-bit division took 37 us
+// for 1.35M edges and 8 heads.)
+template <int K>
 __global__ __launch_bounds__(kBlock) void edge_scores_graph(const int* __restrict__ col,
                                                             const int* __restrict__ key,
                                                             const int* __restrict__ perm,
-                                                            int parts, int64_t E, int H,
+                                                            int parts, unsigned n, unsigned hk,
                                                             const float* __restrict__ as,
                                                             const float* __restrict__ ad,
                                                             float slope, float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // (position, head)
-  if (i >= E * H) return;
-  const int64_t k = i / H;
-  const int h = (int)(i - k * H);
-  const int64_t sv = col[k], t = key[k] / parts;
-  const float z = as[sv * H + h] + ad[t * H + h];
-  out[(int64_t)edge_at(perm, (int)k) * H + h] = z >= 0.0f ? z : slope * z;
+  const unsigned i = blockIdx.x * kBlock + threadIdx.x;  // (position, K heads)
+  if (i >= n) return;
+  const unsigned k = i / hk, h = i - k * hk;
+  const int64_t sv = col[k], t = parts == 1 ? key[k] : key[k] / parts;
+  const float* a = as + (sv * hk + h) * K;
+  const float* b = ad + (t * hk + h) * K;
+  float* o = out + ((int64_t)edge_at(perm, (int)k) * hk + h) * K;
+  float z[K];
+  if constexpr (K == 4) {
+    const f4 u = *reinterpret_cast<const f4*>(a), v = *reinterpret_cast<const f4*>(b);
+    z[0] = u.x + v.x; z[1] = u.y + v.y; z[2] = u.z + v.z; z[3] = u.w + v.w;
+  } else {
+    z[0] = a[0] + b[0];
+  }
+#pragma unroll
+  for (int j = 0; j < K; ++j) z[j] = z[j] >= 0.0f ? z[j] : slope * z[j];
+  if constexpr (K == 4) *reinterpret_cast<f4*>(o) = f4{z[0], z[1], z[2], z[3]};
+  else o[0] = z[0];
 }
 
 // Short rows (at most kShortRow edges), 64 / HP per wavefront: lane (r, hh)
@@ -521,9 +535,11 @@ __global__ __launch_bounds__(kSplitWaves * kWave) void softmax_split(
     const bool act = h < H;
     float m = -__builtin_huge_valf();
     double d = 0.0;
+    // the chunks' pairs, a share per slot, then over the slots
     if (act)
-      for (int c = 0; c < nch; ++c)
+      for (int c = slot; c < nch; c += SL)
         stat_merge(m, d, pm[(int64_t)(s0 + c) * H + h], pd[(int64_t)(s0 + c) * H + h]);
+    slots_merge(m, d, HP);
     const double r = 1.0 / d;
     for (int c = w; c < nch; c += kSplitWaves) {
       const int kb = rb + c * chunk, ke = min(re, kb + chunk);
@@ -575,9 +591,15 @@ int launch_gat_graph_scores(const Graph& g, const float* h, int H, int D, const 
     TFG_LAUNCHED("node_projections");
   }
   if (g.E * H > 0) {
-    const unsigned nb = (unsigned)((g.E * H + kBlock - 1) / kBlock);
-    edge_scores_graph<<<nb, kBlock, 0, s>>>(g.col, g.key, by_perm ? g.perm : nullptr, g.parts, g.E,
-                                            H, as, ad, slope, out);
+    // (16-byte accesses: the projections sit in the workspace, rows of 4-head groups)
+    const int K = H % 4 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0 && g.N * H % 4 == 0 ? 4 : 1;
+    const unsigned hk = (unsigned)(H / K), n = (unsigned)(g.E * hk);
+    const unsigned nb = (unsigned)(((int64_t)n + kBlock - 1) / kBlock);
+    const int* perm = by_perm ? g.perm : nullptr;
+    if (K == 4)
+      edge_scores_graph<4><<<nb, kBlock, 0, s>>>(g.col, g.key, perm, g.parts, n, hk, as, ad, slope, out);
+    else
+      edge_scores_graph<1><<<nb, kBlock, 0, s>>>(g.col, g.key, perm, g.parts, n, hk, as, ad, slope, out);
     TFG_LAUNCHED("edge_scores_graph");
   }
   return TFG_OK;

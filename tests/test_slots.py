@@ -140,3 +140,37 @@ def test_attention_rows(tfg, orc, monkeypatch, H, D, plan):
         sc = np.float32(0.5 / np.sqrt(D))
         check(tfg.tfg_gat_dot_aggregate(g, *dv[:3], H, scale=float(sc), want_alpha=True),
               orc.dot_layer(ei, q, k, h, H, sc))
+
+
+@pytest.mark.parametrize("plan", ["0", "1"])
+@pytest.mark.parametrize("H,D", [(1, 1), (1, 3), (1, 7), (1, 16), (1, 33), (1, 64), (1, 100),
+                                 (1, 256), (1, 300), (2, 2), (3, 5), (8, 16), (4, 24), (5, 20),
+                                 (16, 32), (2, 258)])
+def test_edge_gradients(tfg, orc, monkeypatch, H, D, plan):
+    monkeypatch.setenv("TFG_PART_PLAN", plan)
+    ei, n = _graph(700 + 11 * H + D, 200, 1)
+    r = np.random.default_rng([11, H, D])
+    F = H * D
+    big = r.standard_normal((200, F + 1)).astype(np.float32)
+    x = np.ascontiguousarray(big[:, :F])
+    dy = r.standard_normal((n, F)).astype(np.float32)
+    w = r.standard_normal((ei.shape[1], H)).astype(np.float32)
+    g = tfg.tfg_graph_create(torch.from_numpy(ei).cuda(), n, N_src=200, src_parts=2)
+    xd, dyd, wd = torch.from_numpy(big).cuda()[:, :F], torch.from_numpy(dy).cuda(), torch.from_numpy(w).cuda()
+    perm = tfg.tfg_graph_csr(g)[2].cpu().numpy()
+    for reduce in ("sum", "mean", "max"):
+        a = ad = None
+        if reduce == "max":
+            _, ad = tfg.tfg_aggregate(None, xd, n, "max", edge_weight=wd, heads=H, graph=g)
+            a = ad.cpu().numpy()
+        _, ref = orc.aggregate_backward(ei, x, n, dy, reduce, edge_weight=w, heads=H, arg=a)
+        _, scale = orc.aggregate_backward(ei, np.abs(x), n, np.abs(dy), reduce, edge_weight=w,
+                                          heads=H, arg=a)
+        for order in ("coo", "csr"):
+            _, dw = tfg.tfg_aggregate_backward(g, dyd, reduce, x=xd, edge_weight=wd, heads=H,
+                                               argmax=ad, want_dx=False, want_dw=True,
+                                               dw_order=order)
+            got = dw.cpu().numpy()
+            want, s = (ref, scale) if order == "coo" else (ref[perm], scale[perm])
+            err = np.abs(got - want) / np.maximum(s, 1e-300)
+            assert float(np.where(s > 0, err, np.abs(got)).max()) <= 1e-5
