@@ -65,9 +65,12 @@ int check_ws(const void* ws, size_t bytes, size_t need) {
 // thread's pinned buffer when there is one, and synchronises the stream.
 int read_back(hipStream_t s, int n, const int* const* from, int* to) {
   int* pin = readback_buffer();
-  int* buf = pin ? pin : to;
-  for (int i = 0; i < n; ++i)
-    TFG_HIP(hipMemcpyAsync(buf + i, from[i], sizeof(int), hipMemcpyDeviceToHost, s));
+  if (pin) {
+    if (int rc = launch_read_ints(n, from, pin, s)) return rc;
+  } else {
+    for (int i = 0; i < n; ++i)
+      TFG_HIP(hipMemcpyAsync(to + i, from[i], sizeof(int), hipMemcpyDeviceToHost, s));
+  }
   TFG_HIP(hipStreamSynchronize(s));
   if (pin)
     for (int i = 0; i < n; ++i) to[i] = pin[i];

@@ -25,12 +25,15 @@ constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;  // 2048
 
-constexpr int kSortThreads = 1024;                    // 16 waves
-constexpr int kSortItems = 8;                         // items per thread
-constexpr int kSortTile = kSortThreads * kSortItems;  // 8192 edges per tile
-constexpr int kSortWaves = kSortThreads / kWave;
-constexpr int kUpThreads = 512;                       // counting pass: threads per tile
-constexpr int kUpItems = kSortTile / kUpThreads;
+// Edges per sort tile: 8 per thread of a scatter block of T threads. 8192 (T =
+// 1024) on large graphs; smaller tiles where 64 of them hold the graph, since a
+// block of 16 waves then works through a tile that four waves on as many SIMDs
+// finish sooner, on CUs that would stand idle (13,264 edges: scatters 12.3 + 10.9
+// us with two tiles of 8192).
+constexpr int kSortItems = 8;  // items per thread
+constexpr int kMaxSortThreads = 1024;
+constexpr int kMinSortThreads = 256;
+constexpr int kUpThreads = 512;  // counting pass: threads per tile
 constexpr int kMaxDigitBits = 8;
 constexpr int kMaxRadix = 1 << kMaxDigitBits;         // 256
 constexpr int kXcds = 8;
@@ -215,13 +218,14 @@ int64_t scan_tiles(int64_t n) { return (n + kScanTile - 1) / kScanTile; }
 // hist[d * ntiles + tile]; an exclusive scan of the whole table then gives
 // every (digit, tile) its output offset. The first pass also validates the
 // ids.
-template <bool FIRST, typename IdxT>
+template <bool FIRST, typename IdxT, int T>
 __global__ __launch_bounds__(kUpThreads) void upsweep(const IdxT* __restrict__ src,
                                                         const IdxT* __restrict__ tgt, KeyMap m,
                                                         const int* __restrict__ keys, int64_t E,
                                                         int shift, int dbits,
                                                         int* __restrict__ hist,
-                                                        int* __restrict__ err) {
+                                                        int* __restrict__ bad_tiles) {
+  constexpr int kSortTile = T * kSortItems, kUpItems = kSortTile / kUpThreads;
   // one histogram per wave: equal digits (a hub target's edges) then contend
   // only within a wave
   __shared__ int h[kUpThreads / kWave][kMaxRadix];
@@ -266,8 +270,8 @@ __global__ __launch_bounds__(kUpThreads) void upsweep(const IdxT* __restrict__ s
     // (a logical shift: packed words use the sign bit)
     if (p < tile_n) atomicAdd(&h[wave][(int)((unsigned)k >> shift) & (radix - 1)], 1);
   }
-  if (FIRST && any_bad) atomicOr(err, kErrIndex);
-  __syncthreads();
+  const int bad_here = FIRST ? __syncthreads_or(any_bad) : (__syncthreads(), 0);
+  if (FIRST && threadIdx.x == 0) bad_tiles[blockIdx.x] = bad_here;
   for (int d = threadIdx.x; d < radix; d += kUpThreads) {
     int c = 0;
 #pragma unroll
@@ -276,26 +280,49 @@ __global__ __launch_bounds__(kUpThreads) void upsweep(const IdxT* __restrict__ s
   }
 }
 
-// Tables of at most this many tiles are not scanned by a launch of their own:
-// every scatter block adds up the counts it needs from the raw table.
-constexpr int kInBlockTiles = 64;
+// Small digit tables are not scanned by a launch of their own: every scatter
+// block adds up the counts it needs from the raw table, T / radix threads per
+// digit, while that is at most this many loads a thread (89 tiles of 64 digits by
+// 1024 threads: six loads, 2 us; the scan of the table took 6.2 us and a launch).
+constexpr int kInBlockLoads = 16;
+// Smaller tiles are taken while it is at most this many (256 digits, 108,365
+// edges: 53 tiles of 2048 would be 53 loads a thread and 20 us a scatter, 14 tiles
+// of 8192 four loads and 17 us).
+constexpr int kSmallTileLoads = 8;
+constexpr int64_t table_loads(int64_t ntiles, int radix, int threads) {
+  return ntiles * radix / threads;
+}
 
-// Output offset of digit d's run in this tile. scanned: hist holds the
-// exclusive scan of the digit-major table (the offset itself); otherwise the
-// raw counts, and the offset is the total of the digits below d plus the
-// counts of d in the tiles before this one. Every thread of the block calls
-// it (a block scan inside when !scanned); threads d >= radix get 0.
-__device__ __forceinline__ int tile_offset(const int* __restrict__ hist, int d, int radix,
-                                           int ntiles, int tile, int scanned, int* tmp) {
-  if (scanned) return d < radix ? hist[(int64_t)d * ntiles + tile] : 0;
+// Output offset of digit d = threadIdx.x's run in this tile (0 for threads past
+// the radix). scanned: hist holds the exclusive scan of the digit-major table
+// (the offset itself); otherwise the raw counts, and the offset is the total of
+// the digits below d plus the counts of d in the tiles before this one. Every
+// thread of the block calls it; lpre, ltot: kMaxRadix ints of LDS each.
+template <int T>
+__device__ __forceinline__ int tile_offset(const int* __restrict__ hist, int radix, int ntiles,
+                                           int tile, int scanned, int* tmp, int* lpre, int* ltot) {
+  const int tid = (int)threadIdx.x;
+  if (scanned) return tid < radix ? hist[(int64_t)tid * ntiles + tile] : 0;
+  const int per = min(T / radix, kWave);  // threads per digit, a power of two
+  const int d = tid / per, q = tid & (per - 1);
   int pre = 0, tot = 0;
   if (d < radix)
-    for (int t = 0; t < ntiles; ++t) {
+    for (int t = q; t < ntiles; t += per) {
       const int h = hist[d * ntiles + t];
       tot += h;
       pre += t < tile ? h : 0;
     }
-  return block_excl_scan<kSortWaves>(d < radix ? tot : 0, tmp, nullptr) + (d < radix ? pre : 0);
+  for (int o = 1; o < per; o <<= 1) {
+    tot += __shfl_xor(tot, o);
+    pre += __shfl_xor(pre, o);
+  }
+  if (d < radix && q == 0) {
+    lpre[d] = pre;
+    ltot[d] = tot;
+  }
+  __syncthreads();
+  const int t = tid < radix ? ltot[tid] : 0, p = tid < radix ? lpre[tid] : 0;
+  return block_excl_scan<T / kWave>(t, tmp, nullptr) + p;
 }
 
 // Stable scatter of one tile by one digit. Wave w owns tile positions
@@ -307,13 +334,14 @@ __device__ __forceinline__ int tile_offset(const int* __restrict__ hist, int d, 
 // ids in two buffers, then source ids) and written out so that consecutive
 // threads write consecutive addresses of a digit's run.
 //   FIRST: keys and payloads come from edge_index (payload: edge id, source)
-// (16-wave blocks; at most 64 VGPRs so that two blocks fit on a CU)
-template <bool FIRST, typename IdxT>
-__global__ __launch_bounds__(kSortThreads, 8) void scatter(
+// (at most 64 VGPRs: two 16-wave blocks fit on a CU)
+template <bool FIRST, typename IdxT, int T>
+__global__ __launch_bounds__(T, 8) void scatter(
     const IdxT* __restrict__ src, const IdxT* __restrict__ tgt, KeyMap m,
     const int* __restrict__ kin, const int* __restrict__ ein, const int* __restrict__ sin,
     int64_t E, int shift, int dbits, const int* __restrict__ hist, int ntiles, int scanned,
     int* __restrict__ kout, int* __restrict__ eout, int* __restrict__ sout) {
+  constexpr int kSortThreads = T, kSortTile = T * kSortItems, kSortWaves = T / kWave;
   __shared__ unsigned short wcnt[kSortWaves][kMaxRadix];
   __shared__ int loff[kMaxRadix];
   __shared__ int goff[kMaxRadix];
@@ -330,7 +358,7 @@ __global__ __launch_bounds__(kSortThreads, 8) void scatter(
   for (int d = lane; d < kMaxRadix; d += kWave) wcnt[wave][d] = 0;
   // the tile's output offset of digit threadIdx.x, first, while few registers
   // are live (placed in LDS with the local offsets, after the ranking)
-  const int go = tile_offset(hist, (int)threadIdx.x, radix, ntiles, tile, scanned, tmp);
+  const int go = tile_offset<T>(hist, radix, ntiles, tile, scanned, tmp, loff, goff);
   __syncthreads();
 
   // Keys and payloads are loaded together up front (one round of memory
@@ -492,12 +520,13 @@ __device__ __forceinline__ int first_digit(unsigned a, unsigned b, const KeyMap&
 // A and B); 1: a middle pass (A and B to A and B); 2: the last pass (A and B
 // to the sorted key, edge id and source). `shift` is the digit's position in
 // the key (first pass) or in A (the other passes).
-template <int MODE, typename IdxT>
-__global__ __launch_bounds__(kSortThreads, 8) void scatter_packed(
+template <int MODE, typename IdxT, int T>
+__global__ __launch_bounds__(T, 8) void scatter_packed(
     const IdxT* __restrict__ src, const IdxT* __restrict__ tgt, KeyMap m, PackMap q,
     const unsigned* __restrict__ ain, const unsigned* __restrict__ bin, int64_t E, int shift,
     int dbits, const int* __restrict__ hist, int ntiles, int scanned, int* __restrict__ o0,
     int* __restrict__ o1, int* __restrict__ o2) {
+  constexpr int kSortThreads = T, kSortTile = T * kSortItems, kSortWaves = T / kWave;
   __shared__ unsigned short wcnt[kSortWaves][kMaxRadix];
   __shared__ int loff[kMaxRadix];
   __shared__ int goff[kMaxRadix];
@@ -514,7 +543,7 @@ __global__ __launch_bounds__(kSortThreads, 8) void scatter_packed(
   for (int d = lane; d < kMaxRadix; d += kWave) wcnt[wave][d] = 0;
   // the tile's output offset of digit threadIdx.x, first, while few registers
   // are live (placed in LDS with the local offsets, after the ranking)
-  const int go = tile_offset(hist, (int)threadIdx.x, radix, ntiles, tile, scanned, tmp);
+  const int go = tile_offset<T>(hist, radix, ntiles, tile, scanned, tmp, loff, goff);
   __syncthreads();
 
   // pk: the digit in the upper half, below it first the rank within the
@@ -749,14 +778,31 @@ __device__ __forceinline__ void place_row(int64_t r, int beg, int deg, int chunk
   }
 }
 
-// List lengths to the counters of the graph.
-__device__ __forceinline__ void write_counters(const int (&tot)[kLists], int* __restrict__ counters) {
-  counters[0] = tot[0];
-  counters[2] = tot[1];
-  counters[5] = tot[2];
-  counters[6] = tot[3] + tot[4] + tot[5] + tot[6];
-  counters[1] = tot[3];
-  counters[7] = tot[3] + tot[4];
+// List lengths and the id check to the counters of the graph, and to `host`
+// (pinned host memory of the calling thread, or NULL), which the caller reads
+// after it has waited for the stream: no copy is enqueued for them. Thread 0 of
+// a block writes; the tiles' checks are gathered by the whole block.
+__device__ __forceinline__ void write_counters(const int (&tot)[kLists], const int* bad, int ntiles,
+                                               int* __restrict__ counters, int* __restrict__ host) {
+  int any = 0;
+  for (int i = threadIdx.x; i < ntiles; i += blockDim.x) any |= bad[i];
+  any = __syncthreads_or(any);
+  if (threadIdx.x != 0) return;
+  const int c[8] = {tot[0], tot[3], tot[1], any ? kErrIndex : 0, 0, tot[2],
+                    tot[3] + tot[4] + tot[5] + tot[6], tot[3] + tot[4]};
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    counters[i] = c[i];
+    if (host != nullptr) host[i] = c[i];
+  }
+}
+
+// The counters of a graph without rows.
+__global__ __launch_bounds__(kWlThreads) void worklist_none(const int* __restrict__ bad, int ntiles,
+                                                            int* __restrict__ counters,
+                                                            int* __restrict__ host) {
+  const int tot[kLists] = {};
+  write_counters(tot, bad, ntiles, counters, host);
 }
 
 // Entries per list of each block of rows: block_sums[list * nb + block].
@@ -777,7 +823,9 @@ __global__ __launch_bounds__(kWlThreads) void worklist_count(const int* __restri
 // each from 0), their totals after the table, and the list lengths in the
 // counters.
 __global__ __launch_bounds__(1024) void worklist_offsets(int* __restrict__ block_sums, int nb,
-                                                         int* __restrict__ counters) {
+                                                         const int* __restrict__ bad, int ntiles,
+                                                         int* __restrict__ counters,
+                                                         int* __restrict__ host) {
   __shared__ int tmp[kLists * (1024 / kWave + 1)];
   int carry[kLists] = {};
   for (int base = 0; base < nb; base += 1024) {
@@ -792,20 +840,20 @@ __global__ __launch_bounds__(1024) void worklist_offsets(int* __restrict__ block
       carry[i] += tot[i];
     }
   }
-  if (threadIdx.x == 0) {
-    write_counters(carry, counters);
+  if (threadIdx.x == 0)
 #pragma unroll
     for (int i = 0; i < kLists; ++i) block_sums[(int64_t)kLists * nb + i] = carry[i];
-  }
+  write_counters(carry, bad, ntiles, counters, host);
 }
 
 // The three steps in one block, for graphs of at most kWlSingle rows (the
 // same lists, in the same order).
 constexpr int kWlSingle = 4 * kWlThreads;
 __global__ __launch_bounds__(kWlThreads) void worklist_single(
-    const int* __restrict__ rowptr, int64_t N, int chunk, int* __restrict__ counters,
-    WorkItem* __restrict__ heavy, SplitRow* __restrict__ split,
-    WorkItem* __restrict__ short_rows, WorkItem* __restrict__ long_rows) {
+    const int* __restrict__ rowptr, int64_t N, int chunk, const int* __restrict__ bad, int ntiles,
+    int* __restrict__ counters, int* __restrict__ host, WorkItem* __restrict__ heavy,
+    SplitRow* __restrict__ split, WorkItem* __restrict__ short_rows,
+    WorkItem* __restrict__ long_rows) {
   constexpr int kChunks = kWlSingle / kWlThreads;
   __shared__ int tmp[kChunks * kWlWords * (kWlThreads / kWave + 1)];
   // every chunk's row pointers loaded before the first is used, and every
@@ -856,7 +904,7 @@ __global__ __launch_bounds__(kWlThreads) void worklist_single(
     }
     if (r < N) place_row(r, rp[j], rq[j] - rp[j], chunk, cj, o, heavy, split, short_rows, long_rows);
   }
-  if (threadIdx.x == 0) write_counters(all, counters);
+  write_counters(all, bad, ntiles, counters, host);
 }
 
 __global__ __launch_bounds__(kWlThreads) void worklist_fill(
@@ -916,12 +964,18 @@ __global__ __launch_bounds__(kBlock) void part_fill(const int* __restrict__ segp
                                                     const int* __restrict__ row_slot,
                                                     const int* __restrict__ seg_pos,
                                                     WorkItem* __restrict__ exec,
-                                                    SplitRow* __restrict__ rows) {
+                                                    SplitRow* __restrict__ rows,
+                                                    int* __restrict__ counters,
+                                                    int* __restrict__ host) {
   static_assert(kBlock < 1024, "ten bits per class hold a block's counts");
   __shared__ int tmp[3 * (kBlock / kWave + 1)];
   const int64_t t0 = (int64_t)blockIdx.x * kBlock;
   const int64_t t = t0 + threadIdx.x;
   const bool ok = t < N;
+  if (t == 0) {  // the number of items
+    counters[4] = seg_pos[N * parts];
+    if (host != nullptr) host[4] = seg_pos[N * parts];
+  }
   int slot = ok ? row_slot[t] : 0;
   const int s0 = slot;
   for (int p = 0; p < parts; ++p) {
@@ -958,7 +1012,7 @@ int ceil_log2(int64_t n) {
 }
 
 struct SortPlan {
-  int bits, passes, dbits;
+  int bits, passes, dbits, threads;  // threads: of a scatter block (tiles of 8 edges each)
   int64_t ntiles, keyspace;
 };
 
@@ -968,12 +1022,17 @@ SortPlan sort_plan(int64_t E, int64_t N, int parts) {
   p.bits = std::max(1, ceil_log2(std::max<int64_t>(p.keyspace, 2)));
   p.passes = (p.bits + kMaxDigitBits - 1) / kMaxDigitBits;
   p.dbits = (p.bits + p.passes - 1) / p.passes;
-  p.ntiles = (E + kSortTile - 1) / kSortTile;
+  p.threads = kMinSortThreads;
+  auto tiles = [&](int threads) { return (E + threads * kSortItems - 1) / (threads * kSortItems); };
+  while (p.threads < kMaxSortThreads &&
+         table_loads(tiles(p.threads), 1 << p.dbits, p.threads) > kSmallTileLoads)
+    p.threads *= 2;
+  p.ntiles = tiles(p.threads);
   return p;
 }
 
 struct ScratchLayout {
-  size_t hist, sums, bufA, bufB, wl_sums, row_items, seg_items, total;
+  size_t hist, bad, sums, bufA, bufB, wl_sums, row_items, seg_items, total;
 };
 
 ScratchLayout scratch_layout(int64_t E, int64_t N, int parts) {
@@ -988,6 +1047,7 @@ ScratchLayout scratch_layout(int64_t E, int64_t N, int parts) {
   const int64_t radix = int64_t(1) << p.dbits;
   const int64_t scan_n = std::max<int64_t>({N * parts + 1, N + 1, radix * p.ntiles});
   L.hist = take(sizeof(int) * std::max<int64_t>(radix * p.ntiles, 1));
+  L.bad = take(sizeof(int) * std::max<int64_t>(p.ntiles, 1));
   L.sums = take(sizeof(int) * std::max<int64_t>(scan_tiles(scan_n), 1));
   L.bufA = take(sizeof(int) * 3 * std::max<int64_t>(E, 1));
   L.bufB = take(p.passes >= 3 ? sizeof(int) * 3 * std::max<int64_t>(E, 1) : 0);
@@ -998,11 +1058,11 @@ ScratchLayout scratch_layout(int64_t E, int64_t N, int parts) {
   return L;
 }
 
-template <typename IdxT>
-int sort_edges(Graph& g, const IdxT* src, const IdxT* tgt, char* scratch, const ScratchLayout& L,
-               hipStream_t s) {
+template <typename IdxT, int T>
+int sort_edges(Graph& g, const SortPlan& p, const IdxT* src, const IdxT* tgt, char* scratch,
+               const ScratchLayout& L, hipStream_t s) {
+  constexpr int kSortThreads = T;
   const int64_t E = g.E;
-  const SortPlan p = sort_plan(E, g.N, g.parts);
   const KeyMap m{g.E_in, g.N_src, g.N, (int)g.part_rows, g.parts, 1.0 / (double)g.part_rows,
                  0.5 / (double)g.part_rows};
   int* keys = g.key;  // the last pass leaves the sorted keys in the graph
@@ -1013,7 +1073,7 @@ int sort_edges(Graph& g, const IdxT* src, const IdxT* tgt, char* scratch, const 
     int* base = reinterpret_cast<int*>(scratch + (b == 0 ? L.bufA : L.bufB));
     for (int j = 0; j < 3; ++j) bufs[b][j] = base + j * E;
   }
-  int* err = g.counters + 3;
+  int* bad = reinterpret_cast<int*>(scratch + L.bad);  // per tile: ids out of range
   const unsigned nt = (unsigned)p.ntiles;
   const int radix = 1 << p.dbits;
 
@@ -1034,12 +1094,12 @@ int sort_edges(Graph& g, const IdxT* src, const IdxT* tgt, char* scratch, const 
       // packed passes after the first find their digit in A
       const int dshift = (packed && !first) ? 32 - bt + shift - lp : shift;
       if (first)
-        upsweep<true, IdxT><<<nt, kUpThreads, 0, s>>>(src, tgt, m, nullptr, E, shift, p.dbits,
-                                                        hist, err);
+        upsweep<true, IdxT, T><<<nt, kUpThreads, 0, s>>>(src, tgt, m, nullptr, E, shift, p.dbits,
+                                                        hist, bad);
       else
-        upsweep<false, IdxT><<<nt, kUpThreads, 0, s>>>(src, tgt, m, bufs[cur][0], E, dshift,
-                                                         p.dbits, hist, err);
-      const int scanned = p.ntiles > kInBlockTiles;
+        upsweep<false, IdxT, T><<<nt, kUpThreads, 0, s>>>(src, tgt, m, bufs[cur][0], E, dshift,
+                                                         p.dbits, hist, bad);
+      const int scanned = table_loads(p.ntiles, radix, T) > kInBlockLoads;
       if (scanned) {
         const int rc = exclusive_scan(hist, hist, radix * p.ntiles, sums, s);
         if (rc) return rc;
@@ -1054,19 +1114,19 @@ int sort_edges(Graph& g, const IdxT* src, const IdxT* tgt, char* scratch, const 
         const unsigned* ai = reinterpret_cast<const unsigned*>(ki);
         const unsigned* bi = reinterpret_cast<const unsigned*>(ei);
         if (first)
-          scatter_packed<0, IdxT><<<nt, kSortThreads, 0, s>>>(
+          scatter_packed<0, IdxT, T><<<nt, kSortThreads, 0, s>>>(
               src, tgt, m, q, ai, bi, E, dshift, p.dbits, hist, (int)p.ntiles, scanned, ko, eo, so);
         else if (last)
-          scatter_packed<2, IdxT><<<nt, kSortThreads, 0, s>>>(
+          scatter_packed<2, IdxT, T><<<nt, kSortThreads, 0, s>>>(
               src, tgt, m, q, ai, bi, E, dshift, p.dbits, hist, (int)p.ntiles, scanned, ko, eo, so);
         else
-          scatter_packed<1, IdxT><<<nt, kSortThreads, 0, s>>>(
+          scatter_packed<1, IdxT, T><<<nt, kSortThreads, 0, s>>>(
               src, tgt, m, q, ai, bi, E, dshift, p.dbits, hist, (int)p.ntiles, scanned, ko, eo, so);
       } else if (first) {
-        scatter<true, IdxT><<<nt, kSortThreads, 0, s>>>(src, tgt, m, ki, ei, si, E, shift, p.dbits,
+        scatter<true, IdxT, T><<<nt, kSortThreads, 0, s>>>(src, tgt, m, ki, ei, si, E, shift, p.dbits,
                                                         hist, (int)p.ntiles, scanned, ko, eo, so);
       } else {
-        scatter<false, IdxT><<<nt, kSortThreads, 0, s>>>(src, tgt, m, ki, ei, si, E, shift,
+        scatter<false, IdxT, T><<<nt, kSortThreads, 0, s>>>(src, tgt, m, ki, ei, si, E, shift,
                                                          p.dbits, hist, (int)p.ntiles, scanned, ko,
                                                          eo, so);
       }
@@ -1088,7 +1148,7 @@ int sort_edges(Graph& g, const IdxT* src, const IdxT* tgt, char* scratch, const 
   return TFG_OK;
 }
 
-int build_part_plan(Graph& g, char* scratch, const ScratchLayout& L, hipStream_t s) {
+int build_part_plan(Graph& g, char* scratch, const ScratchLayout& L, int* host, hipStream_t s) {
   int* row_items = reinterpret_cast<int*>(scratch + L.row_items);
   int* seg_items = reinterpret_cast<int*>(scratch + L.seg_items);
   int* sums = reinterpret_cast<int*>(scratch + L.sums);
@@ -1103,10 +1163,8 @@ int build_part_plan(Graph& g, char* scratch, const ScratchLayout& L, hipStream_t
   rc = exclusive_scan(seg_items, seg_items, NP + 1, sums, s);
   if (rc) return rc;
   part_fill<<<nb, kBlock, 0, s>>>(g.segptr, g.N, g.parts, g.chunk, row_items, seg_items, g.pexec,
-                                  g.prows);
+                                  g.prows, g.counters, host);
   TFG_LAUNCHED("part_fill");
-  // the number of items, read back with the other counters
-  TFG_HIP(hipMemcpyAsync(g.counters + 4, seg_items + NP, sizeof(int), hipMemcpyDeviceToDevice, s));
   return TFG_OK;
 }
 
@@ -1143,6 +1201,24 @@ int* readback_buffer() {
                : nullptr;
   }();
   return p;
+}
+
+// Device ints to pinned host memory by one small kernel (a copy each costs the
+// host and the stream several microseconds).
+struct ReadInts {
+  const int* from[8];
+};
+namespace {
+__global__ void read_ints(ReadInts r, int n, int* __restrict__ host) {
+  if ((int)threadIdx.x < n) host[threadIdx.x] = *r.from[threadIdx.x];
+}
+}  // namespace
+int launch_read_ints(int n, const int* const* from, int* pinned, hipStream_t s) {
+  ReadInts r{};
+  for (int i = 0; i < n; ++i) r.from[i] = from[i];
+  read_ints<<<1, 64, 0, s>>>(r, n, pinned);
+  TFG_LAUNCHED("counter readback");
+  return TFG_OK;
 }
 
 int default_chunk() {
@@ -1212,37 +1288,44 @@ int build_graph(Graph& g, const void* src, const void* tgt, int index_type, void
   const ScratchLayout L = scratch_layout(g.E, g.N, g.parts);
   if (scratch_bytes < L.total) return fail(TFG_ERR_WORKSPACE, "graph scratch buffer too small");
   char* sc = static_cast<char*>(scratch);
-  fill_int<<<1, 64, 0, s>>>(g.counters, 8, 0);
+  const SortPlan p = sort_plan(g.E, g.N, g.parts);
   int rc;
-  if (index_type == TFG_I64)
-    rc = sort_edges<int64_t>(g, static_cast<const int64_t*>(src), static_cast<const int64_t*>(tgt),
-                             sc, L, s);
-  else
-    rc = sort_edges<int32_t>(g, static_cast<const int32_t*>(src), static_cast<const int32_t*>(tgt),
-                             sc, L, s);
+#define TFG_SORT(I, T)                                                                          \
+  sort_edges<I, T>(g, p, static_cast<const I*>(src), static_cast<const I*>(tgt), sc, L, s)
+#define TFG_SORT_T(I) \
+  (p.threads == 256 ? TFG_SORT(I, 256) : p.threads == 512 ? TFG_SORT(I, 512) : TFG_SORT(I, 1024))
+  if (index_type == TFG_I64) rc = TFG_SORT_T(int64_t);
+  else rc = TFG_SORT_T(int32_t);
+#undef TFG_SORT_T
+#undef TFG_SORT
   if (rc) return rc;
+  int* pin = readback_buffer();
+  const int* bad = reinterpret_cast<const int*>(sc + L.bad);
+  const int ntiles = (int)p.ntiles;
   if (g.N > 0) {
     const int nb = (int)((g.N + kWlThreads - 1) / kWlThreads);
     int* wl = reinterpret_cast<int*>(sc + L.wl_sums);
     if (g.N <= kWlSingle) {
-      worklist_single<<<1, kWlThreads, 0, s>>>(g.rowptr, g.N, g.chunk, g.counters, g.heavy,
-                                               g.split, g.short_rows, g.long_rows);
+      worklist_single<<<1, kWlThreads, 0, s>>>(g.rowptr, g.N, g.chunk, bad, ntiles, g.counters, pin,
+                                               g.heavy, g.split, g.short_rows, g.long_rows);
     } else {
       worklist_count<<<nb, kWlThreads, 0, s>>>(g.rowptr, g.N, g.chunk, wl, nb);
-      worklist_offsets<<<1, 1024, 0, s>>>(wl, nb, g.counters);
+      worklist_offsets<<<1, 1024, 0, s>>>(wl, nb, bad, ntiles, g.counters, pin);
       worklist_fill<<<nb, kWlThreads, 0, s>>>(g.rowptr, g.N, g.chunk, wl, nb, g.heavy, g.split,
                                               g.short_rows, g.long_rows);
     }
     TFG_LAUNCHED("work lists");
     if (g.parts > 1) {
-      rc = build_part_plan(g, sc, L, s);
+      rc = build_part_plan(g, sc, L, pin, s);
       if (rc) return rc;
     }
+  } else {
+    worklist_none<<<1, kWlThreads, 0, s>>>(bad, ntiles, g.counters, pin);
+    TFG_LAUNCHED("work lists");
   }
   int stack_host[8];
-  int* pin = readback_buffer();
   int* host = pin ? pin : stack_host;
-  TFG_HIP(hipMemcpyAsync(host, g.counters, sizeof(int) * 8, hipMemcpyDeviceToHost, s));
+  if (!pin) TFG_HIP(hipMemcpyAsync(host, g.counters, sizeof(int) * 8, hipMemcpyDeviceToHost, s));
   TFG_HIP(hipStreamSynchronize(s));
   if (host[3] & kErrIndex) return fail(TFG_ERR_INDEX_RANGE, "edge_index holds an id outside [0, N)");
   g.n_heavy = host[0];
