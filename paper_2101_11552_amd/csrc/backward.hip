@@ -378,88 +378,72 @@ void launch_reorder(const int* perm, int64_t E, int H, const float* in, float* o
 
 // Softmax gradient ds = alpha * (dalpha - sum over the row of alpha *
 // dalpha), per head, with the products summed in double (exact products of
-// floats), in the layouts of the softmax: short rows one lane per (row,
-// head), other light rows and chunks one wavefront each with their values in
-// registers (NST slot steps, the next power of two of the item's), split rows
-// of at most kGradSplitWaves chunks one block each with the chunk sums added
-// in chunk order in LDS. Chunks of longer split rows store their sums
-// (pdot), which softmax_grad_split adds in chunk order before writing.
-constexpr int kGradCap = 8;          // slot steps held in registers
-constexpr int kGradSplitWaves = 16;  // chunks per split row done by one block
+// floats), in the layouts of the softmax (softmax_stats.h): lane groups with
+// their values in registers, and the chunks of split rows in two launches, the
+// first of which stores their sums (pdot).
 
-__device__ __forceinline__ void grad_short_row(const WorkItem& it, const int* __restrict__ perm,
-                                               const float* __restrict__ alpha,
-                                               const float* __restrict__ da, int H, int hh,
-                                               int HP, float* __restrict__ ds) {
-  const int kb = it.kbeg, n = it.kend - it.kbeg;  // 0 <= n <= kShortRow
-  int nw = 0;  // the wavefront's longest row
-#pragma unroll
-  for (int j = 1; j <= kShortRow; ++j) nw = __any(n >= j) ? j : nw;
-  int e[kShortRow];
-#pragma unroll
-  for (int j = 0; j < kShortRow; ++j) e[j] = j < n ? edge_at(perm, kb + j) : 0;
-  for (int h = hh; h < H; h += HP) {
-    float a[kShortRow], g[kShortRow];
-#pragma unroll
-    for (int j = 0; j < kShortRow; ++j) {
-      a[j] = j < n ? alpha[(int64_t)e[j] * H + h] : 0.0f;
-      g[j] = j < n ? da[(int64_t)e[j] * H + h] : 0.0f;
-    }
-    double dot = 0.0;
-#pragma unroll
-    for (int j = 0; j < kShortRow; ++j)
-      if (j < nw) dot += (double)a[j] * (double)g[j];
-#pragma unroll
-    for (int j = 0; j < kShortRow; ++j)
-      if (j < n) ds[(int64_t)e[j] * H + h] = (float)((double)a[j] * ((double)g[j] - dot));
-  }
-}
-
-// alpha and dalpha of head h for the registers' ids (0 where there is none)
-template <int NST>
+// alpha and dalpha of the heads h for the registers' ids (0 where there is none)
+template <int NST, int K>
 __device__ __forceinline__ void grad_load(const float* __restrict__ alpha,
                                           const float* __restrict__ da, int H, int h, bool act,
-                                          const int (&e)[NST], float (&a)[NST],
-                                          float (&g)[NST]) {
+                                          const int (&e)[NST], float (&a)[NST][K],
+                                          float (&g)[NST][K]) {
 #pragma unroll
   for (int u = 0; u < NST; ++u) {
     const bool ok = act && e[u] >= 0;
-    a[u] = ok ? alpha[(int64_t)e[u] * H + h] : 0.0f;
-    g[u] = ok ? da[(int64_t)e[u] * H + h] : 0.0f;
+    if (ok) {
+      load_k<K>(alpha + ((int64_t)e[u] * H + h) * K, a[u]);
+      load_k<K>(da + ((int64_t)e[u] * H + h) * K, g[u]);
+    }
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      a[u][i] = ok ? a[u][i] : 0.0f;
+      g[u][i] = ok ? g[u][i] : 0.0f;
+    }
   }
 }
 
-template <int NST>
-__device__ __forceinline__ double grad_dot(const float (&a)[NST], const float (&g)[NST], int HP) {
+template <int NST, int K>
+__device__ __forceinline__ double grad_dot(const float (&a)[NST][K], const float (&g)[NST][K],
+                                           int i, int HP, int lanes) {
   double dot = 0.0;
 #pragma unroll
-  for (int u = 0; u < NST; ++u) dot += (double)a[u] * (double)g[u];
-  return slots_sum(dot, HP);
+  for (int u = 0; u < NST; ++u) dot += (double)a[u][i] * (double)g[u][i];
+  return slots_sum(dot, HP, lanes);
 }
 
-template <int NST>
-__device__ __forceinline__ void grad_write(const float (&a)[NST], const float (&g)[NST],
-                                           const int (&e)[NST], double dot, int H, int h,
-                                           bool act, float* __restrict__ ds) {
+template <int NST, int K>
+__device__ __forceinline__ void grad_write(const float (&a)[NST][K], const float (&g)[NST][K],
+                                           const int (&e)[NST], const double (&dot)[K], int H,
+                                           int h, bool act, float* __restrict__ ds) {
 #pragma unroll
   for (int u = 0; u < NST; ++u)
-    if (act && e[u] >= 0) ds[(int64_t)e[u] * H + h] = (float)((double)a[u] * ((double)g[u] - dot));
+    if (act && e[u] >= 0) {
+      float v[K];
+#pragma unroll
+      for (int i = 0; i < K; ++i) v[i] = (float)((double)a[u][i] * ((double)g[u][i] - dot[i]));
+      store_k<K>(ds + ((int64_t)e[u] * H + h) * K, v);
+    }
 }
 
 // A whole item's sum over [kb, ke) for head h, loading the values (the items
-// longer than kGradCap slot steps), and its ds from a second sweep.
+// longer than group_steps() slot steps), and its ds from a second sweep.
+constexpr int kGradSweep = 4;  // values in flight
 __device__ __forceinline__ double grad_sweep_dot(const int* __restrict__ perm,
                                                  const float* __restrict__ alpha,
                                                  const float* __restrict__ da, int H, int h,
                                                  bool act, int kb, int ke, int slot, int SL,
                                                  int HP) {
   double dot = 0.0;
-  for (int k = kb + slot; k < ke; k += SL)
-    if (act) {
-      const int64_t i = (int64_t)edge_at(perm, k) * H + h;
-      dot += (double)alpha[i] * (double)da[i];
-    }
-  return slots_sum(dot, HP);
+  for (int k = kb + slot; k < ke; k += kGradSweep * SL) {
+    int e[kGradSweep];
+    float a[kGradSweep][1], g[kGradSweep][1];
+    load_ids<kGradSweep>(perm, k, ke, 0, SL, e);
+    grad_load<kGradSweep, 1>(alpha, da, H, h, act, e, a, g);
+#pragma unroll
+    for (int u = 0; u < kGradSweep; ++u) dot += (double)a[u][0] * (double)g[u][0];
+  }
+  return slots_sum(dot, HP, kWave);
 }
 
 __device__ __forceinline__ void grad_sweep_write(const int* __restrict__ perm,
@@ -467,176 +451,160 @@ __device__ __forceinline__ void grad_sweep_write(const int* __restrict__ perm,
                                                  const float* __restrict__ da, int H, int h,
                                                  bool act, int kb, int ke, int slot, int SL,
                                                  double dot, float* __restrict__ ds) {
-  for (int k = kb + slot; k < ke; k += SL)
-    if (act) {
-      const int64_t i = (int64_t)edge_at(perm, k) * H + h;
-      ds[i] = (float)((double)alpha[i] * ((double)da[i] - dot));
-    }
+  const double d[1] = {dot};
+  for (int k = kb + slot; k < ke; k += kGradSweep * SL) {
+    int e[kGradSweep];
+    float a[kGradSweep][1], g[kGradSweep][1];
+    load_ids<kGradSweep>(perm, k, ke, 0, SL, e);
+    grad_load<kGradSweep, 1>(alpha, da, H, h, act, e, a, g);
+    grad_write<kGradSweep, 1>(a, g, e, d, H, h, act, ds);
+  }
 }
 
-template <int NST>
+template <int NST, int K>
 __device__ __forceinline__ void grad_item_regs(const int* __restrict__ perm,
                                                const float* __restrict__ alpha,
                                                const float* __restrict__ da, int H, int HP,
-                                               int kb, int ke, int slot, int hh, int pslot,
-                                               float* __restrict__ ds,
+                                               const GroupItem& it, float* __restrict__ ds,
                                                double* __restrict__ pdot) {
-  const int SL = kWave / HP;
+  const int SL = it.lanes / HP;
+  const int slot = (lane_id() & (it.lanes - 1)) / HP, hh = lane_id() & (HP - 1);
   int e[NST];
-  load_ids<NST>(perm, kb, ke, slot, SL, e);
+  load_ids<NST>(perm, it.kb, it.ke, slot, SL, e);
   for (int hb = 0; hb < H; hb += HP) {
     const int h = hb + hh;
     const bool act = h < H;
-    float a[NST], g[NST];
-    grad_load<NST>(alpha, da, H, h, act, e, a, g);
-    const double dot = grad_dot<NST>(a, g, HP);
-    if (pslot >= 0) {
-      if (slot == 0 && act) pdot[(int64_t)pslot * H + h] = dot;
-      continue;
+    float a[NST][K], g[NST][K];
+    double dot[K];
+    grad_load<NST, K>(alpha, da, H, h, act, e, a, g);
+#pragma unroll
+    for (int i = 0; i < K; ++i) dot[i] = grad_dot<NST, K>(a, g, i, HP, it.lanes);
+    if (it.pslot < 0) {
+      grad_write<NST, K>(a, g, e, dot, H, h, act, ds);
+    } else if (slot == 0 && act) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) pdot[((int64_t)it.pslot * H + h) * K + i] = dot[i];
     }
-    grad_write<NST>(a, g, e, dot, H, h, act, ds);
   }
 }
 
-// Wavefronts [0, short_waves) take 64 / HP short rows each; the next n_long
-// one light row of more than kShortRow edges each; the rest one chunk of a
-// split row of more than kGradSplitWaves chunks (the others are left to
-// softmax_grad_split).
+// 1.35M edges and 8 heads, rows of 8 on average: 62 us with one wavefront per row of
+// over 8 edges and one head per lane, now 31.
+template <int K>
 __global__ __launch_bounds__(kItemBlock) void softmax_grad_items(
-    const WorkItem* __restrict__ short_rows, int n_short, int short_waves,
-    const WorkItem* __restrict__ long_rows, int n_long, const WorkItem* __restrict__ heavy,
-    int n_heavy, const int* __restrict__ rowptr, int chunk, const int* __restrict__ perm,
-    const float* __restrict__ alpha, const float* __restrict__ da, int H, int HP,
-    float* __restrict__ ds, double* __restrict__ pdot) {
-  const int lane = threadIdx.x & (kWave - 1);
-  int wid = uniform(blockIdx.x * (kItemBlock / kWave) + threadIdx.x / kWave);
-  if (wid < short_waves) {
-    const int i = wid * (kWave / HP) + lane / HP;
-    if (i < n_short) grad_short_row(short_rows[i], perm, alpha, da, H, lane % HP, HP, ds);
-    return;
-  }
-  wid -= short_waves;
-  if (wid >= n_long + n_heavy) return;
-  const int SL = kWave / HP;
-  const int slot = lane / HP, hh = lane % HP;
-  int kb, ke, pslot = -1;
-  if (wid < n_long) {
-    kb = uniform(long_rows[wid].kbeg);
-    ke = uniform(long_rows[wid].kend);
-  } else {
-    const WorkItem* it = heavy + (wid - n_long);
-    const int row = uniform(it->row);
-    const int deg = uniform(rowptr[row + 1]) - uniform(rowptr[row]);
-    if ((deg + chunk - 1) / chunk <= kGradSplitWaves) return;
-    kb = uniform(it->kbeg);
-    ke = uniform(it->kend);
-    pslot = uniform(it->slot);
-  }
-  const int nst = (ke - kb + SL - 1) / SL;
+    RowGroups L, const int* __restrict__ perm, const float* __restrict__ alpha,
+    const float* __restrict__ da, int H, int HP, float* __restrict__ ds,
+    double* __restrict__ pdot) {
+  const GroupItem it = group_item(L, blockIdx.x);
+  const int SL = it.lanes / HP, nst = (it.longest + SL - 1) / SL;
   if (nst <= 1) {
-    grad_item_regs<1>(perm, alpha, da, H, HP, kb, ke, slot, hh, pslot, ds, pdot);
+    grad_item_regs<1, K>(perm, alpha, da, H, HP, it, ds, pdot);
   } else if (nst <= 2) {
-    grad_item_regs<2>(perm, alpha, da, H, HP, kb, ke, slot, hh, pslot, ds, pdot);
+    grad_item_regs<2, K>(perm, alpha, da, H, HP, it, ds, pdot);
   } else if (nst <= 4) {
-    grad_item_regs<4>(perm, alpha, da, H, HP, kb, ke, slot, hh, pslot, ds, pdot);
-  } else if (nst <= kGradCap) {
-    grad_item_regs<kGradCap>(perm, alpha, da, H, HP, kb, ke, slot, hh, pslot, ds, pdot);
-  } else {
-    for (int hb = 0; hb < H; hb += HP) {
+    grad_item_regs<4, K>(perm, alpha, da, H, HP, it, ds, pdot);
+  } else if (K == 1 && nst <= 8) {
+    grad_item_regs<K == 1 ? 8 : 1, K>(perm, alpha, da, H, HP, it, ds, pdot);
+  } else {  // groups of 64 lanes: one item; single heads
+    const int H1 = H * K, hp = min(HP * K, kWave), sl1 = kWave / hp;
+    const int slot = lane_id() / hp, hh = lane_id() & (hp - 1);
+    for (int hb = 0; hb < H1; hb += hp) {
       const int h = hb + hh;
-      const bool act = h < H;
-      const double dot = grad_sweep_dot(perm, alpha, da, H, h, act, kb, ke, slot, SL, HP);
-      if (pslot >= 0) {
-        if (slot == 0 && act) pdot[(int64_t)pslot * H + h] = dot;
-        continue;
-      }
-      grad_sweep_write(perm, alpha, da, H, h, act, kb, ke, slot, SL, dot, ds);
+      const bool act = h < H1;
+      const double dot = grad_sweep_dot(perm, alpha, da, H1, h, act, it.kb, it.ke, slot, sl1, hp);
+      if (it.pslot < 0)
+        grad_sweep_write(perm, alpha, da, H1, h, act, it.kb, it.ke, slot, sl1, dot, ds);
+      else if (slot == 0 && act)
+        pdot[(int64_t)it.pslot * H1 + h] = dot;
     }
   }
 }
 
-// Chunk w of a split row of at most kGradSplitWaves chunks (NST = 0: the
-// values are loaded again to write); every wavefront runs the same head
-// passes and barriers, with or without a chunk.
-template <int NST>
-__device__ __forceinline__ void grad_split_chunk(const int* __restrict__ perm,
+// A split row's sum for head h from its chunks' sums (p at the head), a share
+// per slot, four in flight, then over the slots.
+__device__ __forceinline__ double row_dot(const double* __restrict__ p, int nch, int H, bool act,
+                                          int slot, int SL, int HP) {
+  constexpr int U = 4;
+  double dot = 0.0;
+  if (act)
+    for (int c = slot; c < nch; c += U * SL) {
+      double q[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) q[u] = p[(int64_t)min(c + u * SL, nch - 1) * H];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c + u * SL < nch) dot += q[u];
+    }
+  return slots_sum(dot, HP, kWave);
+}
+
+// ds of the chunks of split rows, one wavefront per chunk (NST = 0: the values
+// loaded one by one). One block of 16 wavefronts per split row: 30 us for 1,400
+// chunks of 460 rows, now 8.
+template <int NST, int K>
+__device__ __forceinline__ void grad_chunk_write(const int* __restrict__ perm,
                                                  const float* __restrict__ alpha,
                                                  const float* __restrict__ da, int H, int HP,
-                                                 int kb, int ke, int nch, int w, int lane,
-                                                 double (&lsum)[kGradSplitWaves][kWave],
+                                                 const WorkItem& it, const ChunkRow& r,
+                                                 const double* __restrict__ pdot,
                                                  float* __restrict__ ds) {
   const int SL = kWave / HP;
-  const int slot = lane / HP, hh = lane % HP;
-  const bool has = kb < ke;
+  const int slot = lane_id() / HP, hh = lane_id() & (HP - 1);
   constexpr int R = NST > 0 ? NST : 1;
   int e[R];
-  if constexpr (NST > 0) load_ids<NST>(perm, kb, ke, slot, SL, e);
+  if constexpr (NST > 0) load_ids<NST>(perm, it.kbeg, it.kend, slot, SL, e);
   for (int hb = 0; hb < H; hb += HP) {
     const int h = hb + hh;
     const bool act = h < H;
-    float a[R], g[R];
-    double dot = 0.0;
-    if (has) {
-      if constexpr (NST > 0) {
-        grad_load<NST>(alpha, da, H, h, act, e, a, g);
-        dot = grad_dot<NST>(a, g, HP);
-      } else {
-        dot = grad_sweep_dot(perm, alpha, da, H, h, act, kb, ke, slot, SL, HP);
-      }
-    }
-    lsum[w][lane] = dot;
-    __syncthreads();
-    double tot = 0.0;
-    for (int c = 0; c < nch; ++c) tot += lsum[c][lane];
-    __syncthreads();  // the sums are read before the next head pass writes
-    if (!has) continue;
+    float a[R][K], g[R][K];
+    double dot[K];
+    if constexpr (NST > 0) grad_load<NST, K>(alpha, da, H, h, act, e, a, g);
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+      dot[i] = row_dot(pdot + ((int64_t)r.slot0 * H + h) * K + i, r.nch, H * K, act, slot, SL, HP);
     if constexpr (NST > 0)
-      grad_write<NST>(a, g, e, tot, H, h, act, ds);
+      grad_write<NST, K>(a, g, e, dot, H, h, act, ds);
     else
-      grad_sweep_write(perm, alpha, da, H, h, act, kb, ke, slot, SL, tot, ds);
+      grad_sweep_write(perm, alpha, da, H, h, act, it.kbeg, it.kend, slot, SL, dot[0], ds);
   }
 }
 
-// One block per split row (kGradSplitWaves wavefronts): grad_split_chunk for
-// a row of at most kGradSplitWaves chunks; for a longer one the chunk sums
-// from softmax_grad_items, added in chunk order, and wavefront w writes
-// chunks w, w + kGradSplitWaves, ...
-__global__ __launch_bounds__(kGradSplitWaves * kWave) void softmax_grad_split(
+template <int K>
+__global__ __launch_bounds__(kItemBlock) void softmax_grad_chunks(
+    const WorkItem* __restrict__ heavy, const int* __restrict__ rowptr, int chunk,
+    const int* __restrict__ perm, const float* __restrict__ alpha, const float* __restrict__ da,
+    int H, int HP, const double* __restrict__ pdot, float* __restrict__ ds) {
+  const WorkItem it = heavy[blockIdx.x];
+  const ChunkRow r = chunk_row(it, rowptr, chunk);
+  if (r.nch > kGiantChunks) return;
+  const int SL = kWave / HP, cst = (chunk + SL - 1) / SL;
+  if (cst <= 2) {
+    grad_chunk_write<2, K>(perm, alpha, da, H, HP, it, r, pdot, ds);
+  } else if (cst <= 4) {
+    grad_chunk_write<4, K>(perm, alpha, da, H, HP, it, r, pdot, ds);
+  } else if (K == 1 && cst <= 8) {
+    grad_chunk_write<K == 1 ? 8 : 2, K>(perm, alpha, da, H, HP, it, r, pdot, ds);
+  } else {  // single heads
+    grad_chunk_write<0, 1>(perm, alpha, da, H * K, min(HP * K, kWave), it, r, pdot, ds);
+  }
+}
+
+// Rows of more than kGiantChunks chunks: the sums added once per wavefront of
+// the row's block, and wavefront w writes chunks w, w + kGiantWaves, ...
+__global__ __launch_bounds__(kGiantWaves * kWave) void softmax_grad_giant(
     const SplitRow* __restrict__ split, const int* __restrict__ rowptr, int chunk,
     const int* __restrict__ perm, const float* __restrict__ alpha, const float* __restrict__ da,
     int H, int HP, const double* __restrict__ pdot, float* __restrict__ ds) {
-  __shared__ double lsum[kGradSplitWaves][kWave];
-  const SplitRow* sr = split + blockIdx.x;
-  const int row = uniform(sr->row), nch = uniform(sr->nchunks), s0 = uniform(sr->slot0);
-  const int rb = uniform(rowptr[row]), re = uniform(rowptr[row + 1]);
+  const SplitRow sr = split[blockIdx.x];
+  if (sr.nchunks <= kGiantChunks) return;
+  const int rb = uniform(rowptr[sr.row]), re = uniform(rowptr[sr.row + 1]);
   const int w = uniform((int)threadIdx.x / kWave);
-  const int lane = threadIdx.x & (kWave - 1);
-  const int SL = kWave / HP;
-  if (nch <= kGradSplitWaves) {
-    const int kb = rb + w * chunk, ke = min(re, kb + chunk);  // kb >= ke: no chunk
-    const int cst = (chunk + SL - 1) / SL;  // slot steps of a whole chunk
-    if (cst <= 2)
-      grad_split_chunk<2>(perm, alpha, da, H, HP, kb, ke, nch, w, lane, lsum, ds);
-    else if (cst <= 4)
-      grad_split_chunk<4>(perm, alpha, da, H, HP, kb, ke, nch, w, lane, lsum, ds);
-    else if (cst <= kGradCap)
-      grad_split_chunk<kGradCap>(perm, alpha, da, H, HP, kb, ke, nch, w, lane, lsum, ds);
-    else if (cst <= 2 * kGradCap)
-      grad_split_chunk<2 * kGradCap>(perm, alpha, da, H, HP, kb, ke, nch, w, lane, lsum, ds);
-    else
-      grad_split_chunk<0>(perm, alpha, da, H, HP, kb, ke, nch, w, lane, lsum, ds);
-    return;
-  }
-  const int slot = lane / HP, hh = lane % HP;
+  const int SL = kWave / HP, slot = lane_id() / HP, hh = lane_id() & (HP - 1);
   for (int hb = 0; hb < H; hb += HP) {
     const int h = hb + hh;
     const bool act = h < H;
-    // the chunks' sums, a share per slot, then over the slots
-    double dot = 0.0;
-    if (act)
-      for (int c = slot; c < nch; c += SL) dot += pdot[(int64_t)(s0 + c) * H + h];
-    dot = slots_sum(dot, HP);
-    for (int c = w; c < nch; c += kGradSplitWaves) {
+    const double dot = row_dot(pdot + (int64_t)sr.slot0 * H + h, sr.nchunks, H, act, slot, SL, HP);
+    for (int c = w; c < sr.nchunks; c += kGiantWaves) {
       const int kb = rb + c * chunk, ke = min(re, kb + chunk);
       grad_sweep_write(perm, alpha, da, H, h, act, kb, ke, slot, SL, dot, ds);
     }
@@ -840,25 +808,36 @@ int launch_segment_softmax_backward(const Graph& g, const float* alpha, const fl
                                     int H, float* ds, void* ws, hipStream_t s, bool graph_order) {
   if (g.N == 0 || g.E == 0 || H == 0) return TFG_OK;
   const int* perm = graph_order ? nullptr : g.perm;  // alpha, dalpha, ds in the graph order
-  int hp = 1;
-  while (hp * 2 <= std::min(H, kWave)) hp *= 2;
+  const int hp = heads_per_pass(H);
   // the double part of the per-chunk statistics (row_stats_bytes layout)
   double* pdot = reinterpret_cast<double*>(
       static_cast<char*>(ws) +
       align_up(sizeof(float) * (size_t)std::max<int64_t>((int64_t)g.n_heavy * H, 1), 256));
-  const int64_t short_waves = (g.n_short + kWave / hp - 1) / (kWave / hp);
-  const int64_t waves = short_waves + g.n_long + g.n_heavy;
-  if (waves > INT32_MAX) return fail(TFG_ERR_TOO_LARGE, "softmax gradient: too many work items");
-  if (waves > 0) {
-    softmax_grad_items<<<(unsigned)((waves + (kItemBlock / kWave) - 1) / (kItemBlock / kWave)), kItemBlock, 0, s>>>(
-        g.short_rows, g.n_short, (int)short_waves, g.long_rows, g.n_long, g.heavy, g.n_heavy,
-        g.rowptr, g.chunk, perm, alpha, dalpha, H, hp, ds, pdot);
-    TFG_LAUNCHED("softmax_grad_items");
-  }
-  if (g.n_split > 0) {
-    softmax_grad_split<<<(unsigned)g.n_split, kGradSplitWaves * kWave, 0, s>>>(
+  const auto run = [&](auto k_) {
+    constexpr int K = decltype(k_)::value;
+    const int hk = H / K, hpk = heads_per_pass(hk);
+    RowGroups L;
+    const int64_t waves = row_groups<K>(g, hpk, L);
+    if (waves > INT32_MAX) return fail(TFG_ERR_TOO_LARGE, "softmax gradient: too many work items");
+    if (waves > 0) {
+      softmax_grad_items<K><<<(unsigned)waves, kItemBlock, 0, s>>>(L, perm, alpha, dalpha, hk, hpk,
+                                                                   ds, pdot);
+      TFG_LAUNCHED("softmax_grad_items");
+    }
+    if (g.n_heavy > 0) {
+      softmax_grad_chunks<K><<<(unsigned)g.n_heavy, kItemBlock, 0, s>>>(
+          g.heavy, g.rowptr, g.chunk, perm, alpha, dalpha, hk, hpk, pdot, ds);
+      TFG_LAUNCHED("softmax_grad_chunks");
+    }
+    return (int)TFG_OK;
+  };
+  const int rc = H % 4 == 0 ? run(std::integral_constant<int, 4>{})
+                            : run(std::integral_constant<int, 1>{});
+  if (rc) return rc;
+  if (g.n_heavy > kGiantChunks) {
+    softmax_grad_giant<<<(unsigned)g.n_split, kGiantWaves * kWave, 0, s>>>(
         g.split, g.rowptr, g.chunk, perm, alpha, dalpha, H, hp, pdot, ds);
-    TFG_LAUNCHED("softmax_grad_split");
+    TFG_LAUNCHED("softmax_grad_giant");
   }
   return TFG_OK;
 }

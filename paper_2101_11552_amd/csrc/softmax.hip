@@ -5,6 +5,8 @@
 //               shifted exponentials (the reduce, in one online sweep) and the
 //               division (the last map), one wavefront per work item of the
 //               graph's row plan.
+#include <type_traits>
+
 #include "softmax_stats.h"
 
 namespace tfg {
@@ -166,79 +168,32 @@ __global__ __launch_bounds__(kBlock) void edge_scores_graph(const int* __restric
   else o[0] = z[0];
 }
 
-// Short rows (at most kShortRow edges), 64 / HP per wavefront: lane (r, hh)
-// takes row short_rows[i] and heads hh, hh + HP, ...; the row's scores are
-// loaded at once and kept in registers: maximum, then the sum of exp(s - m)
-// in graph order (at most kShortRow terms of at most 1, one of them 1: float
-// keeps it within a few units of 2^-24), then alpha = exp(s - m) * (1 / sum).
-// No cross-lane traffic.
-__device__ __forceinline__ void softmax_short_row(const WorkItem& it,
-                                                  const int* __restrict__ perm,
-                                                  const float* __restrict__ s, int H, int hh,
-                                                  int HP, float* __restrict__ out,
-                                                  float* __restrict__ out_csr) {
-  const int kb = it.kbeg, n = it.kend - it.kbeg;  // 0 <= n <= kShortRow
-  // the wavefront's longest row: steps past it are skipped by all lanes
-  int nw = 0;
+// Rows and the chunks of long rows go in lane groups (softmax_stats.h).
+// Items of at most group_steps() slot steps are swept once, over NST steps (a power
+// of two, a template argument chosen per wavefront): their edge ids and scores
+// are loaded together and stay in registers, the maximum comes from the
+// registers and a butterfly over the slots, then each score is replaced by
+// exp(s - m) and summed (butterfly again), and alpha is written from the
+// registers. Longer items (more than 16 heads) keep a running pair instead
+// (stat_add: maximum and rescaled sum in one sweep of loads) and load the scores
+// again to write alpha.
+constexpr int kSmSteps = 4;  // slot steps per round of loads (the running sweep)
+
+// Scores of the heads h for the ids (-inf where there is no edge or no head).
+template <int NST, int K>
+__device__ __forceinline__ void load_scores(const float* __restrict__ s, int H, int h, bool act,
+                                            const int (&e)[NST], float (&v)[NST][K]) {
 #pragma unroll
-  for (int j = 1; j <= kShortRow; ++j) nw = __any(n >= j) ? j : nw;
-  int e[kShortRow];
+  for (int u = 0; u < NST; ++u) {
+    const bool ok = act && e[u] >= 0;
+    if (ok) load_k<K>(s + ((int64_t)e[u] * H + h) * K, v[u]);
 #pragma unroll
-  for (int j = 0; j < kShortRow; ++j) e[j] = j < n ? edge_at(perm, kb + j) : 0;
-  for (int h = hh; h < H; h += HP) {
-    float v[kShortRow];
-    float m = -__builtin_huge_valf();
-#pragma unroll
-    for (int j = 0; j < kShortRow; ++j) {
-      v[j] = j < n ? s[(int64_t)e[j] * H + h] : 0.0f;
-      if (j < n) m = v[j] > m ? v[j] : m;
-    }
-    float d = 0.0f;
-#pragma unroll
-    for (int j = 0; j < kShortRow; ++j)
-      if (j < nw) {
-        v[j] = expf(v[j] - m);
-        if (j < n) d += v[j];
-      }
-    const float r = 1.0f / d;
-#pragma unroll
-    for (int j = 0; j < kShortRow; ++j)
-      if (j < n) {
-        const float a = v[j] * r;
-        out[(int64_t)e[j] * H + h] = a;
-        if (out_csr) out_csr[(int64_t)(kb + j) * H + h] = a;
-      }
+    for (int i = 0; i < K; ++i) v[u][i] = ok ? v[u][i] : -__builtin_huge_valf();
   }
 }
 
-// The other rows go one work item (a whole row, or a chunk of a long row)
-// per wavefront. Lanes are (slot, head) pairs: HP heads (a power of two) per
-// pass and SL = 64 / HP edge slots; slot step u of an item starting at kb is
-// position kb + slot + u * SL.
-//
-// Items of at most kSmCap slot steps are swept once, over NST steps (the
-// next power of two, a template argument chosen per item, so that the
-// wavefront runs no step that holds none of its edges): their edge ids and
-// scores are loaded together and stay in registers, the maximum comes from
-// the registers and a butterfly over the slots, then each score is replaced
-// by exp(s - m) and summed in double (butterfly again), and alpha is written
-// from the registers. Longer items keep a running pair instead (stat_add:
-// maximum and rescaled sum in one sweep of loads) and load the scores again
-// to write alpha.
-constexpr int kSmCap = 8;    // slot steps held in registers
-constexpr int kSmSteps = 4;  // slot steps per round of loads (the running sweep)
-
-// Scores of head h for the ids (-inf where there is no edge or no head).
-template <int NST>
-__device__ __forceinline__ void load_scores(const float* __restrict__ s, int H, int h, bool act,
-                                            const int (&e)[NST], float (&v)[NST]) {
-#pragma unroll
-  for (int u = 0; u < NST; ++u)
-    v[u] = (act && e[u] >= 0) ? s[(int64_t)e[u] * H + h] : -__builtin_huge_valf();
-}
-
-__device__ __forceinline__ float slots_max(float m, int HP) {
-  for (int off = HP; off < kWave; off <<= 1) {
+__device__ __forceinline__ float slots_max(float m, int HP, int lanes) {
+  for (int off = HP; off < lanes; off <<= 1) {
     const float o = __shfl_xor(m, off);
     m = o > m ? o : m;
   }
@@ -253,42 +208,50 @@ __device__ __forceinline__ void slots_merge(float& m, double& d, int HP) {
   }
 }
 
-// Maximum of the registers, over all slots of the head.
-template <int NST>
-__device__ __forceinline__ float regs_max(const float (&v)[NST], int HP) {
+// Maximum of the registers of head i, over all slots of the head.
+template <int NST, int K>
+__device__ __forceinline__ float regs_max(const float (&v)[NST][K], int i, int HP, int lanes) {
   float m = -__builtin_huge_valf();
 #pragma unroll
-  for (int u = 0; u < NST; ++u) m = v[u] > m ? v[u] : m;
-  return slots_max(m, HP);
+  for (int u = 0; u < NST; ++u) m = v[u][i] > m ? v[u][i] : m;
+  return slots_max(m, HP, lanes);
 }
 
-// Sum of exp(v - m) over all slots of the head (a missing edge, v = -inf,
-// adds exp(-inf) = 0): at most kSmCap terms per lane in float, then the
-// lanes' sums in double; with KEEP the registers become exp(v - m).
-template <int NST, bool KEEP>
-__device__ __forceinline__ double regs_exp_sum(float (&v)[NST], float m, int HP) {
-  float d = 0.0f;
+// The registers' exp(v - m) (a missing edge, v = -inf, gives 0; with no maximum
+// yet every score is -inf or NaN, and stays 0 or NaN), and their sum over all slots
+// of the head: 8 terms at a time in float, then in double.
+__device__ __forceinline__ float exp_base(float m) { return m == -__builtin_huge_valf() ? 0.0f : m; }
+template <int NST, int K>
+__device__ __forceinline__ double regs_exp_sum(float (&v)[NST][K], int i, float m, int HP,
+                                               int lanes) {
+  const float base = exp_base(m);
+  double sum = 0.0;
 #pragma unroll
-  for (int u = 0; u < NST; ++u) {
-    const float x = expf(v[u] - m);
-    if (KEEP) v[u] = x;
-    d += x;
+  for (int u0 = 0; u0 < NST; u0 += 8) {
+    float d = 0.0f;
+#pragma unroll
+    for (int u = u0; u < NST && u < u0 + 8; ++u) {
+      v[u][i] = expf(v[u][i] - base);
+      d += v[u][i];
+    }
+    sum += (double)d;
   }
-  return slots_sum((double)d, HP);
+  return slots_sum(sum, HP, lanes);
 }
 
 // alpha = x * r for the registers' edges (x = exp(s - m), r = 1 / sum).
-template <int NST>
-__device__ __forceinline__ void regs_write(const float (&x)[NST], const int (&e)[NST], float r,
-                                           int kb, int slot, int SL, int H, int h, bool act,
-                                           float* __restrict__ out,
+template <int NST, int K>
+__device__ __forceinline__ void regs_write(float (&x)[NST][K], const int (&e)[NST],
+                                           const float (&r)[K], int kb, int slot, int SL, int H,
+                                           int h, bool act, float* __restrict__ out,
                                            float* __restrict__ out_csr) {
 #pragma unroll
   for (int u = 0; u < NST; ++u)
     if (act && e[u] >= 0) {
-      const float a = x[u] * r;
-      out[(int64_t)e[u] * H + h] = a;
-      if (out_csr) out_csr[(int64_t)(kb + slot + u * SL) * H + h] = a;
+#pragma unroll
+      for (int i = 0; i < K; ++i) x[u][i] *= r[i];
+      store_k<K>(out + ((int64_t)e[u] * H + h) * K, x[u]);
+      if (out_csr) store_k<K>(out_csr + ((int64_t)(kb + slot + u * SL) * H + h) * K, x[u]);
     }
 }
 
@@ -345,205 +308,195 @@ __device__ __forceinline__ void sweep_write(const int* __restrict__ perm,
   }
 }
 
-// One item from the registers: a whole row (pslot < 0) writes alpha, a chunk
-// of a split row its pair.
-template <int NST>
+// One item per group from the registers: a whole row (pslot < 0) writes alpha,
+// a chunk of a split row its pair.
+template <int NST, int K>
 __device__ __forceinline__ void item_regs(const int* __restrict__ perm,
-                                          const float* __restrict__ s, int H, int HP, int kb,
-                                          int ke, int slot, int hh, int pslot,
-                                          float* __restrict__ out, float* __restrict__ out_csr,
-                                          float* __restrict__ pm, double* __restrict__ pd) {
-  const int SL = kWave / HP;
+                                          const float* __restrict__ s, int H, int HP,
+                                          const GroupItem& it, float* __restrict__ out,
+                                          float* __restrict__ out_csr, float* __restrict__ pm,
+                                          double* __restrict__ pd) {
+  const int SL = it.lanes / HP;
+  const int slot = (lane_id() & (it.lanes - 1)) / HP, hh = lane_id() & (HP - 1);
   int e[NST];
-  load_ids<NST>(perm, kb, ke, slot, SL, e);
+  load_ids<NST>(perm, it.kb, it.ke, slot, SL, e);
   for (int hb = 0; hb < H; hb += HP) {
     const int h = hb + hh;
     const bool act = h < H;
-    float v[NST];
-    load_scores<NST>(s, H, h, act, e, v);
-    const float m = regs_max<NST>(v, HP);
-    const double d = regs_exp_sum<NST, true>(v, m, HP);
-    if (pslot >= 0) {
-      if (slot == 0 && act) {
-        pm[(int64_t)pslot * H + h] = m;
-        pd[(int64_t)pslot * H + h] = d;
-      }
-      continue;
+    float v[NST][K], m[K], r[K];
+    double d[K];
+    load_scores<NST, K>(s, H, h, act, e, v);
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      m[i] = regs_max<NST, K>(v, i, HP, it.lanes);
+      d[i] = regs_exp_sum<NST, K>(v, i, m[i], HP, it.lanes);
+      r[i] = (float)(1.0 / d[i]);
     }
-    regs_write<NST>(v, e, (float)(1.0 / d), kb, slot, SL, H, h, act, out, out_csr);
+    if (it.pslot < 0) {
+      regs_write<NST, K>(v, e, r, it.kb, slot, SL, H, h, act, out, out_csr);
+    } else if (slot == 0 && act) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        pm[((int64_t)it.pslot * H + h) * K + i] = m[i];
+        pd[((int64_t)it.pslot * H + h) * K + i] = d[i];
+      }
+    }
   }
 }
 
-// Split rows: a row of more than kSplitWaves chunks has its chunks' pairs
-// written here (pm, pd at the chunk's slot) and combined by softmax_split;
-// the chunks of the other split rows are left to softmax_split entirely.
-constexpr int kSplitWaves = 16;
-
-// Wavefronts [0, short_waves) take 64 / HP short rows each; the next n_long
-// one whole light row of more than kShortRow edges each, the rest one chunk
-// of a split row.
+// 1.35M edges and 8 heads, rows of 8 on average: 35 us with one wavefront per row of
+// over 8 edges and one head per lane, now 27.
+template <int K>
 __global__ __launch_bounds__(kItemBlock) void softmax_items(
-    const WorkItem* __restrict__ short_rows, int n_short, int short_waves,
-    const WorkItem* __restrict__ long_rows, int n_long, const WorkItem* __restrict__ heavy,
-    int n_heavy, const int* __restrict__ rowptr, int chunk, const int* __restrict__ perm,
-    const float* __restrict__ s, int H, int HP, float* __restrict__ out,
-    float* __restrict__ out_csr, float* __restrict__ pm, double* __restrict__ pd) {
-  const int lane = threadIdx.x & (kWave - 1);
-  int wid = uniform(blockIdx.x * (kItemBlock / kWave) + threadIdx.x / kWave);
-  if (wid < short_waves) {
-    const int i = wid * (kWave / HP) + lane / HP;
-    if (i < n_short) softmax_short_row(short_rows[i], perm, s, H, lane % HP, HP, out, out_csr);
-    return;
-  }
-  wid -= short_waves;
-  if (wid >= n_long + n_heavy) return;
-  const int SL = kWave / HP;
-  const int slot = lane / HP, hh = lane % HP;
-  int kb, ke, pslot = -1;
-  if (wid < n_long) {
-    kb = uniform(long_rows[wid].kbeg);
-    ke = uniform(long_rows[wid].kend);
-  } else {
-    const WorkItem* it = heavy + (wid - n_long);
-    const int row = uniform(it->row);
-    const int deg = uniform(rowptr[row + 1]) - uniform(rowptr[row]);
-    if ((deg + chunk - 1) / chunk <= kSplitWaves) return;
-    kb = uniform(it->kbeg);
-    ke = uniform(it->kend);
-    pslot = uniform(it->slot);
-  }
-  const int nst = (ke - kb + SL - 1) / SL;
+    RowGroups L, const int* __restrict__ perm, const float* __restrict__ s, int H, int HP,
+    float* __restrict__ out, float* __restrict__ out_csr, float* __restrict__ pm,
+    double* __restrict__ pd) {
+  const GroupItem it = group_item(L, blockIdx.x);
+  const int SL = it.lanes / HP, nst = (it.longest + SL - 1) / SL;
   if (nst <= 1) {
-    item_regs<1>(perm, s, H, HP, kb, ke, slot, hh, pslot, out, out_csr, pm, pd);
+    item_regs<1, K>(perm, s, H, HP, it, out, out_csr, pm, pd);
   } else if (nst <= 2) {
-    item_regs<2>(perm, s, H, HP, kb, ke, slot, hh, pslot, out, out_csr, pm, pd);
+    item_regs<2, K>(perm, s, H, HP, it, out, out_csr, pm, pd);
   } else if (nst <= 4) {
-    item_regs<4>(perm, s, H, HP, kb, ke, slot, hh, pslot, out, out_csr, pm, pd);
-  } else if (nst <= kSmCap) {
-    item_regs<kSmCap>(perm, s, H, HP, kb, ke, slot, hh, pslot, out, out_csr, pm, pd);
-  } else {
-    for (int hb = 0; hb < H; hb += HP) {
+    item_regs<4, K>(perm, s, H, HP, it, out, out_csr, pm, pd);
+  } else if (K == 1 && nst <= 8) {
+    item_regs<K == 1 ? 8 : 1, K>(perm, s, H, HP, it, out, out_csr, pm, pd);
+  } else {  // groups of 64 lanes: one item; single heads
+    const int H1 = H * K, hp = min(HP * K, kWave), sl1 = kWave / hp;
+    const int slot = lane_id() / hp, hh = lane_id() & (hp - 1);
+    for (int hb = 0; hb < H1; hb += hp) {
       const int h = hb + hh;
-      const bool act = h < H;
+      const bool act = h < H1;
       float m;
       double d;
-      sweep_stats(perm, s, H, h, act, kb, ke, slot, SL, HP, m, d);
-      if (pslot >= 0) {
-        if (slot == 0 && act) {
-          pm[(int64_t)pslot * H + h] = m;
-          pd[(int64_t)pslot * H + h] = d;
-        }
-        continue;
+      sweep_stats(perm, s, H1, h, act, it.kb, it.ke, slot, sl1, hp, m, d);
+      if (it.pslot < 0) {
+        sweep_write(perm, s, H1, h, act, it.kb, it.ke, slot, sl1, m, 1.0 / d, out, out_csr);
+      } else if (slot == 0 && act) {
+        pm[(int64_t)it.pslot * H1 + h] = m;
+        pd[(int64_t)it.pslot * H1 + h] = d;
       }
-      sweep_write(perm, s, H, h, act, kb, ke, slot, SL, m, 1.0 / d, out, out_csr);
     }
   }
 }
 
-// A split row of at most kSplitWaves chunks, by one block: wavefront w takes
-// chunk w, finds its pair (from the registers, or a running sweep), leaves it
-// in LDS, and after the barrier every wavefront combines the pairs in chunk
-// order and writes its chunk's alpha (from the registers when they hold the
-// chunk). Every wavefront runs the same head passes and barriers, with or
-// without a chunk.
-template <int NST>
-__device__ __forceinline__ void split_chunk(const int* __restrict__ perm,
-                                            const float* __restrict__ s, int H, int HP, int kb,
-                                            int ke, int nch, int w, int lane,
-                                            float (&lm)[kSplitWaves][kWave],
-                                            double (&ld)[kSplitWaves][kWave],
+// The pair of a split row for head h from its chunks' pairs, a share per slot,
+// then over the slots: the maximum, then the sums weighed to it, four pairs in
+// flight.
+__device__ __forceinline__ void row_pair(const float* __restrict__ pm,
+                                         const double* __restrict__ pd, int nch, int H, bool act,
+                                         int slot, int SL, int HP, float& m, double& d) {
+  constexpr int U = 4;
+  m = -__builtin_huge_valf();
+  d = 0.0;
+  if (act)
+    for (int c = slot; c < nch; c += U * SL) {
+      float t[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) t[u] = pm[(int64_t)min(c + u * SL, nch - 1) * H];
+#pragma unroll
+      for (int u = 0; u < U; ++u) m = t[u] > m ? t[u] : m;
+    }
+  m = slots_max(m, HP, kWave);
+  if (act)
+    for (int c = slot; c < nch; c += U * SL) {
+      float t[U];
+      double q[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t j = (int64_t)min(c + u * SL, nch - 1) * H;
+        t[u] = pm[j];
+        q[u] = pd[j];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c + u * SL < nch) d += q[u] * (double)(t[u] == m ? 1.0f : expf(t[u] - m));
+    }
+  d = slots_sum(d, HP, kWave);
+}
+
+// Alpha of the chunks of split rows, one wavefront per chunk. (One block of 16
+// wavefronts per split row, with the chunks' pairs combined behind barriers: 24
+// us for 1,400 chunks of 460 rows, now 11.)
+template <int NST, int K>
+__device__ __forceinline__ void chunk_write(const int* __restrict__ perm,
+                                            const float* __restrict__ s, int H, int HP,
+                                            const WorkItem& it, const ChunkRow& r,
+                                            const float* __restrict__ pm,
+                                            const double* __restrict__ pd,
                                             float* __restrict__ out,
                                             float* __restrict__ out_csr) {
   const int SL = kWave / HP;
-  const int slot = lane / HP, hh = lane % HP;
-  const bool has = kb < ke;
-  constexpr int R = NST > 0 ? NST : 1;  // registers (NST = 0: the running sweep)
+  const int slot = lane_id() / HP, hh = lane_id() & (HP - 1);
+  constexpr int R = NST > 0 ? NST : 1;  // registers (NST = 0: the scores loaded in rounds)
   int e[R];
-  if constexpr (NST > 0) load_ids<NST>(perm, kb, ke, slot, SL, e);
+  if constexpr (NST > 0) load_ids<NST>(perm, it.kbeg, it.kend, slot, SL, e);
   for (int hb = 0; hb < H; hb += HP) {
     const int h = hb + hh;
     const bool act = h < H;
-    float v[R];
-    float m = -__builtin_huge_valf();
-    double d = 0.0;
-    if (has) {
-      if constexpr (NST > 0) {
-        load_scores<NST>(s, H, h, act, e, v);
-        m = regs_max<NST>(v, HP);
-        d = regs_exp_sum<NST, false>(v, m, HP);
-      } else {
-        sweep_stats(perm, s, H, h, act, kb, ke, slot, SL, HP, m, d);
-      }
+    float v[R][K], m[K], inv[K];
+    if constexpr (NST > 0) load_scores<NST, K>(s, H, h, act, e, v);
+    const int64_t p0 = ((int64_t)r.slot0 * H + h) * K;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      double d;
+      row_pair(pm + p0 + i, pd + p0 + i, r.nch, H * K, act, slot, SL, HP, m[i], d);
+      if constexpr (NST > 0) inv[i] = (float)(1.0 / d);
+      else sweep_write(perm, s, H, h, act, it.kbeg, it.kend, slot, SL, m[i], 1.0 / d, out, out_csr);
     }
-    lm[w][lane] = m;
-    ld[w][lane] = d;
-    __syncthreads();
-    // the row's maximum, then the chunks' sums rescaled to it, in chunk order
-    float mr = -__builtin_huge_valf();
-    for (int c = 0; c < nch; ++c) mr = lm[c][lane] > mr ? lm[c][lane] : mr;
-    double dr = 0.0;
-    for (int c = 0; c < nch; ++c) dr += ld[c][lane] * (double)expf(lm[c][lane] - mr);
-    __syncthreads();  // the pairs are read before the next head pass writes
-    if (!has) continue;
-    const double r = 1.0 / dr;
     if constexpr (NST > 0) {
 #pragma unroll
-      for (int u = 0; u < NST; ++u) v[u] = expf(v[u] - mr);
-      regs_write<NST>(v, e, (float)r, kb, slot, SL, H, h, act, out, out_csr);
-    } else {
-      sweep_write(perm, s, H, h, act, kb, ke, slot, SL, mr, r, out, out_csr);
+      for (int u = 0; u < NST; ++u)
+#pragma unroll
+        for (int i = 0; i < K; ++i) v[u][i] = expf(v[u][i] - m[i]);
+      regs_write<NST, K>(v, e, inv, it.kbeg, slot, SL, H, h, act, out, out_csr);
     }
   }
 }
 
-// One block per split row (kSplitWaves wavefronts). A row of at most
-// kSplitWaves chunks goes through split_chunk (the register sweep when a
-// whole chunk fits, the same choice for every chunk of the launch). A longer
-// row: the chunks' pairs come from softmax_items and are combined in chunk
-// order the same way, and wavefront w writes chunks w, w + kSplitWaves, ...
-__global__ __launch_bounds__(kSplitWaves * kWave) void softmax_split(
+template <int K>
+__global__ __launch_bounds__(kItemBlock) void softmax_chunks(
+    const WorkItem* __restrict__ heavy, const int* __restrict__ rowptr, int chunk,
+    const int* __restrict__ perm, const float* __restrict__ s, int H, int HP,
+    const float* __restrict__ pm, const double* __restrict__ pd, float* __restrict__ out,
+    float* __restrict__ out_csr) {
+  const WorkItem it = heavy[blockIdx.x];
+  const ChunkRow r = chunk_row(it, rowptr, chunk);
+  if (r.nch > kGiantChunks) return;
+  const int SL = kWave / HP, cst = (chunk + SL - 1) / SL;
+  if (cst <= 2) {
+    chunk_write<2, K>(perm, s, H, HP, it, r, pm, pd, out, out_csr);
+  } else if (cst <= 4) {
+    chunk_write<4, K>(perm, s, H, HP, it, r, pm, pd, out, out_csr);
+  } else if (K == 1 && cst <= 8) {
+    chunk_write<K == 1 ? 8 : 2, K>(perm, s, H, HP, it, r, pm, pd, out, out_csr);
+  } else {  // single heads
+    chunk_write<0, 1>(perm, s, H * K, min(HP * K, kWave), it, r, pm, pd, out, out_csr);
+  }
+}
+
+// Rows of more than kGiantChunks chunks: the pairs combined once per wavefront
+// of the row's block, and wavefront w writes chunks w, w + kGiantWaves, ...
+__global__ __launch_bounds__(kGiantWaves * kWave) void softmax_giant(
     const SplitRow* __restrict__ split, const int* __restrict__ rowptr, int chunk,
     const int* __restrict__ perm, const float* __restrict__ s, int H, int HP,
     const float* __restrict__ pm, const double* __restrict__ pd, float* __restrict__ out,
     float* __restrict__ out_csr) {
-  __shared__ float lm[kSplitWaves][kWave];
-  __shared__ double ld[kSplitWaves][kWave];
-  const SplitRow* sr = split + blockIdx.x;
-  const int row = uniform(sr->row), nch = uniform(sr->nchunks), s0 = uniform(sr->slot0);
-  const int rb = uniform(rowptr[row]), re = uniform(rowptr[row + 1]);
+  const SplitRow sr = split[blockIdx.x];
+  if (sr.nchunks <= kGiantChunks) return;
+  const int rb = uniform(rowptr[sr.row]), re = uniform(rowptr[sr.row + 1]);
   const int w = uniform((int)threadIdx.x / kWave);
-  const int lane = threadIdx.x & (kWave - 1);
-  const int SL = kWave / HP;
-  if (nch <= kSplitWaves) {
-    const int kb = rb + w * chunk, ke = min(re, kb + chunk);  // kb >= ke: no chunk
-    const int cst = (chunk + SL - 1) / SL;  // slot steps of a whole chunk
-    if (cst <= 2)
-      split_chunk<2>(perm, s, H, HP, kb, ke, nch, w, lane, lm, ld, out, out_csr);
-    else if (cst <= 4)
-      split_chunk<4>(perm, s, H, HP, kb, ke, nch, w, lane, lm, ld, out, out_csr);
-    else if (cst <= kSmCap)
-      split_chunk<kSmCap>(perm, s, H, HP, kb, ke, nch, w, lane, lm, ld, out, out_csr);
-    else if (cst <= 2 * kSmCap)
-      split_chunk<2 * kSmCap>(perm, s, H, HP, kb, ke, nch, w, lane, lm, ld, out, out_csr);
-    else
-      split_chunk<0>(perm, s, H, HP, kb, ke, nch, w, lane, lm, ld, out, out_csr);
-    return;
-  }
-  const int slot = lane / HP, hh = lane % HP;
+  const int SL = kWave / HP, slot = lane_id() / HP, hh = lane_id() & (HP - 1);
   for (int hb = 0; hb < H; hb += HP) {
     const int h = hb + hh;
     const bool act = h < H;
-    float m = -__builtin_huge_valf();
-    double d = 0.0;
-    // the chunks' pairs, a share per slot, then over the slots
-    if (act)
-      for (int c = slot; c < nch; c += SL)
-        stat_merge(m, d, pm[(int64_t)(s0 + c) * H + h], pd[(int64_t)(s0 + c) * H + h]);
-    slots_merge(m, d, HP);
-    const double r = 1.0 / d;
-    for (int c = w; c < nch; c += kSplitWaves) {
+    float m;
+    double d;
+    const int64_t p0 = (int64_t)sr.slot0 * H + h;
+    row_pair(pm + p0, pd + p0, sr.nchunks, H, act, slot, SL, HP, m, d);
+    for (int c = w; c < sr.nchunks; c += kGiantWaves) {
       const int kb = rb + c * chunk, ke = min(re, kb + chunk);
-      sweep_write(perm, s, H, h, act, kb, ke, slot, SL, m, r, out, out_csr);
+      sweep_write(perm, s, H, h, act, kb, ke, slot, SL, m, 1.0 / d, out, out_csr);
     }
   }
 }
@@ -616,24 +569,35 @@ int launch_segment_softmax(const Graph& g, const float* scores, int H, float* ou
   // scores and alpha in the graph order: position k is edge k, one output
   const int* perm = graph_order ? nullptr : g.perm;
   if (graph_order) out_csr = nullptr;
-  int hp = 1;
-  while (hp * 2 <= std::min(H, kWave)) hp *= 2;
+  const int hp = heads_per_pass(H);
   float* pm = static_cast<float*>(ws);
   double* pd = reinterpret_cast<double*>(
       static_cast<char*>(ws) + align_up(sizeof(float) * (size_t)std::max<int64_t>((int64_t)g.n_heavy * H, 1), 256));
-  const int64_t short_waves = (g.n_short + kWave / hp - 1) / (kWave / hp);
-  const int64_t waves = short_waves + g.n_long + g.n_heavy;
-  if (waves > INT32_MAX) return fail(TFG_ERR_TOO_LARGE, "segment softmax: too many work items");
-  if (waves > 0) {
-    softmax_items<<<(unsigned)((waves + (kItemBlock / kWave) - 1) / (kItemBlock / kWave)), kItemBlock, 0, s>>>(
-        g.short_rows, g.n_short, (int)short_waves, g.long_rows, g.n_long, g.heavy, g.n_heavy,
-        g.rowptr, g.chunk, perm, scores, H, hp, out, out_csr, pm, pd);
-    TFG_LAUNCHED("softmax_items");
-  }
-  if (g.n_split > 0) {
-    softmax_split<<<(unsigned)g.n_split, kSplitWaves * kWave, 0, s>>>(
+  const auto run = [&](auto k_) {
+    constexpr int K = decltype(k_)::value;
+    const int hk = H / K, hpk = heads_per_pass(hk);
+    RowGroups L;
+    const int64_t waves = row_groups<K>(g, hpk, L);
+    if (waves > INT32_MAX) return fail(TFG_ERR_TOO_LARGE, "segment softmax: too many work items");
+    if (waves > 0) {
+      softmax_items<K><<<(unsigned)waves, kItemBlock, 0, s>>>(L, perm, scores, hk, hpk, out,
+                                                              out_csr, pm, pd);
+      TFG_LAUNCHED("softmax_items");
+    }
+    if (g.n_heavy > 0) {
+      softmax_chunks<K><<<(unsigned)g.n_heavy, kItemBlock, 0, s>>>(
+          g.heavy, g.rowptr, g.chunk, perm, scores, hk, hpk, pm, pd, out, out_csr);
+      TFG_LAUNCHED("softmax_chunks");
+    }
+    return (int)TFG_OK;
+  };
+  const int rc = H % 4 == 0 ? run(std::integral_constant<int, 4>{})
+                            : run(std::integral_constant<int, 1>{});
+  if (rc) return rc;
+  if (g.n_heavy > kGiantChunks) {
+    softmax_giant<<<(unsigned)g.n_split, kGiantWaves * kWave, 0, s>>>(
         g.split, g.rowptr, g.chunk, perm, scores, H, hp, pm, pd, out, out_csr);
-    TFG_LAUNCHED("softmax_split");
+    TFG_LAUNCHED("softmax_giant");
   }
   return TFG_OK;
 }

@@ -26,26 +26,135 @@ __device__ __forceinline__ void stat_merge(float& m, double& d, float m2, double
 
 // One exponential per score: t = exp(-|v - m|) is the new term when the
 // maximum stays and the rescale factor of d when it grows (from m = -inf the
-// factor is 0).
+// factor is 0). A score of -inf adds nothing, also to an empty pair.
 __device__ __forceinline__ void stat_add(float& m, double& d, float v) {
 #pragma clang fp contract(off)
   const float dlt = v - m;
-  const float t = expf(-__builtin_fabsf(dlt));
+  const float t = v == -__builtin_huge_valf() ? 0.0f : expf(-__builtin_fabsf(dlt));
   const bool up = dlt > 0.0f;
   d = up ? d * (double)t + 1.0 : d + (double)t;
   m = up ? v : m;
 }
 
-// Register sweeps of the row plan's items (softmax and its gradient): lanes
-// are (slot, head) pairs, SL = 64 / HP slots; slot step u of an item
-// starting at kb is position kb + slot + u * SL.
-// Edge ids of NST steps of [kb, ke) (-1 past ke).
+// Rows and chunks of long rows, several per wavefront:
+// an item takes a group of `lanes` neighbouring lanes, which are (slot, head)
+// pairs: HP heads (a power of two) and SL = lanes / HP slots; slot step u of an item
+// starting at kb is position kb + slot + u * SL. Where H is a multiple of 4 a lane
+// holds K = 4 heads of an edge (16-byte accesses), and HP, H count these fours.
+// One wavefront per item and one head per lane left most lanes with one or two
+// values, and the butterflies, the round trips on each row's extent and the 4-byte
+// accesses set the pace.
+template <int K>
+constexpr int group_steps() { return K == 4 ? 4 : 8; }  // slot steps held in registers
+
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+template <int K>
+__device__ __forceinline__ void load_k(const float* __restrict__ p, float (&v)[K]) {
+  if constexpr (K == 4) {
+    const f4u t = *reinterpret_cast<const f4u*>(p);
+    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+  } else {
+    v[0] = *p;
+  }
+}
+template <int K>
+__device__ __forceinline__ void store_k(float* __restrict__ p, const float (&v)[K]) {
+  if constexpr (K == 4) *reinterpret_cast<f4u*>(p) = f4u{v[0], v[1], v[2], v[3]};
+  else *p = v[0];
+}
+
+// HP for H heads: every head in one pass where 64 lanes hold them, some lanes
+// idle. (The largest power of two within H idles as many in its last pass and
+// reads the ids and the scattered lines of the caller's order twice: 8M edges, 3
+// heads, 619 us.)
+inline int heads_per_pass(int H) {
+  int hp = 1;
+  while (hp < H && hp < kWave) hp <<= 1;
+  return hp;
+}
+
+constexpr int kGroupLists = 5;
+struct RowGroups {
+  const WorkItem* items[kGroupLists];
+  int n[kGroupLists];
+  int lanes[kGroupLists];
+  int waves[kGroupLists];
+};
+
+// The plan's lists, longest items first, and the number of wavefronts. A list
+// of items of at most `edges` edges takes as many slots as leave a lane its
+// steps, and at least 64 bytes per step of a row (or all its edges).
+template <int K>
+inline int64_t row_groups(const Graph& g, int hp, RowGroups& L) {
+  int64_t total = 0;
+  auto add = [&](int i, const WorkItem* items, int n, int edges) {
+    int lanes = hp;
+    while (lanes < kWave && (lanes / hp * group_steps<K>() < edges || (lanes * K < 16 && lanes / hp < edges))) lanes <<= 1;
+    L.items[i] = items;
+    L.n[i] = n;
+    L.lanes[i] = lanes;
+    L.waves[i] = (int)(((int64_t)n * lanes + kWave - 1) / kWave);
+    total += L.waves[i];
+  };
+  add(0, g.heavy, g.n_heavy, g.chunk);
+  add(1, g.long_rows, g.n_over64, g.chunk);
+  add(2, g.long_rows + g.n_over64, g.n_over32 - g.n_over64, 64);
+  add(3, g.long_rows + g.n_over32, g.n_long - g.n_over32, 32);
+  add(4, g.short_rows, g.n_short, kShortRow);
+  return total;
+}
+
+// The item of this lane's group (no edges past the list's end), its lane count
+// and the longest item of the wavefront.
+struct GroupItem {
+  int kb, ke, pslot, lanes, longest;
+};
+__device__ __forceinline__ GroupItem group_item(const RowGroups& L, int wid) {
+  int li = 0;
+#pragma unroll
+  for (int i = 0; i + 1 < kGroupLists; ++i)
+    if (li == i && wid >= L.waves[i]) {  // uniform
+      wid -= L.waves[i];
+      li = i + 1;
+    }
+  GroupItem r;
+  r.lanes = L.lanes[li];
+  const int i = wid * (kWave / r.lanes) + lane_id() / r.lanes;
+  const bool have = i < L.n[li];
+  const WorkItem it = L.items[li][have ? i : 0];
+  r.kb = it.kbeg;
+  r.ke = have ? it.kend : it.kbeg;
+  r.pslot = have ? it.slot : -1;
+  int n = r.ke - r.kb;
+  for (int o = r.lanes; o < kWave; o <<= 1) n = max(n, __shfl_xor(n, o));
+  r.longest = uniform(n);
+  return r;
+}
+
+// Long rows: a second launch, one wavefront per chunk, combines the chunks'
+// statistics itself; rows of more than kGiantChunks chunks (whose wavefronts would
+// read more statistics than scores) go one block of kGiantWaves wavefronts each,
+// in a launch made where the graph has that many chunks.
+constexpr int kGiantChunks = 2048;
+constexpr int kGiantWaves = 16;
+
+// The row of a chunk: its number of chunks and the slot of its first.
+struct ChunkRow {
+  int nch, slot0;
+};
+__device__ __forceinline__ ChunkRow chunk_row(const WorkItem& it, const int* __restrict__ rowptr,
+                                              int chunk) {
+  const int rb = uniform(rowptr[it.row]), re = uniform(rowptr[it.row + 1]);
+  return {(re - rb + chunk - 1) / chunk, it.slot - (it.kbeg - rb) / chunk};
+}
+
 // Where the per-edge values of graph position k live: at the caller's edge id
 // perm[k], or (perm NULL: arrays kept in the graph order) at k itself.
 __device__ __forceinline__ int edge_at(const int* __restrict__ perm, int k) {
   return perm != nullptr ? perm[k] : k;
 }
 
+// Edge ids of NST steps of [kb, ke) (-1 past ke).
 template <int NST>
 __device__ __forceinline__ void load_ids(const int* __restrict__ perm, int kb, int ke, int slot,
                                          int SL, int (&e)[NST]) {
@@ -56,10 +165,10 @@ __device__ __forceinline__ void load_ids(const int* __restrict__ perm, int kb, i
   }
 }
 
-// Sum over the slots of a head (lanes l, l ^ HP, l ^ 2 HP, ...). IEEE
-// addition commutes, so every lane of a head ends with the same sum.
-__device__ __forceinline__ double slots_sum(double d, int HP) {
-  for (int off = HP; off < kWave; off <<= 1) d += __shfl_xor(d, off);
+// Sum over the slots of a head (lanes l, l ^ HP, l ^ 2 HP, ... of a group of
+// `lanes`). IEEE addition commutes, so every lane of a head ends with the same sum.
+__device__ __forceinline__ double slots_sum(double d, int HP, int lanes) {
+  for (int off = HP; off < lanes; off <<= 1) d += __shfl_xor(d, off);
   return d;
 }
 

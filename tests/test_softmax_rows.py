@@ -1,0 +1,77 @@
+"""Segment softmax and its gradient at the row lengths and head counts where their lane groups
+can go wrong: every length around the lists' edges and the chunks' (128 edges), hubs of 17 and 65
+chunks, one of over 2,048 (its statistics combined by a block), heads in one and in several
+passes, and rows with scores of -inf. Against 64-bit sums, at 1e-5: a few float32 roundings of the
+exponential and the division (2^-24 each, times the scores' size of up to about 25)."""
+
+import os
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+pytestmark = pytest.mark.gpu
+
+LENGTHS = [0, 1, 2, 7, 8, 9, 10, 15, 16, 17, 23, 31, 32, 33, 47, 63, 64, 65, 100, 127, 128, 129,
+           255, 256, 257, 700]
+
+
+@pytest.fixture(scope="module")
+def tfg():
+    import paper_2101_11552_amd as m
+    m.load()
+    return m
+
+
+def _case(tfg, seed, H, hubs, masked):
+    r = np.random.default_rng(seed)
+    deg = r.permutation(np.concatenate([np.repeat(LENGTHS, 6), np.array(hubs, dtype=np.int64)]))
+    tgt = np.repeat(np.arange(deg.size), deg)[r.permutation(int(deg.sum()))]
+    ei = np.stack([r.integers(0, deg.size, tgt.size), tgt]).astype(np.int64)
+    s = (6 * r.standard_normal((tgt.size, H))).astype(np.float32)
+    if masked:  # the first edges of the input order among them: whole chunks and leading slots
+        s[r.random(s.shape) < 0.6] = -np.inf
+        s[: tgt.size // 3] = -np.inf
+    g = tfg.tfg_graph_create(torch.from_numpy(ei).cuda(), deg.size)
+    return r, tgt, deg.size, s, g
+
+
+def _softmax64(s, tgt, n):
+    m = np.full((n, s.shape[1]), -np.inf)
+    np.maximum.at(m, tgt, s.astype(np.float64))
+    with np.errstate(invalid="ignore"):
+        x = np.exp(s - m[tgt])  # NaN where every score of the row is -inf
+    d = np.zeros((n, s.shape[1]))
+    np.add.at(d, tgt, x)
+    return x / d[tgt]
+
+
+@pytest.mark.parametrize("H,hubs,masked", [
+    (1, [2100, 8300, 300_000], False), (8, [2100, 8300, 300_000], False), (2, [2100], False),
+    (3, [2100], False), (4, [2100], True), (5, [8300], False), (8, [2100, 8300], True),
+    (16, [2100], False), (17, [2100], False), (32, [2100], True), (64, [2100], False),
+    (80, [2100], True)])
+def test_softmax_rows(tfg, H, hubs, masked):
+    r, tgt, n, s, g = _case(tfg, H + masked, H, hubs, masked)
+    perm = np.argsort(tgt, kind="stable")
+    ref = _softmax64(s, tgt, n)
+    t = torch.from_numpy(tgt).cuda()
+    a, a_csr = tfg.tfg_segment_softmax(torch.from_numpy(s).cuda(), t, n, graph=g, out_csr=True)
+    ordered = tfg.tfg_segment_softmax_graph(g, torch.from_numpy(s[perm]).cuda())
+    a, a_csr, ordered = a.cpu().numpy(), a_csr.cpu().numpy(), ordered.cpu().numpy()
+    np.testing.assert_array_equal(a_csr, a[perm])
+    np.testing.assert_array_equal(ordered, a[perm])
+    np.testing.assert_allclose(a, ref, rtol=1e-5, atol=1e-30, equal_nan=True)
+
+    al = np.nan_to_num(a)
+    da = r.standard_normal(s.shape).astype(np.float32)
+    ds = tfg.tfg_segment_softmax_graph_backward(g, torch.from_numpy(al[perm]).cuda(),
+                                                torch.from_numpy(da[perm]).cuda())
+    dot, size = (np.zeros((n, H)) for _ in range(2))
+    np.add.at(dot, tgt, al.astype(np.float64) * da)
+    np.add.at(size, tgt, al.astype(np.float64) * np.abs(da))
+    want, scale = al * (da - dot[tgt]), al * (np.abs(da) + size[tgt])
+    err = np.abs(ds.cpu().numpy() - want[perm]) / np.maximum(scale[perm], 1e-30)
+    assert float(err.max()) <= 1e-5
