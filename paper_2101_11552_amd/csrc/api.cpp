@@ -664,7 +664,8 @@ int tfg_segment_pool(const float* x, int64_t Nb, int64_t F, int64_t ldx, const v
   hipStream_t s = as_stream(stream);
   int* goff = static_cast<int*>(ws);
   int* err = reinterpret_cast<int*>(static_cast<char*>(ws) + align_up(sizeof(int) * (size_t)(G + 1), 256));
-  rc = launch_segment_pool(x, Nb, F, ldx, graph_index, index_type, G, reduce, out, argmax, goff, err, s);
+  rc = launch_segment_pool(x, Nb, F, ldx, graph_index, index_type, G, reduce, out, argmax, goff,
+                           validate ? err : nullptr, s);
   if (rc) return rc;
   if (validate) {
     int flags = 0;
@@ -696,7 +697,7 @@ int tfg_segment_pool_backward(const float* dy, int64_t G, int64_t F, const void*
   int* goff = static_cast<int*>(ws);
   int* err = reinterpret_cast<int*>(static_cast<char*>(ws) + align_up(sizeof(int) * (size_t)(G + 1), 256));
   rc = launch_segment_pool_backward(dy, G, F, graph_index, index_type, Nb, reduce, argmax, dx, ldx,
-                                    goff, err, s);
+                                    goff, validate ? err : nullptr, s);
   if (rc) return rc;
   if (validate) {
     int flags = 0;

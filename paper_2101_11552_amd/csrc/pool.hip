@@ -1,14 +1,16 @@
 // Graph pooling over a sorted node -> graph index (gfx950): segment bounds
 // from the sorted index (with range and order checks), then one wavefront per
 // graph reducing its contiguous node rows (sum / mean / max + argmax); and its
-// gradient, one thread per node and column vector.
+// gradient, four nodes and a column vector per thread.
 #include "wave.h"
 
 namespace tfg {
 namespace {
 
-typedef float f2 __attribute__((ext_vector_type(2)));
-typedef float f4 __attribute__((ext_vector_type(4)));
+// four columns of a row at dword alignment (any width and leading dimension: the
+// last lane of a row steps back to end at its last column)
+typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef int i4 __attribute__((ext_vector_type(4), aligned(4)));
 
 __global__ void zero_ints(int* __restrict__ p, int64_t n) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -22,7 +24,7 @@ __device__ __forceinline__ int64_t clamp_gid(int64_t g, int64_t G) {
 // goff[g] = first node of graph g, goff[G] = Nb. Node n writes the starts of
 // the graphs (gi[n-1], gi[n]]; the thread n = Nb writes the empty tail graphs.
 // With valid sorted input every entry is written exactly once. Otherwise the
-// error flag is set, and every entry is still written (so goff needs no
+// error flag is set (unless err is NULL), and every entry is still written (so goff needs no
 // clearing first) with a value in [0, Nb]: the clamped ids run from -1 (before
 // node 0) to G (after node Nb - 1), so each g in [0, G] lies in (prev, cur] for
 // the first n whose cur reaches g.
@@ -39,7 +41,7 @@ __global__ __launch_bounds__(kBlock) void segment_bounds(const IdxT* __restrict_
     int bad = 0;
     if (cur < 0 || cur >= G) bad |= kErrIndex;
     if (n > 0 && cur < prev) bad |= kErrUnsorted;
-    if (bad) atomicOr(err, bad);
+    if (bad != 0 && err != nullptr) atomicOr(err, bad);
   } else {
     cur = G;  // the tail: graphs after the last node's graph start at Nb
   }
@@ -52,12 +54,15 @@ __device__ __forceinline__ void load_row(const float* __restrict__ p, float (&v)
   if constexpr (V == 4) {
     f4 t = *reinterpret_cast<const f4*>(p);
     v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-  } else if constexpr (V == 2) {
-    f2 t = *reinterpret_cast<const f2*>(p);
-    v[0] = t.x; v[1] = t.y;
   } else {
     v[0] = *p;
   }
+}
+
+template <int V>
+__device__ __forceinline__ void store_row(float* __restrict__ p, const float (&v)[V]) {
+  if constexpr (V == 4) __builtin_nontemporal_store(f4{v[0], v[1], v[2], v[3]}, reinterpret_cast<f4*>(p));
+  else __builtin_nontemporal_store(v[0], p);
 }
 
 __device__ __forceinline__ void max_combine(float& v, int& a, float vb, int ab) {
@@ -84,8 +89,8 @@ __global__ __launch_bounds__(kItemBlock) void pool_rows(const float* __restrict_
   b = b < 0 ? 0 : (b > Nb ? (int)Nb : b);
   e = e < b ? b : (e > Nb ? (int)Nb : e);
   for (int f0 = 0; f0 < F; f0 += FC) {
-    const int f = f0 + sl * V;
-    const bool fok = f < F;
+    const int fw = f0 + sl * V, f = min(fw, F - V);
+    const bool fok = fw < F;
     float acc[U][V];
     int arg[U][V];
 #pragma unroll
@@ -179,8 +184,6 @@ void launch_pool_vec(int vec, int slots, dim3 grid, hipStream_t s, const float* 
                      int* argout) {
   if (vec == 4)
     launch_pool_slots<4, MAX>(slots, grid, s, x, ldx, F, goff, G, Nb, mean, out, argout);
-  else if (vec == 2)
-    launch_pool_slots<2, MAX>(slots, grid, s, x, ldx, F, goff, G, Nb, mean, out, argout);
   else
     launch_pool_slots<1, MAX>(slots, grid, s, x, ldx, F, goff, G, Nb, mean, out, argout);
 }
@@ -189,54 +192,97 @@ void launch_pool_vec(int vec, int slots, dim3 grid, hipStream_t s, const float* 
 
 namespace {
 
-// Gradient of the pooling: one thread per (node, V columns) writes
-// dx[n, c] = dy[g, c] (sum), dy[g, c] / count(g) (mean), or dy[g, c] where
-// node n won the forward max of (g, c), else 0. g = the clamped graph id; the
-// counts come from the segment bounds.
+// Gradient of the pooling: dx[n, c] = dy[g, c] (sum), dy[g, c] / count(g) (mean),
+// or dy[g, c] where node n won the forward max of (g, c), else 0. g = the clamped
+// graph id; the counts come from the segment bounds. A thread takes V columns of
+// kGradNodes nodes, 1 << lg neighbouring lanes a row, the chains from graph id to
+// dy row of its nodes in flight together, and the stores stream past the L2s.
+// Without the index check sum and max need no segment bounds. 1.05M nodes of 64
+// columns: 63 us with one node per thread and a 64-bit division, now 46 (5.9 TB/s
+// of stores); of 63 columns 151, now 60; 143,000 nodes 20, now 13.
+constexpr int kGradNodes = 4;
 template <typename IdxT, int V>
 __global__ __launch_bounds__(kBlock) void pool_grad(const float* __restrict__ dy, int64_t G,
                                                     int F, const IdxT* __restrict__ gi,
                                                     int64_t Nb, const int* __restrict__ goff,
                                                     int reduce, const int* __restrict__ arg,
-                                                    float* __restrict__ dx, int64_t ldx) {
-  const int cols = F / V;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= Nb * cols) return;
-  const int64_t n = i / cols;
-  const int f = (int)(i - n * cols) * V;
-  const int64_t g = clamp_gid((int64_t)gi[n], G);
-  float v[V];
-  if (g < 0) {
+                                                    float* __restrict__ dx, int64_t ldx, int lg) {
+  const int rows = kBlock >> lg;  // per block and step
+  const int64_t n0 = (int64_t)blockIdx.x * (kGradNodes * rows) + (threadIdx.x >> lg);
+  const int sub = (int)threadIdx.x & ((1 << lg) - 1);
+  int64_t g[kGradNodes];
+  float cnt[kGradNodes];
 #pragma unroll
-    for (int j = 0; j < V; ++j) v[j] = 0.0f;
-  } else {
-    load_row<V>(dy + g * F + f, v);
-    if (reduce == TFG_MEAN) {
-      const float cnt = (float)(goff[g + 1] - goff[g]);
-#pragma unroll
-      for (int j = 0; j < V; ++j) v[j] = cnt > 0.0f ? v[j] / cnt : 0.0f;
-    } else if (reduce == TFG_MAX) {
-#pragma unroll
-      for (int j = 0; j < V; ++j) v[j] = arg[g * F + f + j] == (int)n ? v[j] : 0.0f;
-    }
+  for (int u = 0; u < kGradNodes; ++u) {
+    const int64_t n = n0 + u * rows;
+    g[u] = n < Nb ? clamp_gid((int64_t)gi[n], G) : -1;
   }
 #pragma unroll
-  for (int j = 0; j < V; ++j) dx[n * ldx + f + j] = v[j];
+  for (int u = 0; u < kGradNodes; ++u)
+    cnt[u] = reduce == TFG_MEAN && g[u] >= 0 ? (float)(goff[g[u] + 1] - goff[g[u]]) : 1.0f;
+  for (int fw = sub * V; fw < F; fw += V << lg) {
+    const int f = min(fw, F - V);
+    float v[kGradNodes][V];
+#pragma unroll
+    for (int u = 0; u < kGradNodes; ++u) {
+#pragma unroll
+      for (int j = 0; j < V; ++j) v[u][j] = 0.0f;
+      if (g[u] >= 0) load_row<V>(dy + g[u] * F + f, v[u]);
+    }
+    if (reduce == TFG_MEAN) {
+#pragma unroll
+      for (int u = 0; u < kGradNodes; ++u)
+#pragma unroll
+        for (int j = 0; j < V; ++j) v[u][j] = cnt[u] > 0.0f ? v[u][j] / cnt[u] : 0.0f;
+    } else if (reduce == TFG_MAX) {
+#pragma unroll
+      for (int u = 0; u < kGradNodes; ++u)
+        if (g[u] >= 0) {
+          int a[V];
+          if constexpr (V == 4) {
+            const i4 t = *reinterpret_cast<const i4*>(arg + g[u] * F + f);
+            a[0] = t.x; a[1] = t.y; a[2] = t.z; a[3] = t.w;
+          } else {
+            a[0] = arg[g[u] * F + f];
+          }
+#pragma unroll
+          for (int j = 0; j < V; ++j) v[u][j] = a[j] == (int)(n0 + u * rows) ? v[u][j] : 0.0f;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kGradNodes; ++u)
+      if (n0 + u * rows < Nb) store_row<V>(dx + (n0 + u * rows) * ldx + f, v[u]);
+  }
 }
 
 template <typename IdxT>
-void launch_pool_grad(int vec, const float* dy, int64_t G, int F, const void* gi, int64_t Nb,
+void launch_pool_grad(const float* dy, int64_t G, int F, const void* gi, int64_t Nb,
                       const int* goff, int reduce, const int* arg, float* dx, int64_t ldx,
                       hipStream_t s) {
-  const int64_t n = Nb * (F / vec);
-  const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
+  const int vec = F >= 4 ? 4 : 1;
+  int lg = 0;
+  while (lg < 6 && (vec << lg) < F) ++lg;
+  const int64_t per = (int64_t)kGradNodes * (kBlock >> lg);
+  const unsigned nb = (unsigned)((Nb + per - 1) / per);
   const IdxT* g = static_cast<const IdxT*>(gi);
   if (vec == 4)
-    pool_grad<IdxT, 4><<<nb, kBlock, 0, s>>>(dy, G, F, g, Nb, goff, reduce, arg, dx, ldx);
-  else if (vec == 2)
-    pool_grad<IdxT, 2><<<nb, kBlock, 0, s>>>(dy, G, F, g, Nb, goff, reduce, arg, dx, ldx);
+    pool_grad<IdxT, 4><<<nb, kBlock, 0, s>>>(dy, G, F, g, Nb, goff, reduce, arg, dx, ldx, lg);
   else
-    pool_grad<IdxT, 1><<<nb, kBlock, 0, s>>>(dy, G, F, g, Nb, goff, reduce, arg, dx, ldx);
+    pool_grad<IdxT, 1><<<nb, kBlock, 0, s>>>(dy, G, F, g, Nb, goff, reduce, arg, dx, ldx, lg);
+}
+
+// The segment bounds (err NULL: nobody reads the flag).
+int launch_segment_bounds(const void* graph_index, int index_type, int64_t Nb, int64_t G,
+                          int* goff, int* err, hipStream_t s) {
+  const unsigned nb = (unsigned)((Nb + 1 + kBlock - 1) / kBlock);
+  if (index_type == TFG_I64)
+    segment_bounds<int64_t><<<nb, kBlock, 0, s>>>(static_cast<const int64_t*>(graph_index), Nb, G,
+                                                   goff, err);
+  else
+    segment_bounds<int32_t><<<nb, kBlock, 0, s>>>(static_cast<const int32_t*>(graph_index), Nb, G,
+                                                   goff, err);
+  TFG_LAUNCHED("segment_bounds");
+  return TFG_OK;
 }
 
 }  // namespace
@@ -244,27 +290,15 @@ void launch_pool_grad(int vec, const float* dy, int64_t G, int F, const void* gi
 int launch_segment_pool_backward(const float* dy, int64_t G, int64_t F, const void* graph_index,
                                  int index_type, int64_t Nb, int reduce, const int32_t* argmax,
                                  float* dx, int64_t ldx, int* goff, int* err, hipStream_t s) {
-  zero_ints<<<1, 64, 0, s>>>(err, 1);
+  if (err != nullptr) zero_ints<<<1, 64, 0, s>>>(err, 1);
   if (Nb == 0 || F == 0) return TFG_OK;
-  const unsigned nb = (unsigned)((Nb + 1 + kBlock - 1) / kBlock);
+  // the bounds: for the mean's counts, and where the index is to be checked
+  if (err != nullptr || reduce == TFG_MEAN)
+    if (int rc = launch_segment_bounds(graph_index, index_type, Nb, G, goff, err, s)) return rc;
   if (index_type == TFG_I64)
-    segment_bounds<int64_t><<<nb, kBlock, 0, s>>>(static_cast<const int64_t*>(graph_index), Nb, G,
-                                                   goff, err);
+    launch_pool_grad<int64_t>(dy, G, (int)F, graph_index, Nb, goff, reduce, argmax, dx, ldx, s);
   else
-    segment_bounds<int32_t><<<nb, kBlock, 0, s>>>(static_cast<const int32_t*>(graph_index), Nb, G,
-                                                   goff, err);
-  TFG_LAUNCHED("segment_bounds");
-  auto fits = [&](int v) {
-    return F % v == 0 && ldx % v == 0 && reinterpret_cast<uintptr_t>(dx) % (4 * v) == 0 &&
-           reinterpret_cast<uintptr_t>(dy) % (4 * v) == 0;
-  };
-  const int vec = fits(4) ? 4 : fits(2) ? 2 : 1;
-  if (index_type == TFG_I64)
-    launch_pool_grad<int64_t>(vec, dy, G, (int)F, graph_index, Nb, goff, reduce, argmax, dx, ldx,
-                              s);
-  else
-    launch_pool_grad<int32_t>(vec, dy, G, (int)F, graph_index, Nb, goff, reduce, argmax, dx, ldx,
-                              s);
+    launch_pool_grad<int32_t>(dy, G, (int)F, graph_index, Nb, goff, reduce, argmax, dx, ldx, s);
   TFG_LAUNCHED("pool_grad");
   return TFG_OK;
 }
@@ -272,20 +306,12 @@ int launch_segment_pool_backward(const float* dy, int64_t G, int64_t F, const vo
 int launch_segment_pool(const float* x, int64_t Nb, int64_t F, int64_t ldx, const void* graph_index,
                         int index_type, int64_t G, int reduce, float* out, int32_t* argmax,
                         int* goff, int* err, hipStream_t s) {
-  zero_ints<<<1, 64, 0, s>>>(err, 1);
+  if (err != nullptr) zero_ints<<<1, 64, 0, s>>>(err, 1);
   if (G == 0 || F == 0) return TFG_OK;
-  const unsigned nb = (unsigned)((Nb + 1 + kBlock - 1) / kBlock);
-  if (index_type == TFG_I64)
-    segment_bounds<int64_t><<<nb, kBlock, 0, s>>>(static_cast<const int64_t*>(graph_index), Nb, G,
-                                                   goff, err);
-  else
-    segment_bounds<int32_t><<<nb, kBlock, 0, s>>>(static_cast<const int32_t*>(graph_index), Nb, G,
-                                                   goff, err);
-  TFG_LAUNCHED("segment_bounds");
-  auto fits = [&](int v) {
-    return F % v == 0 && ldx % v == 0 && reinterpret_cast<uintptr_t>(x) % (4 * v) == 0;
-  };
-  const int vec = fits(4) ? 4 : fits(2) ? 2 : 1;
+  if (int rc = launch_segment_bounds(graph_index, index_type, Nb, G, goff, err, s)) return rc;
+  // (maxima of odd widths one column per lane: 30,000 graphs of 63 columns 53 us, with
+  // four 61; sums 50 and 46)
+  const int vec = F >= 4 && !(reduce == TFG_MAX && F % 2 != 0) ? 4 : 1;
   int lanes = (int)std::min<int64_t>((F + vec - 1) / vec, kWave);
   int p2 = 1;
   while (p2 < lanes) p2 <<= 1;
