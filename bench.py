@@ -440,7 +440,7 @@ def run_suite(args):
     _row("backward dw (per-edge dot products)", wl, ms, Ep,
          Ep * (8 + 4 * F) + N * 4 * F + 4 * (N + 1),
          compulsory=Ep * 8 + 2 * N * 4 * F + 4 * (N + 1) + 16 * items(info_f),
-         gathered=Ep * 4 * F, ceiling=ceiling, kernel="edge_grad_rows",
+         gathered=Ep * 4 * F, ceiling=ceiling, kernel="edge_grad_slots",
          cpu_baseline=cpu.get("bw"))
     K = 3
     ms = _timed(torch, lambda: tfg.tfg_propagate(g, x, K, alpha=0.1, h=x,
@@ -497,7 +497,7 @@ def run_suite(args):
                 ei3_np, n3, T), E3, "GE/s", "the whole attention graph")
     _row("fused attention aggregation", wl3, ms_f, E3,
          E3 * (4 + 4 * H + 4 * Fh) + n3 * (4 * Fh + 8 * H) + n3 * (4 * H + 4 * Fh + 4),
-         kernel="node_projections_vec + gat_short + gat_items + gat_merge",
+         kernel="node_projections_vec + gat_slots + gat_merge",
          unfused_chain_ms=round(ms_c, 4), speedup_vs_unfused=round(ms_c / ms_f, 3),
          unfused_chain_graph_order_ms=round(ms_cg, 4),
          unfused_chain_graph_order_hip_graph_ms=round(ms_cg_replay, 4),
@@ -527,7 +527,7 @@ def run_suite(args):
         del qh, kh, vh
     # per edge: source id, the key and value rows; per node: q row, output row
     _row("fused Transformer-style attention (scaled dot product)", wl3, ms_f, E3,
-         E3 * (4 + 8 * Fh) + n3 * (8 * Fh + 4), kernel="gat_short + gat_items (dot) + gat_merge",
+         E3 * (4 + 8 * Fh) + n3 * (8 * Fh + 4), kernel="gat_slots (dot) + gat_merge",
          unfused_chain_ms=round(ms_c, 4), speedup_vs_unfused=round(ms_c / ms_f, 3),
          unfused_chain_graph_order_ms=round(ms_cg, 4),
          cpu_baseline=cpu.get("dot"))
@@ -540,14 +540,14 @@ def run_suite(args):
         cpu["sm"] = _oracle(lambda: oracle.segment_softmax(s_h, ei3_np[1], n3), E3, "GE/s",
                             "the whole attention graph")
     _row("segment softmax", wl3, ms, E3, E3 * (4 + 8 * H) + 4 * (n3 + 1),
-         kernel="softmax_items + softmax_split",
+         kernel="softmax_items + softmax_chunks",
          cpu_baseline=cpu.get("sm"))
     # scores and alpha in the graph order: no permutation, one run per row
     s_g = tfg.tfg_gat_graph_scores(g3, h, a_s, a_d, c["slope"], order="csr")
     ms = _timed(torch, lambda: tfg.tfg_segment_softmax_graph(g3, s_g, order="csr", out=ag_out,
                                                              ws=ag_ws), reps)
     _row("segment softmax, scores and alpha in graph order", wl3, ms, E3,
-         E3 * 8 * H + 4 * (n3 + 1), kernel="softmax_items + softmax_split (no permutation)",
+         E3 * 8 * H + 4 * (n3 + 1), kernel="softmax_items + softmax_chunks (no permutation)",
          cpu_baseline=cpu.get("sm"))
     alpha = tfg.tfg_segment_softmax(s, ei3[1], n3, graph=g3)
     dal = torch.randn_like(alpha)
@@ -558,14 +558,14 @@ def run_suite(args):
     ms = _timed(torch, lambda: tfg.tfg_segment_softmax_backward(alpha, dal, ei3[1], n3, graph=g3),
                 reps)
     _row("segment softmax backward", wl3, ms, E3, E3 * (4 + 12 * H) + 4 * (n3 + 1),
-         kernel="softmax_grad_items + softmax_grad_split",
+         kernel="softmax_grad_items + softmax_grad_chunks",
          cpu_baseline=cpu.get("smb"))
     a_g = tfg.tfg_segment_softmax_graph(g3, s_g, order="csr")
     dal_g = torch.randn_like(a_g)
     ms = _timed(torch, lambda: tfg.tfg_segment_softmax_graph_backward(g3, a_g, dal_g, order="csr"),
                 reps)
     _row("segment softmax backward, in graph order", wl3, ms, E3, E3 * 12 * H + 4 * (n3 + 1),
-         kernel="softmax_grad_items + softmax_grad_split (no permutation)",
+         kernel="softmax_grad_items + softmax_grad_chunks (no permutation)",
          cpu_baseline=cpu.get("smb"))
     del g3, ei3, h, s, alpha, dal, s_g, a_g, dal_g, sg_out, ag_out
     torch.cuda.empty_cache()
