@@ -183,30 +183,6 @@ int64_t gat_partials(const Graph& g, int64_t F, bool dot) {
   return gat_part_plan(g, F, dot) ? g.n_pexec : g.n_heavy;
 }
 
-// Four columns per lane where a head has them. The lanes of a head are rounded
-// up to a multiple of 4 or 2 (more of them then share a score) where that
-// leaves the slot as it is.
-GatShape gat_shape(int H, int D) {
-  GatShape t;
-  t.vec = D >= 4 ? 4 : D == 2 ? 2 : 1;
-  t.G = (D + t.vec - 1) / t.vec;
-  auto lanes = [&](int G) {
-    int n = 4;
-    while (n < std::min(H * G, kWave)) n <<= 1;
-    return n;
-  };
-  t.lps = lanes(t.G);
-  if (t.vec == 4 && t.G > 1)
-    for (int r : {4, 2}) {
-      const int G = (t.G + r - 1) / r * r;
-      if (lanes(G) == t.lps && (H * G <= kWave || G == t.G)) {
-        t.G = G;
-        break;
-      }
-    }
-  return t;
-}
-
 template <bool DOT>
 int run_attention(const Graph& g, int H, int D, const Scores& S, const float* h, float* out,
                   float* alpha_out, void* ws, hipStream_t s) {
@@ -223,7 +199,7 @@ int run_attention(const Graph& g, int H, int D, const Scores& S, const float* h,
   O.pacc = reinterpret_cast<float*>(base + W.pacc);
   O.pm = reinterpret_cast<float*>(base + W.pm);
   O.pd = reinterpret_cast<double*>(base + W.pd);
-  const GatShape t = gat_shape(H, D);
+  const GatShape t = gat_shape(H, D, DOT);
   SlotLists L{};
   int waves;
   slot_lists(g, part_plan ? g.pexec : g.heavy, part_plan ? g.n_pexec : g.n_heavy, part_plan, t.lps,

@@ -26,6 +26,7 @@
 // average: 100 + 84 (a kernel for the short rows) + 35 -> 127 + 10 us.
 #pragma once
 
+#include "gat_shape.h"
 #include "slots.h"
 #include "softmax_stats.h"
 
@@ -53,11 +54,6 @@ struct GatOut {
   float* pacc;  // partial triples, by slot
   float* pm;
   double* pd;
-};
-
-// Columns per lane, lanes per head, lanes per slot.
-struct GatShape {
-  int vec, G, lps;
 };
 
 // One launch over the lists (waves[] filled); the dot product in gat_dot.hip.

@@ -112,7 +112,8 @@ def test_max_gradient(tfg, orc, monkeypatch, F, plan):
 
 
 @pytest.mark.parametrize("plan", ["0", "1"])
-@pytest.mark.parametrize("H,D", [(1, 1), (1, 4), (2, 8), (8, 8), (4, 32), (8, 16), (2, 64), (5, 24),
+@pytest.mark.parametrize("H,D", [(1, 1), (1, 2), (1, 4), (1, 8), (1, 16), (1, 32), (1, 64), (2, 2),
+                                 (2, 8), (3, 8), (8, 8), (4, 32), (8, 16), (2, 64), (5, 24),
                                  (3, 6), (3, 7), (16, 32)])
 def test_attention_rows(tfg, orc, monkeypatch, H, D, plan):
     """Both fused layers over rows of every length, whole or by source part, with the
