@@ -40,32 +40,6 @@ enum { kGradSum = 0, kGradMean = 1, kGradMax = 2 };
 // 512-byte rows at 6 TB/s. 23M edges of 64 columns by source part: 0.68 -> 0.47
 // ms. Rows wider than 256 columns had one thread per edge (2M edges of 300
 // columns: 2.50 -> 0.32 ms).
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float v) {
-  return v + __int_as_float(
-                 __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-
-// Each t[u] summed over the aligned groups of G lanes (a power of two).
-template <int U>
-__device__ __forceinline__ void lanes_sum(float (&t)[U], int G) {
-  if (G >= 2)
-#pragma unroll
-    for (int u = 0; u < U; ++u) t[u] = dpp_add<0xB1>(t[u]);  // quad lanes ^ 1
-  if (G >= 4)
-#pragma unroll
-    for (int u = 0; u < U; ++u) t[u] = dpp_add<0x4E>(t[u]);  // quad lanes ^ 2
-  if (G >= 8)
-#pragma unroll
-    for (int u = 0; u < U; ++u) t[u] = dpp_add<0x141>(t[u]);  // row_half_mirror
-  if (G >= 16)
-#pragma unroll
-    for (int u = 0; u < U; ++u) t[u] = dpp_add<0x140>(t[u]);  // row_mirror
-  for (int o = 16; o < G; o <<= 1)
-#pragma unroll
-    for (int u = 0; u < U; ++u) t[u] += __shfl_xor(t[u], o);
-}
-
 template <int V, int LPS, int MODE, bool NARROW>
 __global__ __launch_bounds__(kItemBlock) void edge_grad_slots(
     SlotLists L, const int* __restrict__ rowptr, const int* __restrict__ col,

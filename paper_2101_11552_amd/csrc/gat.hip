@@ -74,9 +74,11 @@ __global__ __launch_bounds__(kItemBlock) void gat_merge(const SplitRow* __restri
       m = t > m ? t : m;
     }
     double d = 0.0;
-    float acc[V];
+    float part[kMergeU][V];  // a chain per place, added up in pairs
 #pragma unroll
-    for (int v = 0; v < V; ++v) acc[v] = 0.0f;
+    for (int u = 0; u < kMergeU; ++u)
+#pragma unroll
+      for (int v = 0; v < V; ++v) part[u][v] = 0.0f;
     for (int j0 = sub; j0 < nch; j0 += kMergeU * share) {
       float t[kMergeU], a[kMergeU][V];
       double e[kMergeU];
@@ -93,9 +95,13 @@ __global__ __launch_bounds__(kItemBlock) void gat_merge(const SplitRow* __restri
           const float w = t[u] == m ? 1.0f : expf(t[u] - m);
           d += e[u] * (double)w;
 #pragma unroll
-          for (int v = 0; v < V; ++v) acc[v] = __builtin_fmaf(w, a[u][v], acc[v]);
+          for (int v = 0; v < V; ++v) part[u][v] = __builtin_fmaf(w, a[u][v], part[u][v]);
         }
     }
+    float acc[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+      acc[v] = (part[0][v] + part[1][v]) + (part[2][v] + part[3][v]);
     for (int o = lps; o < lps * share; o <<= 1) {
       d += __shfl_xor(d, o);
 #pragma unroll

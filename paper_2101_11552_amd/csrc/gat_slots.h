@@ -77,26 +77,11 @@ __device__ __forceinline__ float group_bcast(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xF, 0xF, false));
 }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-
 // Maximum over the GX lanes of a group.
 template <int GX>
 __device__ __forceinline__ float group_max(float v) {
   if constexpr (GX >= 2) { const float o = dpp<0xB1>(v); v = o > v ? o : v; }  // quad lanes ^ 1
   if constexpr (GX >= 4) { const float o = dpp<0x4E>(v); v = o > v ? o : v; }  // quad lanes ^ 2
-  return v;
-}
-
-// Sum over the G lanes (a power of two, aligned) of a head; every lane gets it.
-__device__ __forceinline__ float head_sum(float v, int G) {
-  if (G >= 2) v += dpp<0xB1>(v);
-  if (G >= 4) v += dpp<0x4E>(v);
-  if (G >= 8) v += dpp<0x141>(v);   // row_half_mirror: the other quad of the eight
-  if (G >= 16) v += dpp<0x140>(v);  // row_mirror: the other half row
-  for (int o = 16; o < G; o <<= 1) v += __shfl_xor(v, o);
   return v;
 }
 
@@ -123,7 +108,6 @@ __global__ __launch_bounds__(kItemBlock) void gat_slots(SlotLists L, const int* 
   constexpr int BW = kIds / NR;
   constexpr int U = 4;  // rows in flight per slot
   constexpr int OWN = (DOT ? U : kIds) / GX;  // scores per lane and round (dot product: group)
-  constexpr int CH = 2;           // accumulator chains
   int wid = blockIdx.x;
   int li = 0;
 #pragma unroll
@@ -167,15 +151,14 @@ __global__ __launch_bounds__(kItemBlock) void gat_slots(SlotLists L, const int* 
     }
     float m = kNegInf;
     double den = 0.0;  // this lane's share of the scores
-    float acc[CH][V];
+    float tot[V];  // (sums in the order of slots.h, the rounds in one chain)
 #pragma unroll
-    for (int c = 0; c < CH; ++c)
-#pragma unroll
-      for (int v = 0; v < V; ++v) acc[c][v] = 0.0f;
+    for (int v = 0; v < V; ++v) tot[v] = 0.0f;
 
     // Brings the sums to the maximum of m and the scores sc, and replaces the
-    // scores by their exponentials.
-    auto weigh = [&](float (&sc)[OWN]) {
+    // scores by their exponentials. (The additive score's comes before a round's
+    // first sums: its chains are still zero.)
+    auto weigh = [&](float (&sc)[OWN], float (&half)[2][V]) {
       float top = sc[0];
 #pragma unroll
       for (int k = 1; k < OWN; ++k) top = sc[k] > top ? sc[k] : top;
@@ -186,9 +169,13 @@ __global__ __launch_bounds__(kItemBlock) void gat_slots(SlotLists L, const int* 
         const float x = m == mn ? 1.0f : expf(m - base);
         den *= (double)x;
 #pragma unroll
-        for (int c = 0; c < CH; ++c)
-#pragma unroll
-          for (int v = 0; v < V; ++v) acc[c][v] *= x;
+        for (int v = 0; v < V; ++v) {
+          tot[v] *= x;
+          if constexpr (DOT) {
+            half[0][v] *= x;
+            half[1][v] *= x;
+          }
+        }
         m = mn;
       }
 #pragma unroll
@@ -229,6 +216,9 @@ __global__ __launch_bounds__(kItemBlock) void gat_slots(SlotLists L, const int* 
           p[k] = in ? leaky(z + adt, S.slope) : kNegInf;
         }
       }
+      float half[2][V];
+#pragma unroll
+      for (int v = 0; v < V; ++v) half[0][v] = half[1][v] = 0.0f;
       each<kIds / U>([&](auto g_) {
         constexpr int GR = decltype(g_)::value;
         if (r0 + GR * U * split < nmax) {  // uniform
@@ -247,37 +237,48 @@ __global__ __launch_bounds__(kItemBlock) void gat_slots(SlotLists L, const int* 
             });
             each<U>([&](auto u_) {
               constexpr int u = decltype(u_)::value, I = GR * U + u;
-              float t = 0.0f;
+              float part[1] = {0.0f};
 #pragma unroll
-              for (int v = 0; v < V; ++v) t = __builtin_fmaf(qv[v], kv[u][v], t);
-              t = S.scale * head_sum(t, G);
+              for (int v = 0; v < V; ++v) part[0] = __builtin_fmaf(qv[v], kv[u][v], part[0]);
+              lanes_sum(part, G);
+              float t = S.scale * part[0];
               t = j0 + I * split < n ? t : kNegInf;
               // lane g of the group keeps edge g
               if (u % GX == 0) p[u / GX] = t;
               else p[u / GX] = gi == u % GX ? t : p[u / GX];
             });
-            weigh(p);
+            weigh(p, half);
           } else {
             each<U>([&](auto u_) {
               constexpr int u = decltype(u_)::value, I = GR * U + u;
               load_row<V>(row_at<NARROW, float>(hb, slot_bcast<I, LPS>(id), row_bytes, lane_off),
                           xv[u]);
             });
-            if constexpr (GR == 0) weigh(p);
+            if constexpr (GR == 0) weigh(p, half);
           }
+          float four[V];
+          auto& c = [&]() -> float(&)[V] {
+            if constexpr (GR % 2 == 0) return half[GR / 2];
+            else return four;
+          }();
+          if constexpr (GR % 2 == 1)
+#pragma unroll
+            for (int v = 0; v < V; ++v) four[v] = 0.0f;
           each<U>([&](auto u_) {
             constexpr int u = decltype(u_)::value, I = GR * U + u;
             const float w = group_bcast<u, GX>(p[(DOT ? u : I) / GX]);
             if (j0 + I * split < n)
 #pragma unroll
-              for (int v = 0; v < V; ++v)
-                acc[u % CH][v] = __builtin_fmaf(w, xv[u][v], acc[u % CH][v]);
+              for (int v = 0; v < V; ++v) c[v] = __builtin_fmaf(w, xv[u][v], c[v]);
           });
+          if constexpr (GR % 2 == 1)
+#pragma unroll
+            for (int v = 0; v < V; ++v) half[GR / 2][v] += four[v];
         }
       });
-    }
 #pragma unroll
-    for (int v = 0; v < V; ++v) acc[0][v] += acc[1][v];
+      for (int v = 0; v < V; ++v) tot[v] += half[0][v] + half[1][v];
+    }
 #pragma unroll
     for (int o = 1; o < GX; o <<= 1) den += __shfl_xor(den, o);
     // the slots of one item, pairwise
@@ -286,23 +287,23 @@ __global__ __launch_bounds__(kItemBlock) void gat_slots(SlotLists L, const int* 
       if (split > i) {  // uniform
         float a2[V];
 #pragma unroll
-        for (int v = 0; v < V; ++v) a2[v] = __shfl_xor(acc[0][v], LPS * i);
+        for (int v = 0; v < V; ++v) a2[v] = __shfl_xor(tot[v], LPS * i);
         const float m2 = __shfl_xor(m, LPS * i);
         const double d2 = __shfl_xor(den, LPS * i);
-        triple_merge<V>(m, den, acc[0], m2, d2, a2);
+        triple_merge<V>(m, den, tot, m2, d2, a2);
       }
     if (!have || !fok || sub != 0) continue;
     if (it.slot < 0) {
       float o[V];
 #pragma unroll
-      for (int v = 0; v < V; ++v) o[v] = n > 0 ? (float)((double)acc[0][v] / den) : 0.0f;
+      for (int v = 0; v < V; ++v) o[v] = n > 0 ? (float)((double)tot[v] / den) : 0.0f;
       store_row<V>(O.out + (int64_t)it.row * F + f, o);
       if (O.rm != nullptr && g == 0) {
         O.rm[(int64_t)it.row * H + head] = m;
         O.rd[(int64_t)it.row * H + head] = den;
       }
     } else {
-      store_row<V>(O.pacc + (int64_t)it.slot * F + f, acc[0]);
+      store_row<V>(O.pacc + (int64_t)it.slot * F + f, tot);
       if (g == 0) {
         O.pm[(int64_t)it.slot * H + head] = m;
         O.pd[(int64_t)it.slot * H + head] = den;

@@ -43,6 +43,34 @@ __device__ __forceinline__ int slot_bcast(const int (&r)[id_regs<LPS>()]) {
     return __builtin_amdgcn_update_dpp(0, r[I / 4], (I % 4) * 0x55, 0xF, 0xF, false);
 }
 
+// v moved between lanes of a row of 16 by a DPP pattern.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
+// Each t[u] summed over the aligned groups of G lanes (a power of two); every lane
+// gets the sum.
+template <int U>
+__device__ __forceinline__ void lanes_sum(float (&t)[U], int G) {
+  for (int o = G / 2; o >= 16; o >>= 1)
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] += __shfl_xor(t[u], o);
+  if (G >= 16)
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] += dpp<0x140>(t[u]);  // row_mirror: the other half row
+  if (G >= 8)
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] += dpp<0x141>(t[u]);  // row_half_mirror: the other quad
+  if (G >= 4)
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] += dpp<0x4E>(t[u]);  // quad lanes ^ 2
+  if (G >= 2)
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] += dpp<0xB1>(t[u]);  // quad lanes ^ 1
+}
+
 // A lane's place in the row whose id (NARROW: whose byte offset) is c.
 template <bool NARROW, typename T>
 __device__ __forceinline__ const T* row_at(const char* base, int c, int64_t row_bytes,
@@ -77,7 +105,6 @@ __global__ __launch_bounds__(kItemBlock) void spmm_slots(
   constexpr int BW = kIds / NR;  // edges per register
   constexpr bool MAX = KIND == kMax || KIND == kMaxTies, MASK = KIND == kMasked;
   constexpr int U = MASK || WM == kHeads ? 4 : 8;  // gathers in flight per slot
-  constexpr int CH = MAX ? 1 : 4;                  // accumulator chains
   int wid = blockIdx.x;
   int li = 0;
 #pragma unroll
@@ -114,14 +141,17 @@ __global__ __launch_bounds__(kItemBlock) void spmm_slots(
     const int head = WM == kHeads ? f / per_head : 0;
     const char* wb = reinterpret_cast<const char*>(w);
     const unsigned head_off = 4u * (unsigned)head;
-    float acc[CH][V];
+    // Sums: chains of four edges, added up in pairs to the sum of a round, the
+    // rounds in turn in two chains. (Four chains that ran through the whole item
+    // were further from the sums in 64 bits: 1.17e-7 against 1.07e-7 over three
+    // layers of rows of 5, 6.9e-8 against 6.6e-8 in a max gradient of 100-edge rows.)
+    float tot[V], odd[V];  // (maxima: tot alone)
     int arg[V];
 #pragma unroll
-    for (int c = 0; c < CH; ++c)
-#pragma unroll
-      for (int v = 0; v < V; ++v) acc[c][v] = 0.0f;
-#pragma unroll
-    for (int v = 0; v < V; ++v) arg[v] = -1;
+    for (int v = 0; v < V; ++v) {
+      tot[v] = odd[v] = 0.0f;
+      arg[v] = -1;
+    }
 
     // rounds of kIds edges per slot: place I of a round is edge j0 + I * split,
     // the `split` slots of an item taking neighbouring edges
@@ -144,6 +174,9 @@ __global__ __launch_bounds__(kItemBlock) void spmm_slots(
           if constexpr (NARROW) wt[r] = wt[r] * 4 * H;
         }
       }
+      float half[2][V];  // the sums of the round's first and last eight places
+#pragma unroll
+      for (int v = 0; v < V; ++v) half[0][v] = half[1][v] = 0.0f;
       each<kIds / U>([&](auto g_) {
         constexpr int G = decltype(g_)::value;
         if (r0 + G * U * split < nmax) {  // uniform
@@ -181,6 +214,9 @@ __global__ __launch_bounds__(kItemBlock) void spmm_slots(
               }
             });
           }
+          float four[V];  // a second chain: every other four places
+#pragma unroll
+          for (int v = 0; v < V; ++v) four[v] = 0.0f;
           each<U>([&](auto u_) {
             constexpr int u = decltype(u_)::value, I = G * U + u;
             float we = 1.0f;
@@ -192,43 +228,51 @@ __global__ __launch_bounds__(kItemBlock) void spmm_slots(
 #pragma unroll
               for (int v = 0; v < V; ++v) {
                 const float m = WM == kNone ? xv[u][v] : we * xv[u][v];
-                bool take = m > acc[0][v];
-                if (KIND == kMaxTies) take |= (m == acc[0][v]) & (e < arg[v]);
+                bool take = m > tot[v];
+                if (KIND == kMaxTies) take |= (m == tot[v]) & (e < arg[v]);
                 if (I == 0) take |= r0 == 0;  // a slot's first edge always
-                acc[0][v] = take ? m : acc[0][v];
+                tot[v] = take ? m : tot[v];
                 arg[v] = take ? e : arg[v];
               }
             } else {
+              auto& c = [&]() -> float(&)[V] {
+                if constexpr (I / 4 % 2 == 0) return half[I / 8];
+                else return four;
+              }();
               if (j0 + I * split < n)
 #pragma unroll
                 for (int v = 0; v < V; ++v)
-                  acc[u % CH][v] = WM == kNone ? acc[u % CH][v] + xv[u][v]
-                                               : __builtin_fmaf(we, xv[u][v], acc[u % CH][v]);
+                  c[v] = WM == kNone ? c[v] + xv[u][v] : __builtin_fmaf(we, xv[u][v], c[v]);
             }
           });
+          if constexpr (!MAX && (U == 8 || G % 2 == 1))
+#pragma unroll
+            for (int v = 0; v < V; ++v) half[G * U / 8][v] += four[v];
         }
       });
+      if constexpr (!MAX)
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          const float t = odd[v] + (half[0][v] + half[1][v]);
+          odd[v] = tot[v];
+          tot[v] = t;
+        }
     }
-    if constexpr (!MAX) {
+    if constexpr (!MAX)
 #pragma unroll
-      for (int step = 1; step < CH; step <<= 1)
-#pragma unroll
-        for (int c = 0; c + step < CH; c += 2 * step)
-#pragma unroll
-          for (int v = 0; v < V; ++v) acc[c][v] += acc[c + step][v];
-    }
+      for (int v = 0; v < V; ++v) tot[v] += odd[v];
     // the slots of one item, pairwise
 #pragma unroll
     for (int i = 1; i < SLOTS; i <<= 1)
       if (split > i) {  // uniform
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-          const float ov = __shfl_xor(acc[0][v], LPS * i);
+          const float ov = __shfl_xor(tot[v], LPS * i);
           if constexpr (MAX) {
             const int oa = __shfl_xor(arg[v], LPS * i);
-            max_combine(acc[0][v], arg[v], ov, oa);
+            max_combine(tot[v], arg[v], ov, oa);
           } else {
-            acc[0][v] += ov;
+            tot[v] += ov;
           }
         }
       }
@@ -237,29 +281,21 @@ __global__ __launch_bounds__(kItemBlock) void spmm_slots(
       if constexpr (MAX) {
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-          acc[0][v] = n == 0 ? 0.0f : acc[0][v];
+          tot[v] = n == 0 ? 0.0f : tot[v];
           arg[v] = n == 0 ? -1 : arg[v];
         }
       } else {
         if (mean && n > 0) {
           const float cnt = (float)n;
 #pragma unroll
-          for (int v = 0; v < V; ++v) acc[0][v] = acc[0][v] / cnt;
+          for (int v = 0; v < V; ++v) tot[v] = tot[v] / cnt;
         }
-        if (ep.h != nullptr) {
-          float t[V];
-          load_row<V>(ep.h + (int64_t)it.row * ep.ldh + f, t);
-#pragma unroll
-          for (int v = 0; v < V; ++v) acc[0][v] = ep.scale * acc[0][v] + ep.alpha * t[v];
-        } else if (ep.scale != 1.0f) {
-#pragma unroll
-          for (int v = 0; v < V; ++v) acc[0][v] = ep.scale * acc[0][v];
-        }
+        apply_epilogue<V>(ep, it.row, f, tot);
       }
-      store_row<V>(out + (int64_t)it.row * F + f, acc[0]);
+      store_row<V>(out + (int64_t)it.row * F + f, tot);
       if (MAX && argout != nullptr) store_irow<V>(argout + (int64_t)it.row * F + f, arg);
     } else {
-      store_row<V>(part + (int64_t)it.slot * F + f, acc[0]);
+      store_row<V>(part + (int64_t)it.slot * F + f, tot);
       if (MAX) store_irow<V>(part_arg + (int64_t)it.slot * F + f, arg);
     }
   }

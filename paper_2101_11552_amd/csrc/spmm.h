@@ -103,7 +103,7 @@ __device__ __forceinline__ void apply_epilogue(const Epilogue& ep, int row, int 
     float t[V];
     load_row<V>(ep.h + (int64_t)row * ep.ldh + f, t);
 #pragma unroll
-    for (int i = 0; i < V; ++i) v[i] = ep.scale * v[i] + ep.alpha * t[i];
+    for (int i = 0; i < V; ++i) v[i] = __builtin_fmaf(ep.alpha, t[i], ep.scale * v[i]);
   } else if (ep.scale != 1.0f) {
 #pragma unroll
     for (int i = 0; i < V; ++i) v[i] = ep.scale * v[i];
