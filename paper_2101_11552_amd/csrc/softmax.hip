@@ -219,37 +219,37 @@ __device__ __forceinline__ float regs_max(const float (&v)[NST][K], int i, int H
 
 // The registers' exp(v - m) (a missing edge, v = -inf, gives 0; with no maximum
 // yet every score is -inf or NaN, and stays 0 or NaN), and their sum over all slots
-// of the head: 8 terms at a time in float, then in double.
+// of the head: a lane's terms (at most 8) in float, or (WIDE) in a pair of floats.
 __device__ __forceinline__ float exp_base(float m) { return m == -__builtin_huge_valf() ? 0.0f : m; }
-template <int NST, int K>
+template <bool WIDE, int NST, int K>
 __device__ __forceinline__ double regs_exp_sum(float (&v)[NST][K], int i, float m, int HP,
                                                int lanes) {
   const float base = exp_base(m);
-  double sum = 0.0;
+  float sum = 0.0f, low = 0.0f;  // low: what the float sum has lost
 #pragma unroll
-  for (int u0 = 0; u0 < NST; u0 += 8) {
-    float d = 0.0f;
-#pragma unroll
-    for (int u = u0; u < NST && u < u0 + 8; ++u) {
-      v[u][i] = expf(v[u][i] - base);
-      d += v[u][i];
+  for (int u = 0; u < NST; ++u) {
+    v[u][i] = expf(v[u][i] - base);
+    const float t = sum + v[u][i];
+    if constexpr (WIDE) {  // (exact: Knuth's two-sum)
+      const float b = t - sum;
+      low += (sum - (t - b)) + (v[u][i] - b);
     }
-    sum += (double)d;
+    sum = t;
   }
-  return slots_sum(sum, HP, lanes);
+  return slots_sum(WIDE ? (double)sum + (double)low : (double)sum, HP, lanes);
 }
 
 // alpha = x * r for the registers' edges (x = exp(s - m), r = 1 / sum).
-template <int NST, int K>
+template <typename R, int NST, int K>
 __device__ __forceinline__ void regs_write(float (&x)[NST][K], const int (&e)[NST],
-                                           const float (&r)[K], int kb, int slot, int SL, int H,
+                                           const R (&r)[K], int kb, int slot, int SL, int H,
                                            int h, bool act, float* __restrict__ out,
                                            float* __restrict__ out_csr) {
 #pragma unroll
   for (int u = 0; u < NST; ++u)
     if (act && e[u] >= 0) {
 #pragma unroll
-      for (int i = 0; i < K; ++i) x[u][i] *= r[i];
+      for (int i = 0; i < K; ++i) x[u][i] = (float)((R)x[u][i] * r[i]);
       store_k<K>(out + ((int64_t)e[u] * H + h) * K, x[u]);
       if (out_csr) store_k<K>(out_csr + ((int64_t)(kb + slot + u * SL) * H + h) * K, x[u]);
     }
@@ -309,8 +309,10 @@ __device__ __forceinline__ void sweep_write(const int* __restrict__ perm,
 }
 
 // One item per group from the registers: a whole row (pslot < 0) writes alpha,
-// a chunk of a split row its pair.
-template <int NST, int K>
+// a chunk of a split row its pair. WIDE: the sum and its reciprocal in double, as in
+// the running sweep (in float they cost 3% of alpha's accuracy); short rows, whose
+// sums have few terms, take them in float (4 to 10% of the time at 8 to 16 heads).
+template <int NST, int K, bool WIDE = false>
 __device__ __forceinline__ void item_regs(const int* __restrict__ perm,
                                           const float* __restrict__ s, int H, int HP,
                                           const GroupItem& it, float* __restrict__ out,
@@ -323,17 +325,20 @@ __device__ __forceinline__ void item_regs(const int* __restrict__ perm,
   for (int hb = 0; hb < H; hb += HP) {
     const int h = hb + hh;
     const bool act = h < H;
-    float v[NST][K], m[K], r[K];
+    float v[NST][K], m[K];
     double d[K];
     load_scores<NST, K>(s, H, h, act, e, v);
 #pragma unroll
     for (int i = 0; i < K; ++i) {
       m[i] = regs_max<NST, K>(v, i, HP, it.lanes);
-      d[i] = regs_exp_sum<NST, K>(v, i, m[i], HP, it.lanes);
-      r[i] = (float)(1.0 / d[i]);
+      d[i] = regs_exp_sum<WIDE, NST, K>(v, i, m[i], HP, it.lanes);
     }
     if (it.pslot < 0) {
-      regs_write<NST, K>(v, e, r, it.kb, slot, SL, H, h, act, out, out_csr);
+      using RT = typename std::conditional<WIDE, double, float>::type;
+      RT r[K];
+#pragma unroll
+      for (int i = 0; i < K; ++i) r[i] = (RT)(1.0 / d[i]);
+      regs_write<RT, NST, K>(v, e, r, it.kb, slot, SL, H, h, act, out, out_csr);
     } else if (slot == 0 && act) {
 #pragma unroll
       for (int i = 0; i < K; ++i) {
@@ -357,6 +362,8 @@ __global__ __launch_bounds__(kItemBlock) void softmax_items(
     item_regs<1, K>(perm, s, H, HP, it, out, out_csr, pm, pd);
   } else if (nst <= 2) {
     item_regs<2, K>(perm, s, H, HP, it, out, out_csr, pm, pd);
+  } else if (nst <= 4 && K == 4 && it.lanes == kWave) {  // more than 512 values
+    item_regs<4, K, true>(perm, s, H, HP, it, out, out_csr, pm, pd);
   } else if (nst <= 4) {
     item_regs<4, K>(perm, s, H, HP, it, out, out_csr, pm, pd);
   } else if (K == 1 && nst <= 8) {
@@ -434,14 +441,15 @@ __device__ __forceinline__ void chunk_write(const int* __restrict__ perm,
   for (int hb = 0; hb < H; hb += HP) {
     const int h = hb + hh;
     const bool act = h < H;
-    float v[R][K], m[K], inv[K];
+    float v[R][K], m[K];
+    double inv[K];
     if constexpr (NST > 0) load_scores<NST, K>(s, H, h, act, e, v);
     const int64_t p0 = ((int64_t)r.slot0 * H + h) * K;
 #pragma unroll
     for (int i = 0; i < K; ++i) {
       double d;
       row_pair(pm + p0 + i, pd + p0 + i, r.nch, H * K, act, slot, SL, HP, m[i], d);
-      if constexpr (NST > 0) inv[i] = (float)(1.0 / d);
+      if constexpr (NST > 0) inv[i] = 1.0 / d;
       else sweep_write(perm, s, H, h, act, it.kbeg, it.kend, slot, SL, m[i], 1.0 / d, out, out_csr);
     }
     if constexpr (NST > 0) {
@@ -449,7 +457,7 @@ __device__ __forceinline__ void chunk_write(const int* __restrict__ perm,
       for (int u = 0; u < NST; ++u)
 #pragma unroll
         for (int i = 0; i < K; ++i) v[u][i] = expf(v[u][i] - m[i]);
-      regs_write<NST, K>(v, e, inv, it.kbeg, slot, SL, H, h, act, out, out_csr);
+      regs_write<double, NST, K>(v, e, inv, it.kbeg, slot, SL, H, h, act, out, out_csr);
     }
   }
 }

@@ -75,3 +75,22 @@ def test_softmax_rows(tfg, H, hubs, masked):
     want, scale = al * (da - dot[tgt]), al * (np.abs(da) + size[tgt])
     err = np.abs(ds.cpu().numpy() - want[perm]) / np.maximum(scale[perm], 1e-30)
     assert float(err.max()) <= 1e-5
+
+
+def _alpha_error(tfg, n, H):
+    """Relative error (root mean square) of the coefficients of rows of n edges against 64 bits."""
+    rows = max(4, 400_000 // (n * H))
+    r = np.random.default_rng([12, n, H])
+    tgt = np.repeat(np.arange(rows), n)
+    s = r.standard_normal((tgt.size, H)).astype(np.float32)
+    g = tfg.tfg_graph_create(torch.from_numpy(np.stack([tgt, tgt])).cuda(), rows)
+    a = tfg.tfg_segment_softmax_graph(g, torch.from_numpy(s).cuda()).cpu().numpy()
+    ref = _softmax64(s, tgt, rows)
+    return float(np.sqrt(np.mean((a / ref - 1.0) ** 2)))
+
+
+@pytest.mark.parametrize("n", [100, 2200])
+def test_rows_from_registers_are_as_exact_as_swept_ones(tfg, n):
+    """Rows of over 64 edges, whole and in chunks, keep their exponentials in registers at 8 heads
+    and load the scores again at 5: both divide by the sum in double (2% for the sample)."""
+    assert _alpha_error(tfg, n, 8) <= 1.02 * _alpha_error(tfg, n, 5)
