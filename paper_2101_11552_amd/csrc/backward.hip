@@ -140,9 +140,10 @@ __global__ __launch_bounds__(kItemBlock) void edge_grad_slots(
               const int e = MODE == kGradMax ? slot_bcast<I, LPS>(pe) : 0;
 #pragma unroll
               for (int v = 0; v < V; ++v) {
+                // (both sides zero where the edge did not win: x may hold -inf there)
                 const bool use = MODE == kGradMax ? ga[v] == e : true;
-                const float w = use ? gy[v] : 0.0f;
-                t[u] = __builtin_fmaf(w, xv[u][v], t[u]);
+                const float w = use ? gy[v] : 0.0f, xs = use ? xv[u][v] : 0.0f;
+                t[u] = __builtin_fmaf(w, xs, t[u]);
               }
             });
           }

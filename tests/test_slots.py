@@ -175,3 +175,29 @@ def test_edge_gradients(tfg, orc, monkeypatch, H, D, plan):
             want, s = (ref, scale) if order == "coo" else (ref[perm], scale[perm])
             err = np.abs(got - want) / np.maximum(s, 1e-300)
             assert float(np.where(s > 0, err, np.abs(got)).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("plan", ["0", "1"])
+@pytest.mark.parametrize("H,D", [(1, 7), (1, 64), (4, 8)])
+def test_max_weight_gradient_beside_infinities(tfg, monkeypatch, H, D, plan):
+    """Entries of -inf, the usual filler before a maximum, lose and add nothing to the gradient
+    of the weights: the same bits as with finite losers in their place."""
+    monkeypatch.setenv("TFG_PART_PLAN", plan)
+    ei, n = _graph(900 + D, 100, 1)
+    r = np.random.default_rng([12, H, D])
+    x = r.standard_normal((100, H * D)).astype(np.float32)
+    drop = r.random(x.shape) < 0.3
+    drop[ei[0][:: 7]] = False
+    dy = torch.from_numpy(r.standard_normal((n, H * D)).astype(np.float32)).cuda()
+    w = torch.from_numpy(r.uniform(0.5, 1.5, (ei.shape[1], H)).astype(np.float32)).cuda()
+    g = tfg.tfg_graph_create(torch.from_numpy(ei).cuda(), n, N_src=100, src_parts=2)
+    res = []
+    for filler in (-np.inf, -1e4):
+        xd = torch.from_numpy(np.where(drop, np.float32(filler), x)).cuda()
+        y, a = tfg.tfg_aggregate(None, xd, n, "max", edge_weight=w, heads=H, graph=g)
+        a = torch.where(y < -1e3, -1, a)  # rows that hold fillers alone: no winner
+        res.append((a, tfg.tfg_aggregate_backward(g, dy, "max", x=xd, edge_weight=w, heads=H,
+                                                  argmax=a, want_dx=False, want_dw=True)[1]))
+    assert torch.equal(res[0][0], res[1][0])
+    assert torch.equal(res[0][1], res[1][1])
+    assert bool(torch.isfinite(res[0][1]).all())
