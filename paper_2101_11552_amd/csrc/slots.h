@@ -171,7 +171,8 @@ __global__ __launch_bounds__(kItemBlock) void spmm_slots(
         if constexpr (NARROW) id[r] = id[r] * (int)row_bytes;
         if constexpr (WM == kHeads) {  // the edge's row of weights (its byte offset)
           wt[r] = n > 0 ? (w_by_perm ? pe[r] : kbeg + j) : 0;
-          if constexpr (NARROW) wt[r] = wt[r] * 4 * H;
+          // (up to 2^32: an unsigned product, kept in a signed register for the DPP moves)
+          if constexpr (NARROW) wt[r] = (int)((unsigned)wt[r] * 4u * (unsigned)H);
         }
       }
       float half[2][V];  // the sums of the round's first and last eight places

@@ -201,3 +201,24 @@ def test_max_weight_gradient_beside_infinities(tfg, monkeypatch, H, D, plan):
     assert torch.equal(res[0][0], res[1][0])
     assert torch.equal(res[0][1], res[1][1])
     assert bool(torch.isfinite(res[0][1]).all())
+
+
+def test_head_weights_beyond_2_gib(tfg):
+    """Per-head weights whose byte offsets pass 2^31 (they stay below 2^32, the 32-bit path's
+    limit): the last targets, whose weights lie there, against sums in 64 bits."""
+    H, n, deg = 64, 1 << 16, 130
+    E = n * deg  # 8.5M edges, 2.18 GB of weights
+    assert 2**31 < 4 * E * H < 2**32
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    src = torch.randint(0, 1000, (E,), generator=gen, device="cuda", dtype=torch.int32)
+    tgt = torch.arange(n, device="cuda", dtype=torch.int32).repeat_interleave(deg)
+    g = tfg.tfg_graph_create(torch.stack([src, tgt]), n, N_src=1000)
+    x = torch.randn(1000, H, generator=gen, device="cuda")
+    w = torch.rand(E, H, generator=gen, device="cuda")
+    for order in ("csr", "coo"):  # the input is grouped by target: both orders are one
+        y = tfg.tfg_aggregate(None, x, n, edge_weight=w, heads=H, weight_order=order, graph=g)
+        last = slice(E - 50 * deg, E)
+        m = w[last].double() * x[src[last].long()].double()
+        ref = m.view(50, deg, H).sum(1)
+        scale = m.abs().view(50, deg, H).sum(1)
+        assert float(((y[-50:].double() - ref).abs() / scale).max()) <= 1e-5
