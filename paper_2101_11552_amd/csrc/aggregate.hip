@@ -114,8 +114,8 @@ __global__ __launch_bounds__(kItemBlock) void fixup_rows(const SplitRow* __restr
   }
 }
 
-// Sum and mean over the part plan with scalar edge ids: one wavefront per work
-// item, two edge slots of 32 lanes, lane l of a slot holding columns 4 l ..
+// Sum and mean over the part plan (every item writes a partial) with scalar edge
+// ids: one wavefront per work item, two edge slots of 32 lanes, lane l of a slot holding columns 4 l ..
 // 4 l + 3 of a 128-column row. The item's edge ids and weights come in with one
 // coalesced load per 64 edges and are read out edge by edge into scalar
 // registers (readlane); the scalar unit forms each row's 32-bit byte offset
@@ -132,16 +132,14 @@ template <bool NARROW>
 __global__ __launch_bounds__(kRowBlock) void spmm_wide(
     const WorkItem* __restrict__ items, int n_items, const int* __restrict__ col,
     const int* __restrict__ perm, const float* __restrict__ w, int w_by_perm,
-    const float* __restrict__ x, int64_t ldx, int F, int mean, float* __restrict__ out,
-    float* __restrict__ part, Epilogue ep) {
+    const float* __restrict__ x, int64_t ldx, int F, float* __restrict__ part) {
   constexpr int V = 4, SL = 2, U = kWideU, LPS = kWave / SL;
   const int wid = uniform(blockIdx.x * (kRowBlock / kWave) + threadIdx.x / kWave);
   if (wid >= n_items) return;
   const int lane = lane_id();
   const int slot = lane / LPS, sl = lane % LPS;
   const WorkItem* itp = items + wid;
-  const int row = uniform(itp->row), kbeg = uniform(itp->kbeg), kend = uniform(itp->kend);
-  const int pslot = uniform(itp->slot);
+  const int kbeg = uniform(itp->kbeg), kend = uniform(itp->kend), pslot = uniform(itp->slot);
   const char* xb = reinterpret_cast<const char*>(x);
   const int64_t row_bytes = ldx * (int64_t)sizeof(float);
   const int f = sl * V;
@@ -201,30 +199,22 @@ __global__ __launch_bounds__(kRowBlock) void spmm_wide(
 #pragma unroll
   for (int v = 0; v < V; ++v) acc[0][v] += __shfl_xor(acc[0][v], LPS);
   if (slot != 0) return;
-  if (pslot < 0) {
-    if (mean && kend > kbeg) {
-      const float cnt = (float)(kend - kbeg);
-#pragma unroll
-      for (int v = 0; v < V; ++v) acc[0][v] = acc[0][v] / cnt;
-    }
-    apply_epilogue<V>(ep, row, f, acc[0]);
-    store_row<V>(out + (int64_t)row * F + f, acc[0]);
-  } else {
-    // partial rows are read back once, by the fix-up, long after: streamed
-    // past the L2, which they would otherwise share with the gathered rows
-    store_row<V>(part + (int64_t)pslot * F + f, acc[0]);
-  }
+  // partial rows are read back once, by the fix-up, long after: streamed
+  // past the L2, which they would otherwise share with the gathered rows
+  store_row<V>(part + (int64_t)pslot * F + f, acc[0]);
 }
 
-// Whether a sum or mean over the part plan goes through spmm_wide: rows of
-// 128 columns that its lanes read with 16-byte loads. There it beats a segment
-// per slot (3.49 against 3.67 ms on 114.6M edges; both slots on one segment keep
-// fewer segments in flight, and the gathered window stays closer to the L2s);
-// on the row plan and at other widths the slots are as fast or faster (256
-// columns 2.39 against 2.41 ms on 23M edges, 200 columns 1.95 against 2.31).
-// TFG_WIDE_ROWS=0 keeps every aggregation on the slots.
-bool use_wide(int64_t F, bool aligned, bool plain_sum, bool part_plan) {
-  if (!plain_sum || !aligned || !part_plan || F != 128) return false;
+// Whether a sum or mean over the part plan goes through spmm_wide: rows of 128
+// columns, which its two slots of 32 lanes of four columns fill. There it beats a
+// segment per slot (3.49 against 3.67 ms on 114.6M edges; both slots on one segment
+// keep fewer segments in flight, and the gathered window stays closer to the L2s);
+// narrower rows leave lanes idle and wider ones take passes, and the slots are as
+// fast or faster there (256 columns 2.39 against 2.41 ms on 23M edges, 200 columns
+// 1.95 against 2.31), as on the row plan. TFG_WIDE_ROWS=0 keeps every aggregation on
+// the slots.
+constexpr int kWideColumns = 128;
+bool use_wide(int64_t F, bool plain_sum, bool part_plan) {
+  if (!plain_sum || !part_plan || F != kWideColumns) return false;
   if (const char* v = std::getenv("TFG_WIDE_ROWS"))
     if (v[0] == '0') return false;
   return true;
@@ -236,8 +226,7 @@ void launch_wide(int n_items, hipStream_t s, const RowArgs& a, int64_t n_src) {
   const dim3 grid((unsigned)n_items);
 #define TFG_WIDE(NN)                                                                          \
   spmm_wide<NN><<<grid, dim3(kRowBlock), 0, s>>>(a.heavy, n_items, a.col, a.perm, a.w,        \
-                                                 a.w_by_perm, a.x, a.ldx, a.F, a.mean, a.out, \
-                                                 a.part, a.ep)
+                                                 a.w_by_perm, a.x, a.ldx, a.F, a.part)
   if (narrow) TFG_WIDE(true); else TFG_WIDE(false);
 #undef TFG_WIDE
 }
@@ -376,8 +365,7 @@ int launch_aggregate(const Graph& g, const float* w, int H, int w_order, const f
   a.n_heavy = n_partials;
   const SplitRow* rows = part_plan ? g.prows : g.split;
   const int n_rows = part_plan ? (int)g.N : g.n_split;
-  const bool aligned = ldx % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
-  if (use_wide(F, aligned, !mx && !heads && mask == nullptr, part_plan) && a.n_heavy > 0)
+  if (use_wide(F, !mx && !heads && mask == nullptr, part_plan) && a.n_heavy > 0)
     launch_wide(a.n_heavy, s, a, g.N_src);
   else
     launch_slots(g, a, mx, heads, mask != nullptr, part_plan, s);
