@@ -26,7 +26,9 @@ def _edges(n, e, dtype):
 # (nodes, edges): nodes set the digits, edges the tile and whether its table is scanned
 SIZES = [(10, 1), (16, 2047), (16, 2048), (255, 2049), (300, 8192), (300, 65537), (2708, 13264),
          (4096, 131073), (5000, 262145), (19717, 65536), (65536, 131073), (65536, 524288),
-         (65536, 524289), (70000, 2048), (70000, 600000), (140000, 2097153)]
+         (65536, 524289), (70000, 2048), (70000, 600000), (140000, 2097153),
+         # fewer than 16 digits: 64 threads each, in 1,024 tiles and one more
+         (1, 8191), (3, 600001), (7, 8388608), (8, 8388609)]
 
 
 @pytest.mark.parametrize("dtype", [np.int32, np.int64])
