@@ -49,6 +49,24 @@ def test_build(tfg, n, e, dtype):
     tfg.tfg_graph_create(d, n, src_parts=1)  # and the flag does not stick
 
 
+@pytest.mark.parametrize("n", [3, 5000])  # work lists by one block, and by several
+@pytest.mark.parametrize("deg", [64 * 128 - 1, 64 * 128, 64 * 128 + 1, 65 * 128, 300 * 128 + 5])
+def test_chunks_of_hub_rows(tfg, n, deg):
+    """Rows of up to 64 chunks, whose items their own thread writes, and of more, which the
+    wavefront does, two of them side by side: every chunk is summed once (integers: exact)."""
+    tgt = np.concatenate([np.full(deg, 1), np.full(deg + 200, 2), np.arange(n)])
+    r = np.random.default_rng([22, n, deg])
+    src = r.integers(0, 50, tgt.size)
+    x = r.integers(-8, 9, (50, 4)).astype(np.float32)
+    order = r.permutation(tgt.size)
+    ei = torch.from_numpy(np.stack([src, tgt])[:, order].astype(np.int64)).cuda()
+    g = tfg.tfg_graph_create(ei, n, N_src=50)
+    y = tfg.tfg_aggregate(None, torch.from_numpy(x).cuda(), n, graph=g).cpu().numpy()
+    ref = np.zeros((n, 4))
+    np.add.at(ref, tgt, x[src])
+    assert np.array_equal(y, ref)
+
+
 @pytest.mark.parametrize("n,e,loops", [(7, 0, True), (5000, 10, False), (2708, 10556, True),
                                        (3000, 2 ** 20 - 3000, True), (3000, 2 ** 20 - 2999, True),
                                        (100000, 2 ** 20, False)])
