@@ -318,8 +318,8 @@ __device__ __forceinline__ void item_regs(const int* __restrict__ perm,
                                           const GroupItem& it, float* __restrict__ out,
                                           float* __restrict__ out_csr, float* __restrict__ pm,
                                           double* __restrict__ pd) {
-  const int SL = it.lanes / HP;
-  const int slot = (lane_id() & (it.lanes - 1)) / HP, hh = lane_id() & (HP - 1);
+  const int SL = it.lanes >> log2_of(HP);
+  const int slot = (lane_id() & (it.lanes - 1)) >> log2_of(HP), hh = lane_id() & (HP - 1);
   int e[NST];
   load_ids<NST>(perm, it.kb, it.ke, slot, SL, e);
   for (int hb = 0; hb < H; hb += HP) {
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(kItemBlock) void softmax_items(
     float* __restrict__ out, float* __restrict__ out_csr, float* __restrict__ pm,
     double* __restrict__ pd) {
   const GroupItem it = group_item(L, blockIdx.x);
-  const int SL = it.lanes / HP, nst = (it.longest + SL - 1) / SL;
+  const int SL = it.lanes >> log2_of(HP), nst = (it.longest + SL - 1) >> log2_of(SL);
   if (nst <= 1) {
     item_regs<1, K>(perm, s, H, HP, it, out, out_csr, pm, pd);
   } else if (nst <= 2) {
@@ -369,8 +369,8 @@ __global__ __launch_bounds__(kItemBlock) void softmax_items(
   } else if (K == 1 && nst <= 8) {
     item_regs<K == 1 ? 8 : 1, K>(perm, s, H, HP, it, out, out_csr, pm, pd);
   } else {  // groups of 64 lanes: one item; single heads
-    const int H1 = H * K, hp = min(HP * K, kWave), sl1 = kWave / hp;
-    const int slot = lane_id() / hp, hh = lane_id() & (hp - 1);
+    const int H1 = H * K, hp = min(HP * K, kWave), sl1 = kWave >> log2_of(hp);
+    const int slot = lane_id() >> log2_of(hp), hh = lane_id() & (hp - 1);
     for (int hb = 0; hb < H1; hb += hp) {
       const int h = hb + hh;
       const bool act = h < H1;
@@ -433,8 +433,8 @@ __device__ __forceinline__ void chunk_write(const int* __restrict__ perm,
                                             const double* __restrict__ pd,
                                             float* __restrict__ out,
                                             float* __restrict__ out_csr) {
-  const int SL = kWave / HP;
-  const int slot = lane_id() / HP, hh = lane_id() & (HP - 1);
+  const int SL = kWave >> log2_of(HP);
+  const int slot = lane_id() >> log2_of(HP), hh = lane_id() & (HP - 1);
   constexpr int R = NST > 0 ? NST : 1;  // registers (NST = 0: the scores loaded in rounds)
   int e[R];
   if constexpr (NST > 0) load_ids<NST>(perm, it.kbeg, it.kend, slot, SL, e);
@@ -471,7 +471,7 @@ __global__ __launch_bounds__(kItemBlock) void softmax_chunks(
   const WorkItem it = heavy[blockIdx.x];
   const ChunkRow r = chunk_row(it, rowptr, chunk);
   if (r.nch > kGiantChunks) return;
-  const int SL = kWave / HP, cst = (chunk + SL - 1) / SL;
+  const int SL = kWave >> log2_of(HP), cst = (chunk + SL - 1) >> log2_of(SL);
   if (cst <= 2) {
     chunk_write<2, K>(perm, s, H, HP, it, r, pm, pd, out, out_csr);
   } else if (cst <= 4) {
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(kGiantWaves * kWave) void softmax_giant(
   if (sr.nchunks <= kGiantChunks) return;
   const int rb = uniform(rowptr[sr.row]), re = uniform(rowptr[sr.row + 1]);
   const int w = uniform((int)threadIdx.x / kWave);
-  const int SL = kWave / HP, slot = lane_id() / HP, hh = lane_id() & (HP - 1);
+  const int SL = kWave >> log2_of(HP), slot = lane_id() >> log2_of(HP), hh = lane_id() & (HP - 1);
   for (int hb = 0; hb < H; hb += HP) {
     const int h = hb + hh;
     const bool act = h < H;

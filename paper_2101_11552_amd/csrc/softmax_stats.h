@@ -81,28 +81,38 @@ struct RowGroups {
   int waves[kGroupLists];
 };
 
-// The plan's lists, longest items first, and the number of wavefronts. A list
-// of items of at most `edges` edges takes as many slots as leave a lane its
-// steps, and at least 64 bytes per step of a row (or all its edges).
+// The plan's lists, longest items first, and the number of wavefronts. A list of
+// items of at most `edges` edges takes as many slots as leave a lane its steps, and
+// at least 64 bytes per step of a row (or all its edges). The short rows take the
+// latter only while their lanes leave part of the chip idle: many of them keep it
+// busy, and slots beyond a row's edges cost a wavefront per few rows (500,000 rows of
+// 2 edges, 2 heads: 49 us with eight slots each, now XX with one, as one thread per
+// row and head took before; 5,000 rows among longer ones: 1.8 us the other way).
+constexpr int64_t kChipLanes = 8192 * kWave;  // 256 CUs x 4 SIMDs x 8 wavefronts
 template <int K>
 inline int64_t row_groups(const Graph& g, int hp, RowGroups& L) {
   int64_t total = 0;
-  auto add = [&](int i, const WorkItem* items, int n, int edges) {
+  auto add = [&](int i, const WorkItem* items, int n, int edges, int64_t most) {
     int lanes = hp;
-    while (lanes < kWave && (lanes / hp * group_steps<K>() < edges || (lanes * K < 16 && lanes / hp < edges))) lanes <<= 1;
+    while (lanes < kWave && (lanes / hp * group_steps<K>() < edges ||
+                             (lanes * K < 16 && lanes / hp < edges && 2 * (int64_t)n * lanes <= most)))
+      lanes <<= 1;
     L.items[i] = items;
     L.n[i] = n;
     L.lanes[i] = lanes;
     L.waves[i] = (int)(((int64_t)n * lanes + kWave - 1) / kWave);
     total += L.waves[i];
   };
-  add(0, g.heavy, g.n_heavy, g.chunk);
-  add(1, g.long_rows, g.n_over64, g.chunk);
-  add(2, g.long_rows + g.n_over64, g.n_over32 - g.n_over64, 64);
-  add(3, g.long_rows + g.n_over32, g.n_long - g.n_over32, 32);
-  add(4, g.short_rows, g.n_short, kShortRow);
+  add(0, g.heavy, g.n_heavy, g.chunk, INT64_MAX);
+  add(1, g.long_rows, g.n_over64, g.chunk, INT64_MAX);
+  add(2, g.long_rows + g.n_over64, g.n_over32 - g.n_over64, 64, INT64_MAX);
+  add(3, g.long_rows + g.n_over32, g.n_long - g.n_over32, 32, INT64_MAX);
+  add(4, g.short_rows, g.n_short, kShortRow, kChipLanes);
   return total;
 }
+
+// log2 of a power of two (a scalar instruction; divisions by lane counts go as shifts).
+__device__ __forceinline__ int log2_of(int v) { return __builtin_ctz((unsigned)v); }
 
 // The item of this lane's group (no edges past the list's end), its lane count
 // and the longest item of the wavefront.
@@ -119,7 +129,8 @@ __device__ __forceinline__ GroupItem group_item(const RowGroups& L, int wid) {
     }
   GroupItem r;
   r.lanes = L.lanes[li];
-  const int i = wid * (kWave / r.lanes) + lane_id() / r.lanes;
+  const int lg = log2_of(r.lanes);
+  const int i = (wid << (log2_of(kWave) - lg)) + (lane_id() >> lg);
   const bool have = i < L.n[li];
   const WorkItem it = L.items[li][have ? i : 0];
   r.kb = it.kbeg;
