@@ -471,14 +471,14 @@ __global__ __launch_bounds__(kItemBlock) void softmax_grad_items(
     const float* __restrict__ da, int H, int HP, float* __restrict__ ds,
     double* __restrict__ pdot) {
   const GroupItem it = group_item(L, blockIdx.x);
-  const int SL = it.lanes >> log2_of(HP), nst = (it.longest + SL - 1) >> log2_of(SL);
-  if (nst <= 1) {
+  const int SL = it.lanes >> log2_of(HP), n = it.ke - it.kb;
+  if (!__any(n > SL)) {
     grad_item_regs<1, K>(perm, alpha, da, H, HP, it, ds, pdot);
-  } else if (nst <= 2) {
+  } else if (!__any(n > 2 * SL)) {
     grad_item_regs<2, K>(perm, alpha, da, H, HP, it, ds, pdot);
-  } else if (nst <= 4) {
+  } else if (!__any(n > 4 * SL)) {
     grad_item_regs<4, K>(perm, alpha, da, H, HP, it, ds, pdot);
-  } else if (K == 1 && nst <= 8) {
+  } else if (K == 1 && !__any(n > 8 * SL)) {
     grad_item_regs<K == 1 ? 8 : 1, K>(perm, alpha, da, H, HP, it, ds, pdot);
   } else {  // groups of 64 lanes: one item; single heads
     const int H1 = H * K, hp = min(HP * K, kWave), sl1 = kWave >> log2_of(hp);

@@ -357,16 +357,16 @@ __global__ __launch_bounds__(kItemBlock) void softmax_items(
     float* __restrict__ out, float* __restrict__ out_csr, float* __restrict__ pm,
     double* __restrict__ pd) {
   const GroupItem it = group_item(L, blockIdx.x);
-  const int SL = it.lanes >> log2_of(HP), nst = (it.longest + SL - 1) >> log2_of(SL);
-  if (nst <= 1) {
+  const int SL = it.lanes >> log2_of(HP), n = it.ke - it.kb;
+  if (!__any(n > SL)) {
     item_regs<1, K>(perm, s, H, HP, it, out, out_csr, pm, pd);
-  } else if (nst <= 2) {
+  } else if (!__any(n > 2 * SL)) {
     item_regs<2, K>(perm, s, H, HP, it, out, out_csr, pm, pd);
-  } else if (nst <= 4 && K == 4 && it.lanes == kWave) {  // more than 512 values
+  } else if (K == 4 && it.lanes == kWave && n <= 4 * SL) {  // more than 512 values
     item_regs<4, K, true>(perm, s, H, HP, it, out, out_csr, pm, pd);
-  } else if (nst <= 4) {
+  } else if (!__any(n > 4 * SL)) {
     item_regs<4, K>(perm, s, H, HP, it, out, out_csr, pm, pd);
-  } else if (K == 1 && nst <= 8) {
+  } else if (K == 1 && !__any(n > 8 * SL)) {
     item_regs<K == 1 ? 8 : 1, K>(perm, s, H, HP, it, out, out_csr, pm, pd);
   } else {  // groups of 64 lanes: one item; single heads
     const int H1 = H * K, hp = min(HP * K, kWave), sl1 = kWave >> log2_of(hp);

@@ -114,31 +114,39 @@ inline int64_t row_groups(const Graph& g, int hp, RowGroups& L) {
 // log2 of a power of two (a scalar instruction; divisions by lane counts go as shifts).
 __device__ __forceinline__ int log2_of(int v) { return __builtin_ctz((unsigned)v); }
 
-// The item of this lane's group (no edges past the list's end), its lane count
-// and the longest item of the wavefront.
+// The item of this lane's group (no edges past the list's end) and its lane count.
 struct GroupItem {
-  int kb, ke, pslot, lanes, longest;
+  int kb, ke, pslot, lanes;
 };
 __device__ __forceinline__ GroupItem group_item(const RowGroups& L, int wid) {
-  int li = 0;
+  // the list's first wavefront, then its fields by scalar selects (a dynamic index
+  // into the arguments would be one more round trip)
+  int before[kGroupLists];
+  before[0] = 0;
 #pragma unroll
-  for (int i = 0; i + 1 < kGroupLists; ++i)
-    if (li == i && wid >= L.waves[i]) {  // uniform
-      wid -= L.waves[i];
-      li = i + 1;
-    }
+  for (int i = 1; i < kGroupLists; ++i) before[i] = before[i - 1] + L.waves[i - 1];
+  const WorkItem* items = L.items[0];
+  int n = L.n[0], lanes = L.lanes[0], first = 0;
+#pragma unroll
+  for (int i = 1; i < kGroupLists; ++i) {
+    const bool here = wid >= before[i];
+    const WorkItem* p = L.items[i];
+    const int ni = L.n[i], li = L.lanes[i];
+    items = here ? p : items;
+    n = here ? ni : n;
+    lanes = here ? li : lanes;
+    first = here ? before[i] : first;
+  }
+  wid -= first;
   GroupItem r;
-  r.lanes = L.lanes[li];
-  const int lg = log2_of(r.lanes);
+  r.lanes = lanes;
+  const int lg = log2_of(lanes);
   const int i = (wid << (log2_of(kWave) - lg)) + (lane_id() >> lg);
-  const bool have = i < L.n[li];
-  const WorkItem it = L.items[li][have ? i : 0];
+  const bool have = i < n;
+  const WorkItem it = items[have ? i : 0];
   r.kb = it.kbeg;
   r.ke = have ? it.kend : it.kbeg;
   r.pslot = have ? it.slot : -1;
-  int n = r.ke - r.kb;
-  for (int o = r.lanes; o < kWave; o <<= 1) n = max(n, __shfl_xor(n, o));
-  r.longest = uniform(n);
   return r;
 }
 
