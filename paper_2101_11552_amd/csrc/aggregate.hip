@@ -25,11 +25,14 @@ void* g_scratch_addr[kMaxDevices] = {};
 
 using namespace rows;
 
-// Combines the partial results of each split row in chunk order, kFixAcc
-// partial rows in flight: sums with one accumulator each, combined pairwise,
-// maxima with the tie rule. A lane covers V consecutive features; the last
-// lane with features of its own steps back to end at F (it repeats some of
-// its neighbour's).
+// Combines the partial results of each split row: `share` neighbouring slots of
+// lps lanes take a row's partials in turn, each kFixAcc partial rows in flight (sums
+// with one accumulator each, combined pairwise; maxima with the tie rule), and are
+// combined pairwise themselves. A lane covers V consecutive features; the last lane
+// with features of its own steps back to end at F (it repeats some of its
+// neighbour's). What bounds a hub row is the chain of loads over its partials: one
+// slot took 1.78 ms for an aggregation with the maxima of 4,700 partials of 4 columns
+// (one wavefront without column vectors 0.86), sixteen slots 0.14.
 constexpr int kFixAcc = 8;
 template <bool MAX, int V>
 __global__ __launch_bounds__(kItemBlock) void fixup_rows(const SplitRow* __restrict__ split,
@@ -37,13 +40,17 @@ __global__ __launch_bounds__(kItemBlock) void fixup_rows(const SplitRow* __restr
                                                      const int* __restrict__ part_arg, int F,
                                                      int mean, float* __restrict__ out,
                                                      int* __restrict__ argout, Epilogue ep,
-                                                     int lps) {
+                                                     int lps, int share) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int wid = blockIdx.x * (kWave / lps) + lane / lps;  // no cross-lane traffic below
-  if (wid >= n_split) return;
-  const SplitRow sr = split[wid];
-  const int row = sr.row, slot0 = sr.slot0, nch = sr.nchunks, deg = sr.deg;
-  for (int fw = (lane & (lps - 1)) * V; fw < F; fw += lps * V) {
+  const int per = kWave / (lps * share);  // rows per wavefront
+  const int wid = blockIdx.x * per + lane / (lps * share);
+  const bool have = wid < n_split;
+  const SplitRow sr = split[have ? wid : 0];
+  const int row = sr.row, slot0 = sr.slot0, nch = have ? sr.nchunks : 0, deg = sr.deg;
+  const int sub = lane / lps & (share - 1);
+  for (int f0 = 0; f0 < F; f0 += lps * V) {
+    const int fw = f0 + (lane & (lps - 1)) * V;
+    const bool fok = fw < F;
     const int f = min(fw, F - V);
     if constexpr (MAX) {
       constexpr int U = kFixAcc / 2;  // two rows each: values and edge ids
@@ -54,13 +61,13 @@ __global__ __launch_bounds__(kItemBlock) void fixup_rows(const SplitRow* __restr
         best[v] = 0.0f;
         a[v] = -1;
       }
-      for (int j = 0; j < nch; j += U) {
+      for (int j = sub; j < nch; j += U * share) {
         float t[U][V];
         int e[U][V];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
           // places past the row's partials repeat the last one, which never wins again
-          const int64_t o = (int64_t)(slot0 + min(j + i, nch - 1)) * F + f;
+          const int64_t o = (int64_t)(slot0 + min(j + i * share, nch - 1)) * F + f;
           load_row_once<V>(part + o, t[i]);
           load_irow<V>(part_arg + o, e[i]);
         }
@@ -69,10 +76,19 @@ __global__ __launch_bounds__(kItemBlock) void fixup_rows(const SplitRow* __restr
 #pragma unroll
           for (int v = 0; v < V; ++v) max_combine(best[v], a[v], t[i][v], e[i][v]);
       }
+      for (int o = lps; o < lps * share; o <<= 1)
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          const float t = __shfl_xor(best[v], o);
+          const int e = __shfl_xor(a[v], o);
+          max_combine(best[v], a[v], t, e);
+        }
 #pragma unroll
       for (int v = 0; v < V; ++v) best[v] = a[v] < 0 ? 0.0f : best[v];
-      store_row<V>(out + (int64_t)row * F + f, best);
-      if (argout != nullptr) store_irow<V>(argout + (int64_t)row * F + f, a);
+      if (have && fok && sub == 0) {
+        store_row<V>(out + (int64_t)row * F + f, best);
+        if (argout != nullptr) store_irow<V>(argout + (int64_t)row * F + f, a);
+      }
     } else {
       // kFixAcc partial rows in flight, one accumulator each
       float a4[kFixAcc][V];
@@ -80,12 +96,12 @@ __global__ __launch_bounds__(kItemBlock) void fixup_rows(const SplitRow* __restr
       for (int i = 0; i < kFixAcc; ++i)
 #pragma unroll
         for (int v = 0; v < V; ++v) a4[i][v] = 0.0f;
-      for (int j = 0; j < nch; j += kFixAcc) {
+      for (int j = sub; j < nch; j += kFixAcc * share) {
         float t[kFixAcc][V];
 #pragma unroll
         for (int i = 0; i < kFixAcc; ++i) {
-          if (j + i < nch) {
-            load_row_once<V>(part + (int64_t)(slot0 + j + i) * F + f, t[i]);
+          if (j + i * share < nch) {
+            load_row_once<V>(part + (int64_t)(slot0 + j + i * share) * F + f, t[i]);
           } else {
 #pragma unroll
             for (int v = 0; v < V; ++v) t[i][v] = 0.0f;
@@ -102,14 +118,19 @@ __global__ __launch_bounds__(kItemBlock) void fixup_rows(const SplitRow* __restr
         for (int i = 0; i + step < kFixAcc; i += 2 * step)
 #pragma unroll
           for (int v = 0; v < V; ++v) a4[i][v] += a4[i + step][v];
-      float s[V];
+      for (int o = lps; o < lps * share; o <<= 1)
 #pragma unroll
-      for (int v = 0; v < V; ++v) {
-        s[v] = a4[0][v];
-        if (mean && deg > 0) s[v] = s[v] / (float)deg;
+        for (int v = 0; v < V; ++v) a4[0][v] += __shfl_xor(a4[0][v], o);
+      if (have && fok && sub == 0) {
+        float s[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          s[v] = a4[0][v];
+          if (mean && deg > 0) s[v] = s[v] / (float)deg;
+        }
+        apply_epilogue<V>(ep, row, f, s);
+        store_row<V>(out + (int64_t)row * F + f, s);
       }
-      apply_epilogue<V>(ep, row, f, s);
-      store_row<V>(out + (int64_t)row * F + f, s);
     }
   }
 }
@@ -371,12 +392,18 @@ int launch_aggregate(const Graph& g, const float* w, int H, int w_order, const f
     launch_slots(g, a, mx, heads, mask != nullptr, part_plan, s);
   TFG_LAUNCHED("aggregation");
   if (n_rows > 0) {
-    int flps = 4;  // lanes per row
+    int flps = 4;  // lanes per slot
     while (flps < kWave && flps * (F >= 4 ? 4 : 1) < F) flps <<= 1;
-    dim3 fgrid((unsigned)((n_rows + kWave / flps - 1) / (kWave / flps)));
+    // slots per row: one by source part (a row has at most a few partials per part);
+    // split rows the average number of partials a row, at least four
+    int share = 1;
+    if (!part_plan)
+      while (share < kWave / flps && (share < 4 || (int64_t)share * n_rows < n_partials)) share <<= 1;
+    const int64_t lanes = (int64_t)n_rows * flps * share;
+    dim3 fgrid((unsigned)((lanes + kWave - 1) / kWave));
 #define TFG_FIXUP(M, VV)                                                                      \
   fixup_rows<M, VV><<<fgrid, dim3(kItemBlock), 0, s>>>(rows, n_rows, a.part, a.part_arg, a.F, \
-                                                       a.mean, out, argmax, a.ep, flps)
+                                                       a.mean, out, argmax, a.ep, flps, share)
     if (mx && F >= 4) TFG_FIXUP(true, 4);
     else if (mx) TFG_FIXUP(true, 1);
     else if (F >= 4) TFG_FIXUP(false, 4);

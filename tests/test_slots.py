@@ -222,3 +222,22 @@ def test_head_weights_beyond_2_gib(tfg):
         ref = m.view(50, deg, H).sum(1)
         scale = m.abs().view(50, deg, H).sum(1)
         assert float(((y[-50:].double() - ref).abs() / scale).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("F", [1, 3, 4, 16, 33, 64, 130, 260])
+@pytest.mark.parametrize("chunks", [[2, 3], [4, 5, 9], [2] * 40 + [70], [33, 65]])
+def test_split_rows(tfg, orc, F, chunks):
+    """Rows of many chunks (128 edges each), whose partials go over 4 to 16 slots of a wavefront by
+    their average number, beside short ones: sums, means and maxima with their edges."""
+    r = np.random.default_rng([14, F, len(chunks)])
+    deg = np.array([128 * c - int(r.integers(0, 127)) for c in chunks] + [0, 3, 20])
+    tgt = np.repeat(np.arange(deg.size), deg)
+    ei = np.stack([r.integers(0, 300, tgt.size), tgt])[:, r.permutation(tgt.size)].astype(np.int64)
+    x = r.standard_normal((300, F)).astype(np.float32)
+    x[r.random(x.shape) < 0.2] = 0.0
+    w = r.standard_normal(tgt.size).astype(np.float32)
+    g = tfg.tfg_graph_create(torch.from_numpy(ei).cuda(), deg.size, N_src=300)
+    for reduce in ("sum", "mean", "max"):
+        res = tfg.tfg_aggregate(None, torch.from_numpy(x).cuda(), deg.size, reduce,
+                                edge_weight=torch.from_numpy(w).cuda(), graph=g)
+        _check(orc, ei, x, deg.size, res, reduce, w, 1)
