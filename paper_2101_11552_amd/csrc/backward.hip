@@ -46,30 +46,12 @@ __global__ __launch_bounds__(kItemBlock) void edge_grad_slots(
     const int* __restrict__ perm, const float* __restrict__ x, int64_t ldx,
     const float* __restrict__ dy, const int* __restrict__ arg, int H, int D, int G,
     float* __restrict__ dw, int dw_by_perm, float scale) {
-  constexpr int SLOTS = kWave / LPS;
   constexpr int NR = id_regs<LPS>();
   constexpr int BW = kIds / NR;
   constexpr int U = 8, Q = 4;  // gathers in flight per slot; edges per reduction
-  int wid = blockIdx.x;
-  int li = 0;
-#pragma unroll
-  for (int i = 0; i + 1 < kSlotLists; ++i)
-    if (li == i && wid >= L.waves[i]) {  // uniform
-      wid -= L.waves[i];
-      li = i + 1;
-    }
-  const WorkItem* items = L.items[li];
-  const int n_items = L.n[li], split = L.split[li];
-  const int lane = lane_id();
-  const int sl = lane % LPS;
-  const int q = wid * SLOTS + lane / LPS;
-  const int ii = q / split, sub = q - ii * split;
-  const bool have = ii < n_items;
-  const WorkItem it = items[have ? ii : 0];
-  const int kbeg = it.kbeg, n = have ? it.kend - it.kbeg : 0;
-  int nmax = __builtin_amdgcn_readlane(n, 0);
-#pragma unroll
-  for (int s = 1; s < SLOTS; ++s) nmax = max(nmax, __builtin_amdgcn_readlane(n, s * LPS));
+  const SlotItem it = slot_item<LPS>(L);
+  const int kbeg = it.kbeg, n = it.n, nmax = it.nmax, split = it.split, sub = it.sub;
+  const int sl = lane_id() % LPS;
   if (nmax == 0) return;
   const int F = H * D;
   const int64_t row_bytes = ldx * (int64_t)sizeof(float);

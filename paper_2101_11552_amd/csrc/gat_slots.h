@@ -108,26 +108,9 @@ __global__ __launch_bounds__(kItemBlock) void gat_slots(SlotLists L, const int* 
   constexpr int BW = kIds / NR;
   constexpr int U = 4;  // rows in flight per slot
   constexpr int OWN = (DOT ? U : kIds) / GX;  // scores per lane and round (dot product: group)
-  int wid = blockIdx.x;
-  int li = 0;
-#pragma unroll
-  for (int i = 0; i + 1 < kSlotLists; ++i)
-    if (li == i && wid >= L.waves[i]) {  // uniform
-      wid -= L.waves[i];
-      li = i + 1;
-    }
-  const WorkItem* items = L.items[li];
-  const int n_items = L.n[li], split = L.split[li];
-  const int lane = lane_id();
-  const int sl = lane % LPS;
-  const int q = wid * SLOTS + lane / LPS;
-  const int ii = q / split, sub = q - ii * split;
-  const bool have = ii < n_items;
-  const WorkItem it = items[have ? ii : 0];
-  const int kbeg = it.kbeg, n = have ? it.kend - it.kbeg : 0;
-  int nmax = __builtin_amdgcn_readlane(n, 0);
-#pragma unroll
-  for (int s = 1; s < SLOTS; ++s) nmax = max(nmax, __builtin_amdgcn_readlane(n, s * LPS));
+  const SlotItem it = slot_item<LPS>(L);
+  const int kbeg = it.kbeg, n = it.n, nmax = it.nmax, split = it.split, sub = it.sub;
+  const int lane = lane_id(), sl = lane % LPS;
   const int F = H * D;
   const int64_t row_bytes = (int64_t)F * (int64_t)sizeof(float);
   const int gi = lane % GX;
@@ -292,7 +275,7 @@ __global__ __launch_bounds__(kItemBlock) void gat_slots(SlotLists L, const int* 
         const double d2 = __shfl_xor(den, LPS * i);
         triple_merge<V>(m, den, tot, m2, d2, a2);
       }
-    if (!have || !fok || sub != 0) continue;
+    if (!it.have || !fok || sub != 0) continue;
     if (it.slot < 0) {
       float o[V];
 #pragma unroll

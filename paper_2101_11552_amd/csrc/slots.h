@@ -88,6 +88,49 @@ __device__ __forceinline__ void each(F&& f) {
   each_of(f, std::make_integer_sequence<int, N>{});
 }
 
+// The item of this lane's slot: place `sub` of the `split` slots that share it, n
+// edges from kbeg (0 past the list's end: !have), and the most edges of an item of the
+// wavefront. The list is chosen by scalar selects among arguments loaded together (a
+// dynamic index into them would be a round trip more, a division per lane another
+// twenty instructions: with rows of one or two edges that is a tenth of the time).
+struct SlotItem {
+  int row, kbeg, n, slot, split, sub, nmax;
+  bool have;
+};
+template <int LPS>
+__device__ __forceinline__ SlotItem slot_item(const SlotLists& L) {
+  constexpr int SLOTS = kWave / LPS;
+  const int wave = blockIdx.x;
+  const WorkItem* items = L.items[0];
+  int n_items = L.n[0], split = L.split[0], first = 0, before = 0;
+#pragma unroll
+  for (int i = 1; i < kSlotLists; ++i) {
+    before += L.waves[i - 1];
+    const bool here = wave >= before;
+    const WorkItem* p = L.items[i];
+    const int ni = L.n[i], si = L.split[i];
+    items = here ? p : items;
+    n_items = here ? ni : n_items;
+    split = here ? si : split;
+    first = here ? before : first;
+  }
+  const int q = (wave - first) * SLOTS + lane_id() / LPS;
+  const int i = q >> __builtin_ctz((unsigned)split);  // a power of two
+  SlotItem r;
+  r.split = split;
+  r.sub = q & (split - 1);
+  r.have = i < n_items;
+  const WorkItem w = items[r.have ? i : 0];
+  r.row = w.row;
+  r.kbeg = w.kbeg;
+  r.slot = w.slot;
+  r.n = r.have ? w.kend - w.kbeg : 0;
+  r.nmax = __builtin_amdgcn_readlane(r.n, 0);
+#pragma unroll
+  for (int s = 1; s < SLOTS; ++s) r.nmax = max(r.nmax, __builtin_amdgcn_readlane(r.n, s * LPS));
+  return r;
+}
+
 // kMax: edge ids ascend along an item (one source part per item); kMaxTies:
 // they need not, equal maxima compare the ids.
 enum { kSum = 0, kMax = 1, kMaxTies = 2, kMasked = 3 };
@@ -105,26 +148,9 @@ __global__ __launch_bounds__(kItemBlock) void spmm_slots(
   constexpr int BW = kIds / NR;  // edges per register
   constexpr bool MAX = KIND == kMax || KIND == kMaxTies, MASK = KIND == kMasked;
   constexpr int U = MASK || WM == kHeads ? 4 : 8;  // gathers in flight per slot
-  int wid = blockIdx.x;
-  int li = 0;
-#pragma unroll
-  for (int i = 0; i + 1 < kSlotLists; ++i)
-    if (li == i && wid >= L.waves[i]) {  // uniform
-      wid -= L.waves[i];
-      li = i + 1;
-    }
-  const WorkItem* items = L.items[li];
-  const int n_items = L.n[li], split = L.split[li];
-  const int lane = lane_id();
-  const int sl = lane % LPS;
-  const int q = wid * SLOTS + lane / LPS;  // slot index in the list's launch
-  const int ii = q / split, sub = q - ii * split;
-  const bool have = ii < n_items;
-  const WorkItem it = items[have ? ii : 0];
-  const int kbeg = it.kbeg, n = have ? it.kend - it.kbeg : 0;
-  int nmax = __builtin_amdgcn_readlane(n, 0);
-#pragma unroll
-  for (int s = 1; s < SLOTS; ++s) nmax = max(nmax, __builtin_amdgcn_readlane(n, s * LPS));
+  const SlotItem it = slot_item<LPS>(L);
+  const int kbeg = it.kbeg, n = it.n, nmax = it.nmax, split = it.split, sub = it.sub;
+  const int sl = lane_id() % LPS;
   const int64_t row_bytes = ldx * (int64_t)sizeof(float);
   const bool need_perm = MAX || MASK || w_by_perm;
 
@@ -277,7 +303,7 @@ __global__ __launch_bounds__(kItemBlock) void spmm_slots(
           }
         }
       }
-    if (!have || !fok || sub != 0) continue;
+    if (!it.have || !fok || sub != 0) continue;
     if (it.slot < 0) {
       if constexpr (MAX) {
 #pragma unroll
