@@ -188,18 +188,24 @@ __global__ __launch_bounds__(kItemBlock) void spmm_slots(
       int id[NR], pe[NR], wt[NR];
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
+        id[r] = pe[r] = wt[r] = 0;
+        // (maxima repeat an item's last edge there)
+        if (!MAX && r > 0 && r0 + r * BW * split >= nmax) continue;  // uniform: past every item
         const int j = min(j0 + (r * BW + sl % BW) * split, n - 1);
         id[r] = n > 0 ? col[kbeg + j] : 0;
         pe[r] = (need_perm && n > 0) ? perm[kbeg + j] : 0;
         if constexpr (WM == kEdge)
           wt[r] = __float_as_int(
               n > 0 ? w[w_by_perm ? pe[r] : kbeg + j] : 0.0f);
+        if constexpr (WM == kHeads) wt[r] = n > 0 ? (w_by_perm ? pe[r] : kbeg + j) : 0;
+      }
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
         if constexpr (NARROW) id[r] = id[r] * (int)row_bytes;
-        if constexpr (WM == kHeads) {  // the edge's row of weights (its byte offset)
-          wt[r] = n > 0 ? (w_by_perm ? pe[r] : kbeg + j) : 0;
-          // (up to 2^32: an unsigned product, kept in a signed register for the DPP moves)
-          if constexpr (NARROW) wt[r] = (int)((unsigned)wt[r] * 4u * (unsigned)H);
-        }
+        // the edge's row of weights as its byte offset, up to 2^32: an unsigned
+        // product, kept in a signed register for the DPP moves
+        if constexpr (WM == kHeads && NARROW)
+          wt[r] = (int)((unsigned)wt[r] * 4u * (unsigned)H);
       }
       float half[2][V];  // the sums of the round's first and last eight places
 #pragma unroll

@@ -86,7 +86,7 @@ struct RowGroups {
 // at least 64 bytes per step of a row (or all its edges). The short rows take the
 // latter only while their lanes leave part of the chip idle: many of them keep it
 // busy, and slots beyond a row's edges cost a wavefront per few rows (500,000 rows of
-// 2 edges, 2 heads: 49 us with eight slots each, now XX with one, as one thread per
+// 2 edges, 2 heads: 49 us with eight slots each, now 16 with one, as one thread per
 // row and head took before; 5,000 rows among longer ones: 1.8 us the other way).
 constexpr int64_t kChipLanes = 8192 * kWave;  // 256 CUs x 4 SIMDs x 8 wavefronts
 template <int K>
