@@ -40,7 +40,7 @@ enum { kGradSum = 0, kGradMean = 1, kGradMax = 2 };
 // 512-byte rows at 6 TB/s. 23M edges of 64 columns by source part: 0.68 -> 0.47
 // ms. Rows wider than 256 columns had one thread per edge (2M edges of 300
 // columns: 2.50 -> 0.32 ms).
-template <int V, int LPS, int MODE, bool NARROW>
+template <int V, int LPS, int U, int MODE, bool NARROW>
 __global__ __launch_bounds__(kItemBlock) void edge_grad_slots(
     SlotLists L, const int* __restrict__ rowptr, const int* __restrict__ col,
     const int* __restrict__ perm, const float* __restrict__ x, int64_t ldx,
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kItemBlock) void edge_grad_slots(
     float* __restrict__ dw, int dw_by_perm, float scale) {
   constexpr int NR = id_regs<LPS>();
   constexpr int BW = kIds / NR;
-  constexpr int U = 8, Q = 4;  // gathers in flight per slot; edges per reduction
+  constexpr int Q = 4;  // edges per reduction (U: gathers in flight per slot)
   const SlotItem it = slot_item<LPS>(L);
   const int kbeg = it.kbeg, n = it.n, nmax = it.nmax, split = it.split, sub = it.sub;
   const int sl = lane_id() % LPS;
@@ -89,11 +89,15 @@ __global__ __launch_bounds__(kItemBlock) void edge_grad_slots(
       int id[NR], pe[NR];
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
+        id[r] = pe[r] = 0;
+        if (r > 0 && r0 + r * BW * split >= nmax) continue;  // uniform: past every item
         const int j = min(j0 + (r * BW + sl % BW) * split, n - 1);
         id[r] = n > 0 ? col[kbeg + j] : 0;
         pe[r] = (need_perm && n > 0) ? perm[kbeg + j] : 0;
-        if constexpr (NARROW) id[r] = id[r] * (int)row_bytes;
       }
+      if constexpr (NARROW)
+#pragma unroll
+        for (int r = 0; r < NR; ++r) id[r] = id[r] * (int)row_bytes;
       each<kIds / U>([&](auto g_) {
         constexpr int GR = decltype(g_)::value;
         if (r0 + GR * U * split < nmax) {  // uniform
@@ -584,24 +588,32 @@ int launch_edge_grad(const Graph& g, const float* x, int64_t ldx, const float* d
              true, L, &waves);
   if (waves == 0) return TFG_OK;
   const bool narrow = (double)g.N_src * (double)ldx * 4.0 < 2147483648.0;
-#define TFG_EG(VV, LL)                                                                        \
+  // Four gathers per slot instead of eight where items have few edges and fill the
+  // wavefront's lanes in one pass: places past an item's end repeat its last row, and
+  // half the registers let eight wavefronts stay in flight for five (500,000 rows of 2
+  // edges of 200 columns 322 -> 253 us; rows of 14 edges of 128 columns 199 and 206).
+  const int items = part_plan ? g.n_pexec : g.n_heavy + g.n_long + g.n_short;
+  const bool few = lps >= 32 && G * vec >= D && g.E <= 8 * (int64_t)items;
+#define TFG_EG(VV, LL, UU)                                                                    \
   do {                                                                                        \
     if (narrow)                                                                               \
-      edge_grad_slots<VV, LL, MODE, true><<<(unsigned)waves, kItemBlock, 0, s>>>(             \
+      edge_grad_slots<VV, LL, UU, MODE, true><<<(unsigned)waves, kItemBlock, 0, s>>>(         \
           L, g.rowptr, g.col, g.perm, x, ldx, dy, arg, H, D, G, dw, by_perm, scale);          \
     else                                                                                      \
-      edge_grad_slots<VV, LL, MODE, false><<<(unsigned)waves, kItemBlock, 0, s>>>(            \
+      edge_grad_slots<VV, LL, UU, MODE, false><<<(unsigned)waves, kItemBlock, 0, s>>>(        \
           L, g.rowptr, g.col, g.perm, x, ldx, dy, arg, H, D, G, dw, by_perm, scale);          \
   } while (0)
-#define TFG_EG_LPS(VV)                   \
-  switch (lps) {                         \
-    case 4: TFG_EG(VV, 4); break;        \
-    case 8: TFG_EG(VV, 8); break;        \
-    case 16: TFG_EG(VV, 16); break;      \
-    case 32: TFG_EG(VV, 32); break;      \
-    default: TFG_EG(VV, 64); break;      \
+#define TFG_EG_LPS(VV)                      \
+  switch (lps) {                            \
+    case 4: TFG_EG(VV, 4, 8); break;        \
+    case 8: TFG_EG(VV, 8, 8); break;        \
+    case 16: TFG_EG(VV, 16, 8); break;      \
+    case 32: TFG_EG(VV, 32, 8); break;      \
+    default: TFG_EG(VV, 64, 8); break;      \
   }
-  if (vec == 4) TFG_EG_LPS(4)
+  if (vec == 4 && few && lps == 32) TFG_EG(4, 32, 4);
+  else if (vec == 4 && few) TFG_EG(4, 64, 4);
+  else if (vec == 4) TFG_EG_LPS(4)
   else TFG_EG_LPS(1)
 #undef TFG_EG_LPS
 #undef TFG_EG
