@@ -453,10 +453,10 @@ __device__ __forceinline__ void grad_item_regs(const int* __restrict__ perm,
 // over 8 edges and one head per lane, now 31.
 template <int K>
 __global__ __launch_bounds__(kItemBlock) void softmax_grad_items(
-    RowGroups L, const int* __restrict__ perm, const float* __restrict__ alpha,
-    const float* __restrict__ da, int H, int HP, float* __restrict__ ds,
-    double* __restrict__ pdot) {
-  const GroupItem it = group_item(L, blockIdx.x);
+    RowGroups L, const int* __restrict__ rowptr, int chunk, int fewer,
+    const int* __restrict__ perm, const float* __restrict__ alpha, const float* __restrict__ da,
+    int H, int HP, float* __restrict__ ds, double* __restrict__ pdot) {
+  const GroupItem it = group_item(L, blockIdx.x, fewer, rowptr, chunk);
   const int SL = it.lanes >> log2_of(HP), n = it.ke - it.kb;
   if (!__any(n > SL)) {
     grad_item_regs<1, K>(perm, alpha, da, H, HP, it, ds, pdot);
@@ -532,12 +532,12 @@ __device__ __forceinline__ void grad_chunk_write(const int* __restrict__ perm,
 
 template <int K>
 __global__ __launch_bounds__(kItemBlock) void softmax_grad_chunks(
-    const WorkItem* __restrict__ heavy, const int* __restrict__ rowptr, int chunk,
+    const WorkItem* __restrict__ heavy, const int* __restrict__ rowptr, int chunk, int fewer,
     const int* __restrict__ perm, const float* __restrict__ alpha, const float* __restrict__ da,
     int H, int HP, const double* __restrict__ pdot, float* __restrict__ ds) {
   const WorkItem it = heavy[blockIdx.x];
   const ChunkRow r = chunk_row(it, rowptr, chunk);
-  if (r.nch > kGiantChunks) return;
+  if (r.nch > kGiantChunks || r.nch <= fewer) return;
   const int SL = kWave >> log2_of(HP), cst = (chunk + SL - 1) >> log2_of(SL);
   if (cst <= 2) {
     grad_chunk_write<2, K>(perm, alpha, da, H, HP, it, r, pdot, ds);
@@ -548,6 +548,55 @@ __global__ __launch_bounds__(kItemBlock) void softmax_grad_chunks(
   } else {  // single heads
     grad_chunk_write<0, 1>(perm, alpha, da, H * K, min(HP * K, kWave), it, r, pdot, ds);
   }
+}
+
+// Split rows of at most kRowWaves chunks in the caller's order, one block each and a
+// wavefront per chunk, whose values stay in registers while the chunks' sums meet in
+// LDS. What bounds this order is the lines that scattered values move, and the two
+// launches above read alpha and dalpha twice: 8M edges of a power-law graph, one head,
+// 405 us, with them 560. Not where the two arrays fit the L2s (460 rows of 1,400
+// chunks, 1.35M edges: 30 us, with them 8) or a value's line holds several heads.
+constexpr int kRowWaves = 16;
+constexpr int kRowHeads = 4;
+constexpr int kRowSteps = 8;  // values a lane holds
+bool grad_by_rows(const Graph& g, int H, bool graph_order) {
+  return !graph_order && H <= kRowHeads && g.n_split > 0 &&
+         g.chunk * heads_per_pass(H) <= kRowSteps * kWave &&
+         8.0 * (double)g.E * (double)H >= 32.0 * (1 << 20);
+}
+template <int NST>
+__device__ __forceinline__ void grad_row(const int* __restrict__ perm,
+                                         const float* __restrict__ alpha,
+                                         const float* __restrict__ da, int H, int HP, int kb,
+                                         int ke, int nch, int w, double (&sums)[kRowWaves][kRowHeads],
+                                         float* __restrict__ ds) {
+  const int SL = kWave >> log2_of(HP);
+  const int slot = lane_id() >> log2_of(HP), h = lane_id() & (HP - 1);
+  int e[NST];
+  float a[NST][1], g[NST][1];
+  load_ids<NST>(perm, kb, ke, slot, SL, e);
+  grad_load<NST, 1>(alpha, da, H, h, h < H, e, a, g);
+  const double dot = grad_dot<NST, 1>(a, g, 0, HP, kWave);
+  if (slot == 0) sums[w][h] = dot;
+  __syncthreads();
+  double total[1] = {0.0};
+  for (int c = 0; c < nch; ++c) total[0] += sums[c][h];
+  grad_write<NST, 1>(a, g, e, total, H, h, h < H, ds);
+}
+__global__ __launch_bounds__(kRowWaves * kWave) void softmax_grad_rows(
+    const SplitRow* __restrict__ split, const int* __restrict__ rowptr, int chunk,
+    const int* __restrict__ perm, const float* __restrict__ alpha, const float* __restrict__ da,
+    int H, int HP, float* __restrict__ ds) {
+  __shared__ double sums[kRowWaves][kRowHeads];
+  const SplitRow sr = split[blockIdx.x];
+  if (sr.nchunks > kRowWaves) return;  // uniform
+  const int re = uniform(rowptr[sr.row + 1]), w = uniform((int)threadIdx.x / kWave);
+  // (wavefronts past the row's chunks hold no edges)
+  const int kb = min(re, uniform(rowptr[sr.row]) + w * chunk), ke = min(re, kb + chunk);
+  const int steps = chunk * HP;  // of a whole chunk, times the wavefront
+  if (steps <= 2 * kWave) grad_row<2>(perm, alpha, da, H, HP, kb, ke, sr.nchunks, w, sums, ds);
+  else if (steps <= 4 * kWave) grad_row<4>(perm, alpha, da, H, HP, kb, ke, sr.nchunks, w, sums, ds);
+  else grad_row<kRowSteps>(perm, alpha, da, H, HP, kb, ke, sr.nchunks, w, sums, ds);
 }
 
 // Rows of more than kGiantChunks chunks: the sums added once per wavefront of
@@ -782,6 +831,7 @@ int launch_segment_softmax_backward(const Graph& g, const float* alpha, const fl
   double* pdot = reinterpret_cast<double*>(
       static_cast<char*>(ws) +
       align_up(sizeof(float) * (size_t)std::max<int64_t>((int64_t)g.n_heavy * H, 1), 256));
+  const int fewer = grad_by_rows(g, H, graph_order) ? kRowWaves : 0;
   const auto run = [&](auto k_) {
     constexpr int K = decltype(k_)::value;
     const int hk = H / K, hpk = heads_per_pass(hk);
@@ -789,13 +839,13 @@ int launch_segment_softmax_backward(const Graph& g, const float* alpha, const fl
     const int64_t waves = row_groups<K>(g, hpk, L);
     if (waves > INT32_MAX) return fail(TFG_ERR_TOO_LARGE, "softmax gradient: too many work items");
     if (waves > 0) {
-      softmax_grad_items<K><<<(unsigned)waves, kItemBlock, 0, s>>>(L, perm, alpha, dalpha, hk, hpk,
-                                                                   ds, pdot);
+      softmax_grad_items<K><<<(unsigned)waves, kItemBlock, 0, s>>>(
+          L, g.rowptr, g.chunk, fewer, perm, alpha, dalpha, hk, hpk, ds, pdot);
       TFG_LAUNCHED("softmax_grad_items");
     }
     if (g.n_heavy > 0) {
       softmax_grad_chunks<K><<<(unsigned)g.n_heavy, kItemBlock, 0, s>>>(
-          g.heavy, g.rowptr, g.chunk, perm, alpha, dalpha, hk, hpk, pdot, ds);
+          g.heavy, g.rowptr, g.chunk, fewer, perm, alpha, dalpha, hk, hpk, pdot, ds);
       TFG_LAUNCHED("softmax_grad_chunks");
     }
     return (int)TFG_OK;
@@ -803,6 +853,11 @@ int launch_segment_softmax_backward(const Graph& g, const float* alpha, const fl
   const int rc = H % 4 == 0 ? run(std::integral_constant<int, 4>{})
                             : run(std::integral_constant<int, 1>{});
   if (rc) return rc;
+  if (fewer > 0) {
+    softmax_grad_rows<<<(unsigned)g.n_split, kRowWaves * kWave, 0, s>>>(
+        g.split, g.rowptr, g.chunk, perm, alpha, dalpha, H, hp, ds);
+    TFG_LAUNCHED("softmax_grad_rows");
+  }
   if (g.n_heavy > kGiantChunks) {
     softmax_grad_giant<<<(unsigned)g.n_split, kGiantWaves * kWave, 0, s>>>(
         g.split, g.rowptr, g.chunk, perm, alpha, dalpha, H, hp, pdot, ds);

@@ -115,10 +115,13 @@ inline int64_t row_groups(const Graph& g, int hp, RowGroups& L) {
 __device__ __forceinline__ int log2_of(int v) { return __builtin_ctz((unsigned)v); }
 
 // The item of this lane's group (no edges past the list's end) and its lane count.
+// Chunks of rows of at most `fewer` chunks count as no edges (0: none).
 struct GroupItem {
   int kb, ke, pslot, lanes;
 };
-__device__ __forceinline__ GroupItem group_item(const RowGroups& L, int wid) {
+__device__ __forceinline__ GroupItem group_item(const RowGroups& L, int wid, int fewer = 0,
+                                                const int* __restrict__ rowptr = nullptr,
+                                                int chunk = 1) {
   // the list's first wavefront, then its fields by scalar selects (a dynamic index
   // into the arguments would be one more round trip)
   int before[kGroupLists];
@@ -147,6 +150,10 @@ __device__ __forceinline__ GroupItem group_item(const RowGroups& L, int wid) {
   r.kb = it.kbeg;
   r.ke = have ? it.kend : it.kbeg;
   r.pslot = have ? it.slot : -1;
+  if (fewer > 0 && r.pslot >= 0 && rowptr[it.row + 1] - rowptr[it.row] <= fewer * chunk) {
+    r.ke = r.kb;
+    r.pslot = -1;
+  }
   return r;
 }
 

@@ -94,3 +94,24 @@ def test_rows_from_registers_are_as_exact_as_swept_ones(tfg, n):
     """Rows of over 64 edges, whole and in chunks, keep their exponentials in registers at 8 heads
     and load the scores again at 5: both divide by the sum in double (2% for the sample)."""
     assert _alpha_error(tfg, n, 8) <= 1.02 * _alpha_error(tfg, n, 5)
+
+
+@pytest.mark.parametrize("H,E", [(1, 4_200_000), (2, 2_100_000), (3, 1_400_001), (4, 1_050_000)])
+def test_gradient_of_split_rows_in_edge_order(tfg, H, E):
+    """Arrays beyond the L2s in the caller's order: split rows of up to 16 chunks by a block each,
+    of more by the chunk launches, against the graph order (the same products, added in double)."""
+    r = np.random.default_rng([15, H])
+    hubs = [129, 256, 257, 15 * 128, 16 * 128, 16 * 128 + 1, 17 * 128, 9000]
+    n = 20_000
+    tgt = np.concatenate([np.repeat(np.arange(len(hubs)), hubs),
+                          r.integers(len(hubs), n, E - sum(hubs) - 600),
+                          r.integers(n, n + 2, 600)])
+    r.shuffle(tgt)
+    g = tfg.tfg_graph_create(torch.from_numpy(np.stack([tgt, tgt])).cuda(), n + 2)
+    s, da = (torch.from_numpy(r.standard_normal((E, H)).astype(np.float32)).cuda() for _ in range(2))
+    al = tfg.tfg_segment_softmax_graph(g, s, order="coo")
+    ds = tfg.tfg_segment_softmax_graph_backward(g, al, da, order="coo")
+    move = lambda t: tfg.tfg_edge_reorder(t, None, g)
+    want = tfg.tfg_segment_softmax_graph_backward(g, move(al), move(da))
+    scale = move(al) * (move(da).abs() + 4)
+    assert float(((move(ds) - want).abs() / scale).max()) <= 2 ** -23
