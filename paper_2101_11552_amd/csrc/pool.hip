@@ -195,7 +195,7 @@ namespace {
 // Gradient of the pooling: dx[n, c] = dy[g, c] (sum), dy[g, c] / count(g) (mean),
 // or dy[g, c] where node n won the forward max of (g, c), else 0. g = the clamped
 // graph id; the counts come from the segment bounds. A thread takes V columns of
-// kGradNodes nodes, 1 << lg neighbouring lanes a row, the chains from graph id to
+// kGradNodes nodes, lpr neighbouring threads a row, the chains from graph id to
 // dy row of its nodes in flight together, and the stores stream past the L2s.
 // Without the index check sum and max need no segment bounds. 1.05M nodes of 64
 // columns: 63 us with one node per thread and a 64-bit division, now 46 (5.9 TB/s
@@ -206,10 +206,13 @@ __global__ __launch_bounds__(kBlock) void pool_grad(const float* __restrict__ dy
                                                     int F, const IdxT* __restrict__ gi,
                                                     int64_t Nb, const int* __restrict__ goff,
                                                     int reduce, const int* __restrict__ arg,
-                                                    float* __restrict__ dx, int64_t ldx, int lg) {
-  const int rows = kBlock >> lg;  // per block and step
-  const int64_t n0 = (int64_t)blockIdx.x * (kGradNodes * rows) + (threadIdx.x >> lg);
-  const int sub = (int)threadIdx.x & ((1 << lg) - 1);
+                                                    float* __restrict__ dx, int64_t ldx, int lpr, int lg,
+                                                    int rows) {
+  // (lg: log2 of lpr, or -1; rows: per block and step)
+  const int r = lg >= 0 ? (int)threadIdx.x >> lg : (int)threadIdx.x / lpr;
+  const int sub = (int)threadIdx.x - r * lpr;
+  if (r >= rows) return;
+  const int64_t n0 = (int64_t)blockIdx.x * (kGradNodes * rows) + r;
   int64_t g[kGradNodes];
   float cnt[kGradNodes];
 #pragma unroll
@@ -220,7 +223,7 @@ __global__ __launch_bounds__(kBlock) void pool_grad(const float* __restrict__ dy
 #pragma unroll
   for (int u = 0; u < kGradNodes; ++u)
     cnt[u] = reduce == TFG_MEAN && g[u] >= 0 ? (float)(goff[g[u] + 1] - goff[g[u]]) : 1.0f;
-  for (int fw = sub * V; fw < F; fw += V << lg) {
+  for (int fw = sub * V; fw < F; fw += V * lpr) {
     const int f = min(fw, F - V);
     float v[kGradNodes][V];
 #pragma unroll
@@ -260,15 +263,25 @@ void launch_pool_grad(const float* dy, int64_t G, int F, const void* gi, int64_t
                       const int* goff, int reduce, const int* arg, float* dx, int64_t ldx,
                       hipStream_t s) {
   const int vec = F >= 4 ? 4 : 1;
+  // threads per row: a power of two within a wavefront, else as many as it has
+  // vectors, whole rows side by side in a block (143,000 nodes of 300 columns: two
+  // passes of a wavefront 53 us, three rows of 75 threads 41)
+  const int lanes = (F + vec - 1) / vec;
   int lg = 0;
-  while (lg < 6 && (vec << lg) < F) ++lg;
-  const int64_t per = (int64_t)kGradNodes * (kBlock >> lg);
+  while (1 << lg < lanes && lg < 6) ++lg;
+  int lpr = 1 << lg;
+  if (lanes > kWave) {
+    lpr = std::min(lanes, kBlock);
+    lg = -1;
+  }
+  const int rows = kBlock / lpr;
+  const int64_t per = (int64_t)kGradNodes * rows;
   const unsigned nb = (unsigned)((Nb + per - 1) / per);
   const IdxT* g = static_cast<const IdxT*>(gi);
   if (vec == 4)
-    pool_grad<IdxT, 4><<<nb, kBlock, 0, s>>>(dy, G, F, g, Nb, goff, reduce, arg, dx, ldx, lg);
+    pool_grad<IdxT, 4><<<nb, kBlock, 0, s>>>(dy, G, F, g, Nb, goff, reduce, arg, dx, ldx, lpr, lg, rows);
   else
-    pool_grad<IdxT, 1><<<nb, kBlock, 0, s>>>(dy, G, F, g, Nb, goff, reduce, arg, dx, ldx, lg);
+    pool_grad<IdxT, 1><<<nb, kBlock, 0, s>>>(dy, G, F, g, Nb, goff, reduce, arg, dx, ldx, lpr, lg, rows);
 }
 
 // The segment bounds (err NULL: nobody reads the flag).
@@ -309,13 +322,20 @@ int launch_segment_pool(const float* x, int64_t Nb, int64_t F, int64_t ldx, cons
   if (err != nullptr) zero_ints<<<1, 64, 0, s>>>(err, 1);
   if (G == 0 || F == 0) return TFG_OK;
   if (int rc = launch_segment_bounds(graph_index, index_type, Nb, G, goff, err, s)) return rc;
-  // (maxima of odd widths one column per lane: 30,000 graphs of 63 columns 53 us, with
-  // four 61; sums 50 and 46)
-  const int vec = F >= 4 && !(reduce == TFG_MAX && F % 2 != 0) ? 4 : 1;
-  int lanes = (int)std::min<int64_t>((F + vec - 1) / vec, kWave);
-  int p2 = 1;
-  while (p2 < lanes) p2 <<= 1;
-  const int slots = std::min(kWave / p2, 16);
+  // Four columns a lane, any width; but where rows are no whole vectors of four, one
+  // for sums of few nodes (200,000 graphs of 3 nodes, 31 columns: 55 us, with four 66),
+  // for maxima of odd widths (30,000 graphs of 63 columns 53 us, with four 61), and for
+  // maxima of even ones unless a graph's nodes fill its slots a few times (3 nodes of 30
+  // columns 84 us, with four 181; 10,000 nodes 479 and 197)
+  const auto slots_of = [&](int v) {
+    const int lanes = (int)std::min<int64_t>((F + v - 1) / v, kWave);
+    int p2 = 1;
+    while (p2 < lanes) p2 <<= 1;
+    return std::min(kWave / p2, 16);
+  };
+  int vec = F >= 4 ? 4 : 1;
+  if (F % 4 != 0 && (reduce != TFG_MAX ? Nb < 16 * G : F % 2 != 0 || Nb < 32 * slots_of(4) * G)) vec = 1;
+  const int slots = slots_of(vec);
   dim3 grid((unsigned)((G + kItemBlock / kWave - 1) / (kItemBlock / kWave)));
   if (reduce == TFG_MAX)
     launch_pool_vec<true>(vec, slots, grid, s, x, ldx, (int)F, goff, G, Nb, 0, out, argmax);

@@ -9,13 +9,15 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("F", [1, 2, 3, 4, 5, 7, 8, 15, 17, 31, 33, 63, 65, 130, 255, 257, 300])
+@pytest.mark.parametrize("F", [1, 2, 3, 4, 5, 7, 8, 15, 17, 30, 31, 33, 62, 63, 65, 130, 255, 256,
+                               257, 300, 500, 602, 1030])
+@pytest.mark.parametrize("most", [40, 5])  # nodes: four columns a lane, and one where F % 4 != 0
 @pytest.mark.parametrize("dtype", [np.int32, np.int64])
-def test_pool_widths(F, dtype):
+def test_pool_widths(F, most, dtype):
     import paper_2101_11552_amd as tfg
     tfg.load()
     r = np.random.default_rng(F)
-    sizes = np.concatenate([[0, 0], r.integers(0, 40, 60), [1, 200, 0]])
+    sizes = np.concatenate([[0, 0], r.integers(0, most, 60), [1, 5 * most, 0]])
     G, Nb = sizes.size, int(sizes.sum())
     gi = np.repeat(np.arange(G), sizes).astype(dtype)
     wide = torch.from_numpy(r.standard_normal((Nb, F + 1)).astype(np.float32)).cuda()
