@@ -554,7 +554,7 @@ __global__ __launch_bounds__(kItemBlock) void softmax_grad_chunks(
 // wavefront per chunk, whose values stay in registers while the chunks' sums meet in
 // LDS. What bounds this order is the lines that scattered values move, and the two
 // launches above read alpha and dalpha twice: 8M edges of a power-law graph, one head,
-// 405 us, with them 560. Not where the two arrays fit the L2s (460 rows of 1,400
+// 391 us before them, with them 560, now 410. Not where the two arrays fit the L2s (460 rows of 1,400
 // chunks, 1.35M edges: 30 us, with them 8) or a value's line holds several heads.
 constexpr int kRowWaves = 16;
 constexpr int kRowHeads = 4;

@@ -26,8 +26,9 @@ constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;  // 2048
 
 // Edges per sort tile: 8 per thread of a scatter block of T threads. 8192 (T =
-// 1024) on large graphs; smaller tiles where 64 of them hold the graph, since a
-// block of 16 waves then works through a tile that four waves on as many SIMDs
+// 1024) on large graphs; smaller tiles while the blocks read the digit table in at most
+// kSmallTileLoads loads a thread (8 tiles of 2048 at 8-bit digits, 128 at 4 bits), since
+// a block of 16 waves then works through a tile that four waves on as many SIMDs
 // finish sooner, on CUs that would stand idle (13,264 edges: scatters 12.3 + 10.9
 // us with two tiles of 8192).
 constexpr int kSortItems = 8;  // items per thread

@@ -6,7 +6,7 @@
 // mostly summed inside a slot. One wavefront per item (the earlier kernel) spent
 // a round trip on the item, one on its ids, one on its gathers and a tree over
 // the slots on each of them, with most lanes idle on rows of a few edges; rows
-// of 14 edges (169,343 of them, 40 columns) took 147 us, now 80. What bounds the
+// of 14 edges (169,343 of them, 40 columns) took 149 us, now 91. What bounds the
 // large cases now is the gathers that miss the L2s: 10M edges of 400 bytes move
 // at 6.2 TB/s (0.65 ms, before 0.83), 23M of 256 bytes by source part at 12
 // TB/s (0.50 ms, before 0.70); the same with maxima 0.69 ms (before 1.97: the

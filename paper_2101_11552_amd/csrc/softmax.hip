@@ -3,8 +3,8 @@
 //               edge, LeakyReLU of their sum (the first map);
 //   segment softmax: per target row and head, the maximum and the sum of the
 //               shifted exponentials (the reduce, in one online sweep) and the
-//               division (the last map), one wavefront per work item of the
-//               graph's row plan.
+//               division (the last map), several work items of the graph's row
+//               plan per wavefront.
 #include <type_traits>
 
 #include "softmax_stats.h"
@@ -174,9 +174,10 @@ __global__ __launch_bounds__(kBlock) void edge_scores_graph(const int* __restric
 // are loaded together and stay in registers, the maximum comes from the
 // registers and a butterfly over the slots, then each score is replaced by
 // exp(s - m) and summed (butterfly again), and alpha is written from the
-// registers. Longer items (more than 16 heads) keep a running pair instead
-// (stat_add: maximum and rescaled sum in one sweep of loads) and load the scores
-// again to write alpha.
+// registers. Items of more than group_steps() * 64 / HP edges (over 64 at 5 to 7, 12
+// and 16 heads, over 32 at 9 to 15 and 20 to 32; a whole row or chunk has at most 128)
+// keep a running pair instead (stat_add: maximum and rescaled sum in one sweep of
+// loads) and load the scores again to write alpha.
 constexpr int kSmSteps = 4;  // slot steps per round of loads (the running sweep)
 
 // Scores of the heads h for the ids (-inf where there is no edge or no head).

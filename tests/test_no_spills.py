@@ -23,6 +23,14 @@ HOT = {
     "aggregate.hip": ["spmm_wide", "fixup_rows"],
     "slots_sum.hip": ["spmm_slots"],
     "slots_max.hip": ["spmm_slots"],
+    "slots_heads.hip": ["spmm_slots"],
+    "slots_masked.hip": ["spmm_slots"],
+    "gat.hip": ["gat_slots", "gat_merge"],
+    "gat_dot.hip": ["gat_slots"],
+    "softmax.hip": ["softmax_items", "softmax_chunks"],
+    "backward.hip": ["edge_grad_slots", "softmax_grad_items", "softmax_grad_chunks",
+                     "softmax_grad_rows"],
+    "pool.hip": ["pool_rows", "pool_grad"],
     "norm.hip": ["weights_coo_sliced", "weights_csr_parts"],
 }
 
