@@ -18,12 +18,12 @@
 // numerators); whole rows write out = acc / d, chunks of long rows and the (row,
 // source part) segments of the part plan write their triples, which gat_merge
 // combines. By source part the gathered rows stay near the L2s. 114.6M edges of a
-// power-law graph, 8 heads of 8: 4.17 + 0.26 (merge) -> 2.77 + 0.23 ms; the row
+// power-law graph, 8 heads of 8: 4.17 + 0.26 (merge) -> 2.81 + 0.24 ms; the row
 // sums alone take 1.92, the rest is this kernel's arithmetic at five wavefronts a
-// SIMD (88 to 92 registers; held to 80 or 72 it spills, 2.95 and 3.83 ms; eight
+// SIMD (84 to 94 registers with V = 4; held to 80 or 72 it spills, 2.95 and 3.83 ms; eight
 // rows in flight, 104 registers, 3.00). 23M edges, 8 heads of 16, dot product:
 // 3.07 -> 2.31. 1.2M edges, 8 heads of 16, rows of 7 on
-// average: 100 + 84 (a kernel for the short rows) + 35 -> 127 + 10 us.
+// average: 100 + 84 (a kernel for the short rows) + 35 -> 125 + 10 us.
 #pragma once
 
 #include "gat_shape.h"

@@ -8,8 +8,8 @@
 // the slots on each of them, with most lanes idle on rows of a few edges; rows
 // of 14 edges (169,343 of them, 40 columns) took 149 us, now 91. What bounds the
 // large cases now is the gathers that miss the L2s: 10M edges of 400 bytes move
-// at 6.2 TB/s (0.65 ms, before 0.83), 23M of 256 bytes by source part at 12
-// TB/s (0.50 ms, before 0.70); the same with maxima 0.69 ms (before 1.97: the
+// at 6.6 TB/s (0.61 ms, before 0.83), 23M of 256 bytes by source part at 12
+// TB/s (0.50 ms, before 0.70); the same with maxima 0.55 ms (before 1.97: the
 // comparison with its tie rule was the bound, and is now three operations per
 // column, since ids ascend along an item of one source part).
 //
