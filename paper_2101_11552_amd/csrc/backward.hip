@@ -550,12 +550,47 @@ __global__ __launch_bounds__(kItemBlock) void softmax_grad_chunks(
   }
 }
 
+// A row of more than kGiantChunks chunks by a block of `waves` wavefronts: the sums
+// added once per wavefront, and wavefront w writes chunks w, w + waves, ...
+__device__ __forceinline__ void grad_giant_row(const SplitRow& sr, int w, int waves,
+                                               const int* __restrict__ rowptr, int chunk,
+                                               const int* __restrict__ perm,
+                                               const float* __restrict__ alpha,
+                                               const float* __restrict__ da, int H, int HP,
+                                               const double* __restrict__ pdot,
+                                               float* __restrict__ ds) {
+  const int rb = uniform(rowptr[sr.row]), re = uniform(rowptr[sr.row + 1]);
+  const int SL = kWave >> log2_of(HP), slot = lane_id() >> log2_of(HP), hh = lane_id() & (HP - 1);
+  for (int hb = 0; hb < H; hb += HP) {
+    const int h = hb + hh;
+    const bool act = h < H;
+    const double dot = row_dot(pdot + (int64_t)sr.slot0 * H + h, sr.nchunks, H, act, slot, SL, HP);
+    for (int c = w; c < sr.nchunks; c += waves) {
+      const int kb = rb + c * chunk, ke = min(re, kb + chunk);
+      grad_sweep_write(perm, alpha, da, H, h, act, kb, ke, slot, SL, dot, ds);
+    }
+  }
+}
+
+__global__ __launch_bounds__(kGiantWaves * kWave) void softmax_grad_giant(
+    const SplitRow* __restrict__ split, const int* __restrict__ rowptr, int chunk,
+    const int* __restrict__ perm, const float* __restrict__ alpha, const float* __restrict__ da,
+    int H, int HP, const double* __restrict__ pdot, float* __restrict__ ds) {
+  const SplitRow sr = split[blockIdx.x];
+  if (sr.nchunks <= kGiantChunks) return;
+  const int w = uniform((int)threadIdx.x / kWave);
+  grad_giant_row(sr, w, kGiantWaves, rowptr, chunk, perm, alpha, da, H, HP, pdot, ds);
+}
+
 // Split rows of at most kRowWaves chunks in the caller's order, one block each and a
 // wavefront per chunk, whose values stay in registers while the chunks' sums meet in
 // LDS. What bounds this order is the lines that scattered values move, and the two
 // launches above read alpha and dalpha twice: 8M edges of a power-law graph, one head,
-// 391 us before them, with them 560, now 410. Not where the two arrays fit the L2s (460 rows of 1,400
-// chunks, 1.35M edges: 30 us, with them 8) or a value's line holds several heads.
+// 404 us before them, with them 561, now 400. Not where the two arrays fit the L2s (460
+// rows of 1,400 chunks, 1.35M edges: 30 us, with them 8) or a value's line holds several
+// heads. Two blocks share a CU (58 registers; with 70 one block, whose wavefronts past
+// the row's chunks leave it idle: 4 heads, 398 us, now 302). The longest rows go in the
+// same launch: one more of as many blocks costs 12 us where it finds nothing to do.
 constexpr int kRowWaves = 16;
 constexpr int kRowHeads = 4;
 constexpr int kRowSteps = 8;  // values a lane holds
@@ -583,42 +618,24 @@ __device__ __forceinline__ void grad_row(const int* __restrict__ perm,
   for (int c = 0; c < nch; ++c) total[0] += sums[c][h];
   grad_write<NST, 1>(a, g, e, total, H, h, h < H, ds);
 }
-__global__ __launch_bounds__(kRowWaves * kWave) void softmax_grad_rows(
+__global__ __launch_bounds__(kRowWaves * kWave, 8) void softmax_grad_rows(
     const SplitRow* __restrict__ split, const int* __restrict__ rowptr, int chunk,
     const int* __restrict__ perm, const float* __restrict__ alpha, const float* __restrict__ da,
-    int H, int HP, float* __restrict__ ds) {
+    int H, int HP, const double* __restrict__ pdot, float* __restrict__ ds) {
   __shared__ double sums[kRowWaves][kRowHeads];
   const SplitRow sr = split[blockIdx.x];
-  if (sr.nchunks > kRowWaves) return;  // uniform
   const int re = uniform(rowptr[sr.row + 1]), w = uniform((int)threadIdx.x / kWave);
+  if (sr.nchunks > kRowWaves) {  // uniform
+    if (sr.nchunks > kGiantChunks)
+      grad_giant_row(sr, w, kRowWaves, rowptr, chunk, perm, alpha, da, H, HP, pdot, ds);
+    return;
+  }
   // (wavefronts past the row's chunks hold no edges)
   const int kb = min(re, uniform(rowptr[sr.row]) + w * chunk), ke = min(re, kb + chunk);
   const int steps = chunk * HP;  // of a whole chunk, times the wavefront
   if (steps <= 2 * kWave) grad_row<2>(perm, alpha, da, H, HP, kb, ke, sr.nchunks, w, sums, ds);
   else if (steps <= 4 * kWave) grad_row<4>(perm, alpha, da, H, HP, kb, ke, sr.nchunks, w, sums, ds);
   else grad_row<kRowSteps>(perm, alpha, da, H, HP, kb, ke, sr.nchunks, w, sums, ds);
-}
-
-// Rows of more than kGiantChunks chunks: the sums added once per wavefront of
-// the row's block, and wavefront w writes chunks w, w + kGiantWaves, ...
-__global__ __launch_bounds__(kGiantWaves * kWave) void softmax_grad_giant(
-    const SplitRow* __restrict__ split, const int* __restrict__ rowptr, int chunk,
-    const int* __restrict__ perm, const float* __restrict__ alpha, const float* __restrict__ da,
-    int H, int HP, const double* __restrict__ pdot, float* __restrict__ ds) {
-  const SplitRow sr = split[blockIdx.x];
-  if (sr.nchunks <= kGiantChunks) return;
-  const int rb = uniform(rowptr[sr.row]), re = uniform(rowptr[sr.row + 1]);
-  const int w = uniform((int)threadIdx.x / kWave);
-  const int SL = kWave >> log2_of(HP), slot = lane_id() >> log2_of(HP), hh = lane_id() & (HP - 1);
-  for (int hb = 0; hb < H; hb += HP) {
-    const int h = hb + hh;
-    const bool act = h < H;
-    const double dot = row_dot(pdot + (int64_t)sr.slot0 * H + h, sr.nchunks, H, act, slot, SL, HP);
-    for (int c = w; c < sr.nchunks; c += kGiantWaves) {
-      const int kb = rb + c * chunk, ke = min(re, kb + chunk);
-      grad_sweep_write(perm, alpha, da, H, h, act, kb, ke, slot, SL, dot, ds);
-    }
-  }
 }
 
 template <int MODE>
@@ -855,10 +872,9 @@ int launch_segment_softmax_backward(const Graph& g, const float* alpha, const fl
   if (rc) return rc;
   if (fewer > 0) {
     softmax_grad_rows<<<(unsigned)g.n_split, kRowWaves * kWave, 0, s>>>(
-        g.split, g.rowptr, g.chunk, perm, alpha, dalpha, H, hp, ds);
+        g.split, g.rowptr, g.chunk, perm, alpha, dalpha, H, hp, pdot, ds);
     TFG_LAUNCHED("softmax_grad_rows");
-  }
-  if (g.n_heavy > kGiantChunks) {
+  } else if (g.n_heavy > kGiantChunks) {
     softmax_grad_giant<<<(unsigned)g.n_split, kGiantWaves * kWave, 0, s>>>(
         g.split, g.rowptr, g.chunk, perm, alpha, dalpha, H, hp, pdot, ds);
     TFG_LAUNCHED("softmax_grad_giant");

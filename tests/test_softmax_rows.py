@@ -96,12 +96,10 @@ def test_rows_from_registers_are_as_exact_as_swept_ones(tfg, n):
     assert _alpha_error(tfg, n, 8) <= 1.02 * _alpha_error(tfg, n, 5)
 
 
-@pytest.mark.parametrize("H,E", [(1, 4_200_000), (2, 2_100_000), (3, 1_400_001), (4, 1_050_000)])
-def test_gradient_of_split_rows_in_edge_order(tfg, H, E):
-    """Arrays beyond the L2s in the caller's order: split rows of up to 16 chunks by a block each,
-    of more by the chunk launches, against the graph order (the same products, added in double)."""
+def _check_edge_order_gradient(tfg, H, E, hubs):
+    """Rows of the given lengths among E edges: the gradient in the caller's order against the
+    graph order (the same products, added in double)."""
     r = np.random.default_rng([15, H])
-    hubs = [129, 256, 257, 15 * 128, 16 * 128, 16 * 128 + 1, 17 * 128, 9000]
     n = 20_000
     tgt = np.concatenate([np.repeat(np.arange(len(hubs)), hubs),
                           r.integers(len(hubs), n, E - sum(hubs) - 600),
@@ -115,3 +113,17 @@ def test_gradient_of_split_rows_in_edge_order(tfg, H, E):
     want = tfg.tfg_segment_softmax_graph_backward(g, move(al), move(da))
     scale = move(al) * (move(da).abs() + 4)
     assert float(((move(ds) - want).abs() / scale).max()) <= 2 ** -23
+
+
+@pytest.mark.parametrize("H,E", [(1, 4_200_000), (2, 2_100_000), (3, 1_400_001), (4, 1_050_000)])
+def test_gradient_of_split_rows_in_edge_order(tfg, H, E):
+    """Arrays beyond the L2s in the caller's order: split rows of up to 16 chunks by a block each,
+    of more by the chunk launches."""
+    hubs = [129, 256, 257, 15 * 128, 16 * 128, 16 * 128 + 1, 17 * 128, 9000]
+    _check_edge_order_gradient(tfg, H, E, hubs)
+
+
+@pytest.mark.parametrize("H,E", [(1, 4_200_000), (4, 1_050_000)])
+def test_gradient_of_giant_rows_in_edge_order(tfg, H, E):
+    """Beside them, rows of 2,048 chunks (by the chunk launch) and of more (by a block each)."""
+    _check_edge_order_gradient(tfg, H, E, [257, 2048 * 128, 2048 * 128 + 1])
